@@ -86,17 +86,15 @@ __device__ __forceinline__ void tile_of_pid(int pid, int tiles_m, int tiles_n, i
   const int group = pid / per_group, in_group = pid - group * per_group;
   const int first_m = group * kGroupM;
   const int gm = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-  *tm = first_m + in_group % gm;
-  *tn = in_group / gm;
-}
-
-__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int *tm, int *tn) {
-  tile_of_pid(logical_block(), tiles_m, tiles_n, tm, tn);
+  // (the divisions run on the vector unit; what follows from the tile's place belongs in scalar registers)
+  *tm = __builtin_amdgcn_readfirstlane(first_m + in_group % gm);
+  *tn = __builtin_amdgcn_readfirstlane(in_group / gm);
 }
 
 // Accumulator layout of one wave: acc[bm][bn][i] is C[m][n] with
 //   m = m_base + 16*bm + l16,  n = n_base + 16*bn + 4*q + i        (l16 = lane % 16, q = lane / 16).
-// No bounds checks: the caller's tile is full.
+// Outside the matrix the load repeats the last row / column group (the values are never stored) and the store does
+// nothing; N is a multiple of 8 and n of 4, so the 4 columns are in or out together.
 template <int MB, int NB>
 __device__ __forceinline__ void load_acc_tile(const GemmParams &p, f32x4 (&acc)[MB][NB], int m_base, int n_base,
                                               int l16, int q) {
@@ -104,7 +102,8 @@ __device__ __forceinline__ void load_acc_tile(const GemmParams &p, f32x4 (&acc)[
   for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
     for (int bn = 0; bn < NB; ++bn) {
-      const float *src = p.acc_in + static_cast<int64_t>(m_base + bm * 16 + l16) * p.ld_acc + n_base + bn * 16 + 4 * q;
+      const int m = m_base + bm * 16 + l16, n = n_base + bn * 16 + 4 * q;
+      const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < p.N ? n : p.N - 4);
       const float4 c = *reinterpret_cast<const float4 *>(src);
       acc[bm][bn][0] = c.x;
       acc[bm][bn][1] = c.y;
@@ -142,14 +141,25 @@ __device__ __forceinline__ void store_acc4(const GemmParams &p, f32x4 c, int m, 
   store_global8(dst, o);
 }
 
+// plane_row: added to the row where the tile is stored (launches that run parts of the reduction), not to the bound.
 template <int MB, int NB, int kEpi>
 __device__ __forceinline__ void store_acc_tile(const GemmParams &p, const f32x4 (&acc)[MB][NB], int m_base, int n_base,
-                                               int l16, int q, uint16_t *const *s_tab) {
+                                               int plane_row, int l16, int q, uint16_t *const *s_tab) {
+  if (m_base + MB * 16 <= p.M && n_base + NB * 16 <= p.N) {  // (the whole wave tile is inside: no test per store)
+#pragma unroll
+    for (int bm = 0; bm < MB; ++bm)
+#pragma unroll
+      for (int bn = 0; bn < NB; ++bn)
+        store_acc4<kEpi>(p, acc[bm][bn], plane_row + m_base + bm * 16 + l16, n_base + bn * 16 + 4 * q, s_tab);
+    return;
+  }
 #pragma unroll
   for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
-    for (int bn = 0; bn < NB; ++bn)
-      store_acc4<kEpi>(p, acc[bm][bn], m_base + bm * 16 + l16, n_base + bn * 16 + 4 * q, s_tab);
+    for (int bn = 0; bn < NB; ++bn) {
+      const int m = m_base + bm * 16 + l16, n = n_base + bn * 16 + 4 * q;
+      if (m < p.M && n < p.N) store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
+    }
 }
 
 }  // namespace

@@ -16,26 +16,14 @@
 // Same MFMA sequence per output element as every other GEMM kernel of the library (K ascending in steps of 32,
 // v_mfma_f32_16x16x32_bf16, the same lane -> k map), so the result bits are the same.
 //
-// Needs M % 256 == 0, N % 256 == 0, K % 64 == 0, K >= 192 (k_split % 64 == 0, n_split % 256 == 0); no bounds checks.
+// Any M and N, K > 128 (k_split % 64 == 0, n_split % 256 == 0): edges are handled by the range check of the operand
+// loads and guarded stores (OperandSource in gemm_dma.h).
 #pragma once
-#include <utility>
-
 #include "gemm_common.h"
 #include "gemm_dma.h"
 
 namespace osdp {
 namespace {
-
-// f(Int<0>{}), f(Int<1>{}), ..., f(Int<N-1>{}): a loop whose index is a compile-time constant in every iteration, so
-// that register arrays are never indexed at run time and nothing depends on the optimiser's unrolling.
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>) {
-  (f(Int<Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
-}
 
 // The matrix-core step with its accumulator pinned to AGPRs and updated in place.  Written as inline assembly
 // because the compiler, left to place 256 accumulator registers itself, keeps moving them between the two halves of
@@ -46,26 +34,6 @@ __device__ __forceinline__ void static_for(F &&f) {
 // to those the other chose, with VALU moves it does not know to keep clear of the MFMAs.
 __device__ __forceinline__ void mma_16x16x32_agpr(f32x4 &c, bf16x8 a_rows, bf16x8 b_cols) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_cols), "v"(a_rows));
-}
-
-// A wave-level direct-to-LDS load that is issued with all lanes off when `on` is 0 (it then moves nothing): the loads
-// of K blocks beyond the last, which the uniform K loop below would otherwise fetch for nobody.  All 64 lanes are
-// active wherever the kernel calls this, so EXEC is put back to all ones.
-// The source is a byte address common to the wave (in scalar registers) plus a 32-bit byte offset per lane: the 16
-// loads of a K block then share two lane offsets that never change, and moving on to the next block is scalar
-// arithmetic, where per-lane 64-bit pointers cost 32 registers and a vector add each per block.
-__device__ __forceinline__ void dma16_if(uint32_t on, uint64_t base, uint32_t lane_off, uint32_t dst) {  // on: 0 or 0xffffffff
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane(dst), half = __builtin_amdgcn_readfirstlane(on);
-  asm volatile("s_mov_b32 exec_lo, %0\n\ts_mov_b32 exec_hi, %0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, -1"
-               ::"s"(half), "s"(m0), "v"(lane_off), "s"(base) : "memory");
-}
-
-// A 64-bit value that is the same in every lane, as the compiler can see.
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
-  return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
 // One operand's share of a ring slot: 256 rows (or columns) x 64 k, 32 KB, filled by 32 wave-level
@@ -91,10 +59,15 @@ struct W4Operand {
       return static_cast<int64_t>(krow) * ld + (((lane % 32) * 8) ^ Base::swz_mn(krow));
     }
   }
-  static __device__ __forceinline__ constexpr int load_rows(int p) {
-    return kKC ? (chunk(0, p) - chunk(0, 0)) * 8 : (chunk(0, p) - chunk(0, 0)) * 2;
+  static __device__ __forceinline__ int lane_pos(int w, int lane) {  // k (K-contiguous) or mn of those 16 bytes
+    return kKC ? ((lane % 8) ^ Base::swz_k(chunk(w, 0) * 8 + lane / 8)) * 8
+               : ((lane % 32) * 8) ^ Base::swz_mn(chunk(w, 0) * 2 + lane / 32);
   }
-  static __device__ __forceinline__ int64_t block_stride(int64_t ld) { return kKC ? kBK : static_cast<int64_t>(kBK) * ld; }
+  static __device__ __forceinline__ constexpr int first_chunk(int w) { return chunk(w, 0); }
+  static __device__ __forceinline__ constexpr int chunk_step(int p) { return chunk(0, p) - chunk(0, 0); }
+  static __device__ __forceinline__ constexpr int load_rows(int p) {
+    return chunk_step(p) * (kKC ? 8 : 2);
+  }
   static __device__ __forceinline__ bf16x8 frag(const uint16_t *slot, int mn0, int kk, int lane) { return Base::frag(slot, mn0, kk, lane); }
 };
 
@@ -177,9 +150,9 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
   int64_t k0 = 0;    // first k of this workgroup's part
   int plane_row = 0;  // its plane starts at this row of C (the planes lie one below the other: ldc = N)
   if (p.k_parts > 1) {
-    const int tiles = tiles_m * tiles_n, part = pid / tiles;
+    const int tiles = tiles_m * tiles_n, part = __builtin_amdgcn_readfirstlane(pid / tiles);
     pid -= part * tiles;
-    K = p.K / p.k_parts;
+    K = __builtin_amdgcn_readfirstlane(p.K / p.k_parts);
     k0 = static_cast<int64_t>(part) * K;
     plane_row = part * p.M;
   }
@@ -189,23 +162,9 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
   const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
   const int l16 = lane & 15, q4 = lane >> 4;
 
-  const bool second = p.n_split && n0 >= p.n_split;
-  const uint16_t *baseB = second ? p.B2 : p.B;
-  const int64_t ldb = second ? p.ldb2 : p.ldb;
-  const int nB = second ? n0 - p.n_split : n0;
-  // Source of load i of an operand's current K block: byte address blockX + rowX(i), the same for the whole wave,
-  // plus this lane's byte offset laneX (all offsets inside a 256-row block are far below 2^32 bytes).
-  uint64_t blockA = uniform64(reinterpret_cast<uint64_t>(kAK ? p.A + static_cast<int64_t>(m0) * p.lda + k0 : p.A + m0 + k0 * p.lda));
-  uint64_t blockB = uniform64(reinterpret_cast<uint64_t>(kBKc ? baseB + static_cast<int64_t>(nB) * ldb + k0 : baseB + nB + k0 * ldb));
-  const uint32_t laneA = static_cast<uint32_t>(OpA::lane_src(wave, lane, p.lda) * 2);
-  uint32_t laneB = static_cast<uint32_t>(OpB::lane_src(wave, lane, ldb) * 2);
-  auto rowA = [&](int i) { return static_cast<uint64_t>(OpA::load_rows(i)) * static_cast<uint64_t>(p.lda) * 2; };
-  int64_t ldb_cur = ldb;
-  auto rowB = [&](int i) { return static_cast<uint64_t>(OpB::load_rows(i)) * static_cast<uint64_t>(ldb_cur) * 2; };
-  const int64_t stepA = OpA::block_stride(p.lda);
-  int64_t stepB = OpB::block_stride(ldb);
-  const int nb = K / 64;
-  int first_seg = p.k_split ? p.k_split / 64 : nb;
+  TileSource<OpA, OpB, kAK, kBKc, BM, BN, 64> src;
+  src.begin(p, m0, n0, k0, K, wave, lane);
+  const int nb = src.nb;
 
   f32x4 acc[MB][NB];
   if (kAccIn) {
@@ -220,41 +179,23 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
   }
 
   const uint32_t lds_base = lds_address(smem);
-  uint32_t dstA[OpA::kLoads], dstB[OpB::kLoads];
-#pragma unroll
-  for (int i = 0; i < OpA::kLoads; ++i) dstA[i] = OpA::chunk(wave, i) * 1024;
-#pragma unroll
-  for (int i = 0; i < OpB::kLoads; ++i) dstB[i] = OpA::kElems * 2 + OpB::chunk(wave, i) * 1024;
+  const uint32_t dstA = lds_base + OpA::first_chunk(wave) * 1024;
+  const uint32_t dstB = lds_base + OpA::kElems * 2 + OpB::first_chunk(wave) * 1024;
 
-  uint32_t load_mask = ~0u;  // all lanes while there are K blocks left to load, none afterwards
-  auto issue = [&](int slot, auto idx, int64_t advA, int64_t advB) {
+  // load i of the block that the sources stand at, into `slot`; after the last one they move on to the next block
+  // (beyond the last block they deliver zeros that nobody uses)
+  auto issue = [&](int slot, auto idx) {
     constexpr int i = decltype(idx)::value;
-    const uint32_t sb = lds_base + slot * (kSlotElems * 2);
-    if constexpr (i < OpA::kLoads) {
-      dma16_if(load_mask, blockA + rowA(i), laneA, sb + dstA[i]);
-      if constexpr (i == OpA::kLoads - 1) blockA += static_cast<uint64_t>(advA) * 2;  // on to the next K block
-    } else {
-      constexpr int j = i - OpA::kLoads;
-      dma16_if(load_mask, blockB + rowB(j), laneB, sb + dstB[j]);
-      if constexpr (j == OpB::kLoads - 1) blockB += static_cast<uint64_t>(advB) * 2;
-    }
-  };
-  auto block_issued = [&]() {
-    if (p.k_split && --first_seg == 0) {  // B continues in its second K segment
-      blockB = uniform64(reinterpret_cast<uint64_t>(kBKc ? p.B2 + static_cast<int64_t>(n0) * p.ldb2 : p.B2 + n0));
-      laneB = static_cast<uint32_t>(OpB::lane_src(wave, lane, p.ldb2) * 2);
-      ldb_cur = p.ldb2;
-      stepB = OpB::block_stride(p.ldb2);
-    }
+    if constexpr (i < OpA::kLoads) src.a.template load<i>(dstA + slot * (kSlotElems * 2));
+    else src.b.template load<i - OpA::kLoads>(dstB + slot * (kSlotElems * 2));
+    if constexpr (i == L - 1) src.next(p, K, wave, lane);
   };
   bf16x8 fa[2][MB], fb[2][NB];
   asm volatile("s_nop 7");  // accumulator writes (VALU) settle before the first MFMA reads them
 
   // prologue: blocks 0 and 1 go in flight; block 0 is awaited and the fragments of its first K step read
-  static_for<L>([&](auto i) { issue(0, i, stepA, stepB); });
-  block_issued();
-  static_for<L>([&](auto i) { issue(1, i, stepA, stepB); });
-  block_issued();
+  static_for<L>([&](auto i) { issue(0, i); });
+  static_for<L>([&](auto i) { issue(1, i); });
   wait_vmcnt<L>();
   __builtin_amdgcn_s_barrier();
   if constexpr (kCopy) {  // piece 0 of the carried gather (the barrier has published the shard table)
@@ -271,7 +212,7 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
 
   // 64 MFMAs of one K step out of fragment set P; in their shadow the 16 fragment reads of the next K step
   // (slot rs, K step rk) into the other set and, when kLoad, the 16 loads of the block two ahead into slot ls.
-  auto kstep = [&](auto par, auto load_, const uint16_t *rs, int rk, int ls, int64_t advA, int64_t advB, bool advance) {
+  auto kstep = [&](auto par, auto load_, const uint16_t *rs, int rk, int ls) {
     constexpr int P = decltype(par)::value, Q = P ^ 1;
     constexpr bool kLoad = decltype(load_)::value != 0;
     const uint16_t *nA = rs, *nB = rs + OpA::kElems;
@@ -283,10 +224,7 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
         if constexpr (r < NB) fb[Q][r] = OpB::frag(nB, wn + r * 16, rk, lane);
         else fa[Q][r - NB] = OpA::frag(nA, wm + (r - NB) * 16, rk, lane);
       }
-      if constexpr (kLoad && i % 4 == 2) {
-        issue(ls, Int<i / 4>{}, advA, advB);
-        if (i / 4 == L - 1 && advance) block_issued();
-      }
+      if constexpr (kLoad && i % 4 == 2) issue(ls, Int<i / 4>{});
       // carried gather: in the block's first K step the address of the next piece is worked out; in the second,
       // just behind the barrier where every load has landed, the piece in registers goes out and the next comes in
       // (all three behind one uniform test: once the range is copied the remaining K blocks issue nothing for it)
@@ -307,23 +245,19 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
     });
   };
 
-  // Every block runs the same code: the last two blocks still issue their load instructions (with every lane off,
-  // see dma16_if) and the last still reads fragments nobody uses.  The host sends K >= 192.
+  // Every block runs the same code: the last two blocks still issue their load instructions (with every lane out of
+  // range) and the last still reads fragments nobody uses.  The host sends K > 128: three blocks or more.
   int cur = 0;
-  int ahead = 2;  // index of the block the source pointers stand at
   for (int b = 0; b < nb; ++b) {
     const uint16_t *sc = smem + cur * kSlotElems, *sn = smem + (cur ^ 1) * kSlotElems;
     // first K step; its shadow reads the second step's fragments of this block
-    kstep(Int<0>{}, Int<0>{}, sc, 1, 0, 0, 0, false);
+    kstep(Int<0>{}, Int<0>{}, sc, 1, 0);
     // block b is now fully in registers or consumed, and block b+1 must be in LDS
     wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    const bool advance = ahead + 1 < nb;
-    load_mask = ahead < nb ? ~0u : 0u;  // this step loads block `ahead`: there is none beyond nb - 1
-    kstep(Int<1>{}, Int<1>{}, sn, 0, cur, advance ? stepA : 0, advance ? stepB : 0, advance);
-    ahead += 1;
+    kstep(Int<1>{}, Int<1>{}, sn, 0, cur);
     cur ^= 1;
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
@@ -339,7 +273,7 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
 
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");
-  store_acc_tile<MB, NB, kEpi>(p, acc, plane_row + m0 + wm, n0 + wn, l16, q4, s_tab);
+  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, plane_row, l16, q4, s_tab);
 }
 
 }  // namespace

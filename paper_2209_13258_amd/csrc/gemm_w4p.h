@@ -11,8 +11,8 @@
 // acknowledgement.)
 //
 // Same tiles in the same order per XCD, same MFMA sequence per output element as every other GEMM kernel of the
-// library: same bits.  Takes what the plain kernel takes except a carried gather: M % 256 == 0, N % 256 == 0
-// (n_split % 256 == 0), K % 64 == 0 (k_split % 64 == 0), K >= 192 (per part, when the launch runs parts of the reduction).
+// library: same bits.  Takes what the plain kernel takes except a carried gather: any M and N (n_split % 256 == 0),
+// K > 128 (k_split % 64 == 0; per part, when the launch runs parts of the reduction).
 #pragma once
 #include "gemm_w4.h"
 
@@ -66,73 +66,39 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   const int part_tiles = tiles_m * tiles_n, tiles = part_tiles * parts, G = gridDim.x;
   const int first = logical_block();  // < tiles: the host launches at most one workgroup per tile
-  const int part_k = p.K / parts;
-  const int nb = part_k / 64;
-  const int my_tiles = (tiles - first + G - 1) / G;
+  const int part_k = __builtin_amdgcn_readfirstlane(p.K / parts);
+  const int nb = (part_k + 63) / 64;
+  const int my_tiles = __builtin_amdgcn_readfirstlane((tiles - first + G - 1) / G);
 
-  // ---- the load side: tile `lt`, its next block `lb`, the sources of that block ---------------------------
-  int lt = first, lb = 0;
-  uint64_t blockA = 0, blockB = 0;
-  uint32_t laneB = 0;
-  int64_t ldb_cur = p.ldb;
-  const uint32_t laneA = static_cast<uint32_t>(OpA::lane_src(wave, lane, p.lda) * 2);
-  const int64_t stepA = OpA::block_stride(p.lda);
-  int64_t stepB = 0;
-  auto rowA = [&](int i) { return static_cast<uint64_t>(OpA::load_rows(i)) * static_cast<uint64_t>(p.lda) * 2; };
-  auto rowB = [&](int i) { return static_cast<uint64_t>(OpB::load_rows(i)) * static_cast<uint64_t>(ldb_cur) * 2; };
-  int n0l = 0;  // first column of the tile being loaded
-  const int seg_blocks = p.k_split / 64;  // K blocks of B's first segment when B has two (0: one segment)
+  // ---- the load side: tile `lt` and the sources of its next block ------------------------------------------
+  int lt = first;
+  TileSource<OpA, OpB, kAK, kBKc, BM, BN, 64> src;
   auto load_tile = [&](int t) {  // point the sources at block 0 of tile t
     int tm, tn;
-    const int part = t / part_tiles;
+    const int part = __builtin_amdgcn_readfirstlane(t / part_tiles);
     tile_of_pid(t - part * part_tiles, tiles_m, tiles_n, &tm, &tn);
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int64_t k0 = static_cast<int64_t>(part) * part_k;
-    n0l = n0;
-    const bool second = p.n_split && n0 >= p.n_split;
-    const uint16_t *baseB = second ? p.B2 : p.B;
-    const int nB = second ? n0 - p.n_split : n0;
-    ldb_cur = second ? p.ldb2 : p.ldb;
-    blockA = uniform64(reinterpret_cast<uint64_t>(kAK ? p.A + static_cast<int64_t>(m0) * p.lda + k0 : p.A + m0 + k0 * p.lda));
-    blockB = uniform64(reinterpret_cast<uint64_t>(kBKc ? baseB + static_cast<int64_t>(nB) * ldb_cur + k0 : baseB + nB + k0 * ldb_cur));
-    laneB = static_cast<uint32_t>(OpB::lane_src(wave, lane, ldb_cur) * 2);
-    stepB = OpB::block_stride(ldb_cur);
+    src.begin(p, tm * BM, tn * BN, static_cast<int64_t>(part) * part_k, part_k, wave, lane);
   };
-  uint32_t load_mask = ~0u;  // all lanes while there are K blocks left to load, none afterwards
   auto block_issued = [&]() {  // after the last load of a block: on to the next block, of this tile or the next
-    if (++lb == nb) {
-      lb = 0;
+    if (src.block + 1 == nb && lt + G < tiles) {
       lt += G;
-      if (lt < tiles) load_tile(lt);
-      else load_mask = 0u;
+      load_tile(lt);
     } else {
-      blockA += static_cast<uint64_t>(stepA) * 2;
-      if (lb == seg_blocks) {  // B continues in its second K segment
-        ldb_cur = p.ldb2;
-        blockB = uniform64(reinterpret_cast<uint64_t>(kBKc ? p.B2 + static_cast<int64_t>(n0l) * ldb_cur : p.B2 + n0l));
-        laneB = static_cast<uint32_t>(OpB::lane_src(wave, lane, ldb_cur) * 2);
-        stepB = OpB::block_stride(ldb_cur);
-      } else {
-        blockB += static_cast<uint64_t>(stepB) * 2;
-      }
+      src.next(p, part_k, wave, lane);
     }
   };
 
   const uint32_t lds_base = lds_address(smem);
-  uint32_t dstA[OpA::kLoads], dstB[OpB::kLoads];
-#pragma unroll
-  for (int i = 0; i < OpA::kLoads; ++i) dstA[i] = OpA::chunk(wave, i) * 1024;
-#pragma unroll
-  for (int i = 0; i < OpB::kLoads; ++i) dstB[i] = OpA::kElems * 2 + OpB::chunk(wave, i) * 1024;
+  const uint32_t dstA = lds_base + OpA::first_chunk(wave) * 1024;
+  const uint32_t dstB = lds_base + OpA::kElems * 2 + OpB::first_chunk(wave) * 1024;
   auto issue = [&](int slot, auto idx) {
     constexpr int i = decltype(idx)::value;
-    const uint32_t sb = lds_base + slot * (kSlotElems * 2);
-    if constexpr (i < OpA::kLoads) dma16_if(load_mask, blockA + rowA(i), laneA, sb + dstA[i]);
-    else dma16_if(load_mask, blockB + rowB(i - OpA::kLoads), laneB, sb + dstB[i - OpA::kLoads]);
+    if constexpr (i < OpA::kLoads) src.a.template load<i>(dstA + slot * (kSlotElems * 2));
+    else src.b.template load<i - OpA::kLoads>(dstB + slot * (kSlotElems * 2));
   };
 
   // ---- the compute side: tile `ct`, its origin, its accumulators --------------------------------------------
-  int ct = first, cb = 0, m0c = 0, n0c = 0;
+  int ct = first, cb = 0, m0c = 0, n0c = 0, plane_row = 0;
   f32x4 acc[MB][NB];
 #pragma unroll
   for (int bm = 0; bm < MB; ++bm)
@@ -148,14 +114,16 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
   asm volatile("s_nop 1" : "+v"(zero));
   auto begin_tile = [&](int t, int l16e, int q4e) {
     int tm, tn;
-    const int part = t / part_tiles;
+    const int part = __builtin_amdgcn_readfirstlane(t / part_tiles);
     tile_of_pid(t - part * part_tiles, tiles_m, tiles_n, &tm, &tn);
-    m0c = tm * BM + part * p.M;  // (row of C: the part's plane starts at row part * M)
+    m0c = tm * BM;
     n0c = tn * BN;
+    plane_row = part * p.M;  // (the part's plane starts at this row of C)
     static_for<MB * NB>([&](auto idx) {
       constexpr int i = decltype(idx)::value, bn = i / MB, bm = i % MB;  // the order of the K loop's steps
       if constexpr (kAccIn) {
-        const float *src = p.acc_in + static_cast<int64_t>(m0c + wm + bm * 16 + l16e) * p.ld_acc + n0c + wn + bn * 16 + 4 * q4e;
+        const int m = m0c + wm + bm * 16 + l16e, n = n0c + wn + bn * 16 + 4 * q4e;
+        const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < p.N ? n : p.N - 4);
         acc_load(acc[bm][bn], src);
       } else {
         acc_clear(acc[bm][bn], zero);
@@ -205,7 +173,7 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
   };
 
   // One loop over all K blocks of all tiles of this workgroup; every block runs the same code.  Loads beyond the
-  // last block of the last tile are issued with every lane off, and the fragments read ahead at the very end
+  // last block of the last tile are issued with every lane out of range, and the fragments read ahead at the very end
   // are nobody's.
   int cur = 0;
   const int total = my_tiles * nb;
@@ -231,10 +199,13 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
       // the K loop's fragments out of their registers
       static_for<MB * NB>([&](auto idx) {
         constexpr int i = decltype(idx)::value, bm = i / NB, bn = i % NB;
-        if constexpr (kEpi == static_cast<int>(Epilogue::kF32Workspace))  // (stored straight from the accumulators)
-          store_acc4<kEpi>(p, acc[bm][bn], m0c + wm + bm * 16 + l16e, n0c + wn + bn * 16 + 4 * q4e, s_tab);
-        else
-          store_acc4<kEpi>(p, acc_read(acc[bm][bn]), m0c + wm + bm * 16 + l16e, n0c + wn + bn * 16 + 4 * q4e, s_tab);
+        const int m = m0c + wm + bm * 16 + l16e, n = n0c + wn + bn * 16 + 4 * q4e;
+        if (m < p.M && n < p.N) {
+          if constexpr (kEpi == static_cast<int>(Epilogue::kF32Workspace))  // (stored straight from the accumulators)
+            store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
+          else
+            store_acc4<kEpi>(p, acc_read(acc[bm][bn]), plane_row + m, n, s_tab);
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
       ct += G;

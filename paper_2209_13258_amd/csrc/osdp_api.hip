@@ -251,8 +251,8 @@ osdp_status resolve(const osdp_shape *shape, const osdp_plan *plan, int32_t op_i
   // needs a kernel that takes B in two segments.
   auto can_pair = [&](bool concat, int64_t j) {
     if (!r->dp[j] && !r->dp[j + 1]) return true;
-    return concat ? gemm_takes_two_column_segments(T, width(j), width(j + 1), D)
-                  : gemm_takes_two_segments(T, D, width(j), width(j + 1));
+    return concat ? gemm_takes_two_column_segments(width(j), width(j + 1), D)
+                  : gemm_takes_two_segments(width(j), width(j + 1));
   };
   const bool fwd_concat = !rows, bwd_concat = rows;
 

@@ -23,7 +23,8 @@ namespace {
 // Generic kernel: 128 x 128 x 32 tile, 4 waves of 64 x 64, single LDS buffer,
 // every access bounds-checked.  Handles any M, N and any K that is a multiple
 // of 8 (the tail of the last K block is zero-filled, which adds exact zeros);
-// K = 0 is the empty sum: it stores zeros (or acc_in) and reads neither operand.
+// K = 0 is the empty sum: it stores zeros (or acc_in) and reads neither operand.  It runs empty sums, leading
+// dimensions beyond the other kernels' 32-bit offsets, and whatever the tests compare with the other kernels.
 // ---------------------------------------------------------------------------
 constexpr int GBM = 128, GBN = 128, GBK = 32, GLDK = GBK + 8;
 
@@ -119,7 +120,12 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmParams p) {
   for (int k0 = k_begin; k0 < k_end; k0 += GBK) {
     uint4 va[2], vb[2];
     generic_load<kAK>(p.A, p.lda, p.M, m0, k0, k_end, va);
-    generic_load<kBK>(p.B, p.ldb, p.N, n0, k0, k_end, vb);
+    if (p.k_split && k0 >= p.k_split)       // B's second segment, by k or by column (both on tile and block boundaries)
+      generic_load<kBK>(p.B2, p.ldb2, p.N, n0, k0 - p.k_split, k_end - p.k_split, vb);
+    else if (p.n_split && n0 >= p.n_split)
+      generic_load<kBK>(p.B2, p.ldb2, p.N - p.n_split, n0 - p.n_split, k0, k_end, vb);
+    else
+      generic_load<kBK>(p.B, p.ldb, p.n_split ? p.n_split : p.N, n0, k0, p.k_split ? p.k_split : k_end, vb);
     __syncthreads();  // the previous block's LDS reads are done
     generic_store_lds<kAK>(As, va);
     generic_store_lds<kBK>(Bs, vb);
@@ -181,7 +187,7 @@ hipError_t launch_dma(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = p.M / BM, tiles_n = p.N / BN;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(kWaves * 64), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -196,7 +202,7 @@ hipError_t launch_w4(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = p.M / 256, tiles_n = p.N / 256;
+  const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -241,7 +247,7 @@ hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = p.M / 256, tiles_n = p.N / 256;
+  const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
   const int tiles = tiles_m * tiles_n * (p.k_parts > 1 ? p.k_parts : 1);
   hipLaunchKernelGGL(kernel, dim3(tiles < kCUs ? tiles : kCUs), dim3(256), lds, stream, p, tiles_m, tiles_n);
   t_persistent_launches += 1;
@@ -249,27 +255,32 @@ hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
 }
 
 constexpr int kShortK = 1024;
-constexpr int kW4MinK = 192;  // the four-wave kernel's K loop assumes at least three K blocks of 64
+constexpr int kW4MinK = 129;  // the four-wave kernel's K loop assumes at least three K blocks of 64
 constexpr int kW4MinKdW = 8192;
 
 // Estimated cost of covering M x N with BM x BN tiles on 256 CUs: tiles per CU times the tile's area, with a
 // penalty for the lower MFMA efficiency of smaller tiles.  Tiles that run two to a CU were measured in pairs; a
-// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  0 when the tile does not
-// divide the problem.
+// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  A tile that sticks out of the
+// matrix costs what a full one does.
+long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
+
 double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1) {
-  if (M % BM || N % BN) return 0.0;
-  const long tiles = static_cast<long>(M / BM) * (N / BN) * parts;
+  const long tiles = tile_count(M, N, BM, BN) * parts;
   const long per_cu = (tiles + kCUs - 1) / kCUs;
   const bool two_per_cu = BM * BN < 256 * 256;
   const double units = (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5 : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
 }
 
-bool fast_path(int M, int N, int K, int k_split, int n_split) {
+// The direct-to-LDS kernels take every size; a second segment of B must start on a K block or a tile column.
+bool fast_path(int K, int k_split, int n_split) {
   const bool generic = debug_options().gemm_generic.load(std::memory_order_relaxed) != 0;  // testing: the bounds-checked kernel
-  return !generic && M % 128 == 0 && N % 128 == 0 && K > 0 && K % 64 == 0 && k_split % 64 == 0 &&
-         n_split % 128 == 0;
+  return !generic && K > 0 && k_split % 64 == 0 && n_split % 128 == 0;
 }
+
+// Their lanes address an operand's tile with 32-bit byte offsets.
+constexpr int64_t kMaxLd = 1 << 22;
+bool fits_offsets(const GemmParams &p) { return p.lda < kMaxLd && p.ldb < kMaxLd && p.ldb2 < kMaxLd; }
 
 // Tile shapes of the unchecked kernel and their measured cost per unit of tile area relative to 256 x 256, for
 // the three operand layouts (forward, dW, dX).
@@ -297,7 +308,7 @@ constexpr TileShape kTiles[4] = {{256, 256, {1.0, 1.0, 1.0}},
 
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
 
-// Cheapest tile for M x N; a column split must fall on a tile boundary.  -1: none divides the problem.
+// Cheapest tile for M x N; a column split must fall on a tile boundary.
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
 int best_tile(int M, int N, int n_split, int kind, double *cost, int parts = 1) {
@@ -306,7 +317,7 @@ int best_tile(int M, int N, int n_split, int kind, double *cost, int parts = 1) 
   for (int i = 0; i < 4; ++i) {
     if (n_split % kTiles[i].bn) continue;
     const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts);
-    if (c > 0.0 && (best < 0 || c < best_cost)) {
+    if (best < 0 || c < best_cost) {
       best = i;
       best_cost = c;
     }
@@ -347,26 +358,21 @@ template <bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   constexpr int kind = layout_kind(kAK, kBK);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
-  if (fast_path(p.M, p.N, p.K / parts, p.k_split, p.n_split)) {
+  if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
     int best = best_tile(p.M, p.N, p.n_split, kind, nullptr, parts);
-    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 when it divides the problem
+    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 where it fits the segments of B
     const bool force = forced >= 0 && forced <= 3;
-    if (force) {
-      const TileShape &f = kTiles[forced];
-      if (p.M % f.bm == 0 && p.N % f.bn == 0 && p.n_split % f.bn == 0) best = forced;
-    }
+    if (force && p.n_split % kTiles[forced].bn == 0) best = forced;
     // A dX launch with a short reduction whose fp32 partial sum comes from or goes to memory is bound by that
     // traffic, and with only a round or two of large tiles every CU loads, computes and stores in step with the
     // others: two smaller workgroups per CU overlap one's loads and stores with the other's MFMAs (8192 x 4096 with
     // K = 256: 62 -> 54 us; with 8 rounds of large tiles, 4096 x 32768, the large tile stays 7 % ahead).
     if (kind == 2 && (kAccIn || kEpi == static_cast<int>(Epilogue::kF32Workspace)) && p.K <= kShortK && best == 0 &&
-        static_cast<long>(p.M / 256) * (p.N / 256) <= 2 * kCUs && !force) {
-      if (p.N % 256 == 0 && p.n_split % 256 == 0) best = 2;
-      else if (p.n_split % 128 == 0) best = 1;
-    }
+        tile_count(p.M, p.N, 256, 256) <= 2 * kCUs && !force)
+      best = p.n_split % 256 == 0 ? 2 : 1;
     // A launch of at most one tile per CU cannot hide the latency of its loads behind a second workgroup: it gets
     // the whole LDS for a deeper pipeline instead (twice the bytes in flight).
-    const bool deep = best > 0 && static_cast<long>(p.M / kTiles[best].bm) * (p.N / kTiles[best].bn) * parts <= kCUs &&
+    const bool deep = best > 0 && tile_count(p.M, p.N, kTiles[best].bm, kTiles[best].bn) * parts <= kCUs &&
                       debug_options().deep.load(std::memory_order_relaxed) != 0;  // testing: 0 keeps the shallow pipelines
     const int fw = debug_options().four_wave.load(std::memory_order_relaxed);  // testing: 0 never, 1 whenever it can
     switch (best) {
@@ -379,7 +385,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
           // gather by itself, which measured better on every workload than keeping the plain kernel for its sake.
           const int pst = debug_options().persistent.load(std::memory_order_relaxed);  // testing: 0 never, 1 for any number of tiles
           if (pst != 0 && !(parts > 1 && (p.k_split || kAccIn)) &&
-              (pst == 1 || static_cast<long>(p.M / 256) * (p.N / 256) * parts > kCUs))
+              (pst == 1 || tile_count(p.M, p.N, 256, 256) * parts > kCUs))
             return launch_w4p<kAK, kBK, kEpi, kAccIn>(p, stream);
           if constexpr (!(kAK && kBK)) {  // dX launches read every staged slice there is: they never carry a gather
             if (*carry) {
@@ -403,7 +409,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         return launch_dma<128, 128, 64, 64, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
     }
   }
-  if (p.k_split || p.n_split) return hipErrorInvalidValue;  // the bounds-checked kernel takes one B segment only
+  if (p.k_split % GBK || p.n_split % GBN) return hipErrorInvalidValue;
   return launch_generic<kAK, kBK, kEpi, kAccIn>(p, stream);
 }
 
@@ -442,12 +448,12 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
   double whole = 0.0;
   *axis = -1;
   *cut = 0;
-  if (best_tile(M, N, 0, kind, &whole) < 0) return 0.0;
+  best_tile(M, N, 0, kind, &whole);
   // testing: split_launch = 0 keeps every problem in one launch, as does a forced tile shape
   if (debug_options().split_launch.load(std::memory_order_relaxed) == 0 ||
-      debug_options().tile.load(std::memory_order_relaxed) >= 0 || M % 256 || N % 256)
+      debug_options().tile.load(std::memory_order_relaxed) >= 0)
     return whole;
-  const int tm = M / 256, tn = N / 256;
+  const int tm = (M + 255) / 256, tn = (N + 255) / 256;
   const double between = 1.0e7 / K;  // about 5 us from one launch to the next, in the cost's units of tile area
   double best = 0.95 * whole;        // only for a clear gain
   double rest = 0.0;
@@ -456,7 +462,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cn = static_cast<int>(static_cast<long>(kCUs) * r / tm);
     if (cn <= 0) continue;
     if (cn >= tn) break;
-    if (best_tile(M, N - cn * 256, 0, kind, &rest) < 0) continue;
+    best_tile(M, N - cn * 256, 0, kind, &rest);
     const double c = tile_cost(M, cn * 256, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 1; *cut = cn * 256; }
   }
@@ -464,7 +470,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cm = static_cast<int>(static_cast<long>(kCUs) * r / tn);
     if (cm <= 0) continue;
     if (cm >= tm) break;
-    if (best_tile(M - cm * 256, N, 0, kind, &rest) < 0) continue;
+    best_tile(M - cm * 256, N, 0, kind, &rest);
     const double c = tile_cost(cm * 256, N, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 0; *cut = cm * 256; }
   }
@@ -494,7 +500,7 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
       return hipGetLastError();
     }
   }
-  if (!p.k_split && !p.n_split && fast_path(p.M, p.N, p.K, 0, 0)) {
+  if (!p.k_split && !p.n_split && fast_path(p.K, 0, 0) && fits_offsets(p)) {
     int axis, cut;
     plan_launches(p.M, p.N, p.K, layout_kind(kAK, kBK), &axis, &cut);
     if (axis == 1) {
@@ -513,15 +519,12 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
 
 }  // namespace
 
-bool gemm_takes_two_segments(int64_t M, int64_t N, int64_t k_first, int64_t k_second) {
-  return fast_path(static_cast<int>(M), static_cast<int>(N), static_cast<int>(k_first + k_second), static_cast<int>(k_first), 0) &&
-         k_first > 0 && k_second > 0;
+bool gemm_takes_two_segments(int64_t k_first, int64_t k_second) {
+  return k_first > 0 && k_second > 0 && fast_path(static_cast<int>(k_first + k_second), static_cast<int>(k_first), 0);
 }
 
-bool gemm_takes_two_column_segments(int64_t M, int64_t n_first, int64_t n_second, int64_t K) {
-  return n_first > 0 && n_second > 0 &&
-         fast_path(static_cast<int>(M), static_cast<int>(n_first + n_second), static_cast<int>(K), 0, static_cast<int>(n_first)) &&
-         best_tile(static_cast<int>(M), static_cast<int>(n_first + n_second), static_cast<int>(n_first), 0, nullptr) >= 0;
+bool gemm_takes_two_column_segments(int64_t n_first, int64_t n_second, int64_t K) {
+  return n_first > 0 && n_second > 0 && fast_path(static_cast<int>(K), 0, static_cast<int>(n_first));
 }
 
 double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
@@ -529,8 +532,8 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   // (one launch on its best tile: pricing the whole-rounds + remainder pair here instead was measured and made the
   // forward launch grouping of config 3 slightly worse)
   double cost = 0.0;
-  if (fast_path(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0) &&
-      best_tile(static_cast<int>(M), static_cast<int>(N), 0, 0, &cost) >= 0) {
+  if (M > 0 && fast_path(static_cast<int>(K), 0, 0)) {
+    best_tile(static_cast<int>(M), static_cast<int>(N), 0, 0, &cost);
     const int parts = forward_parts ? forward_k_parts(M, K) : 1;
     if (parts > 1) {
       best_tile(static_cast<int>(M), static_cast<int>(N), 0, 0, &cost, parts);

@@ -93,12 +93,12 @@ struct GemmProblem {
 // Enqueue on `stream`.  Returns hipSuccess or the launch error.
 hipError_t launch_gemm(const GemmProblem &p, hipStream_t stream);
 
-// Whether launch_gemm accepts a two-segment B (B2 / k_split) for an M x N product whose K range is
-// k_first columns from B followed by k_second columns from B2.
-bool gemm_takes_two_segments(int64_t M, int64_t N, int64_t k_first, int64_t k_second);
+// Whether launch_gemm accepts a two-segment B (B2 / k_split) whose K range is k_first columns from B followed by
+// k_second columns from B2.
+bool gemm_takes_two_segments(int64_t k_first, int64_t k_second);
 
-// Whether launch_gemm accepts a two-segment N-contiguous B (B2 / n_split): N = n_first + n_second columns.
-bool gemm_takes_two_column_segments(int64_t M, int64_t n_first, int64_t n_second, int64_t K);
+// Whether launch_gemm accepts a two-segment B (B2 / n_split): N = n_first + n_second columns, reduction length K.
+bool gemm_takes_two_column_segments(int64_t n_first, int64_t n_second, int64_t K);
 
 // Rough duration in microseconds of one M x N x K GEMM launch (tile rounds over the CUs at the
 // throughput measured for each tile shape); only used to choose between launch groupings.

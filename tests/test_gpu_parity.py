@@ -759,6 +759,61 @@ def test_every_tile_shape_gives_the_bits_of_the_checked_kernel(H, oracle, T, I, 
                 assert np.array_equal(got[name], ref[name]), f"{name} differs (tile {tile}, k {k}, dim {dim})"
 
 
+@pytest.mark.parametrize("T,I,O,N,ks", [
+    (1, 136, 200, 1, (1,)),        # one row; K = 136: two K blocks and 8 left over
+    (257, 264, 776, 4, (1,)),      # one row beyond a tile edge, K = 264: 8 left over
+    (515, 328, 1040, 2, (1, 2)),    # slices of 520 columns: a tail of 8; dW over 515 tokens
+    (255, 512, 1272, 4, (1, 3)),   # one row short of a tile edge; slices of 424 columns
+])
+def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H, oracle, T, I, O, N, ks, debug):
+    """The direct-to-LDS kernels take any size: rows, columns and k beyond the matrix are range-checked to zeros by their
+    loads, and not stored.  Every tile shape and pipeline at sizes just beside the edges of tiles and K blocks, inside
+    wider arrays whose other columns hold NaN, against the bounds-checked kernel bit for bit."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(73, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+    nan, sc = float("nan"), H.streams()[0]
+
+    def widened(bits, pad):
+        t = torch.full((bits.shape[0], bits.shape[1] + pad), nan, dtype=torch.bfloat16, device="cuda")
+        t[:, : bits.shape[1]] = H.to_dev(bits)
+        return t
+
+    X, dY = widened(d["X"], 8)[:, :I], widened(d["dY"], 24)[:, :O]
+    W = [H.to_dev(s) for s in d["W_shards"]]
+
+    def run(kk, dim):
+        Yw, dXw = (torch.full((T, n + pad), nan, dtype=torch.bfloat16, device="cuda") for n, pad in ((O, 40), (I, 8)))
+        dW = [torch.full((s.numel(),), nan, dtype=torch.bfloat16, device="cuda") for s in W]
+        plan = osdp.Plan([kk], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[dim])
+        need = max(osdp.osdp_split_linear_workspace_bytes(T, I, O, N, kk, b, plan)[0] for b in (False, True))
+        ws = torch.full((max(need, 256),), 255, dtype=torch.uint8, device="cuda")   # (NaN patterns)
+        torch.cuda.synchronize()
+        osdp.osdp_split_linear_fwd(X, W, Yw[:, :O], kk, ws, plan=plan, stream_compute=sc)
+        osdp.osdp_split_linear_bwd(X, dY, W, dXw[:, :I], dW, kk, ws, plan=plan, stream_compute=sc)
+        torch.cuda.synchronize()
+        assert (H.to_bits(Yw)[:, O:] == POISON).all() and (H.to_bits(dXw)[:, I:] == POISON).all()
+        flat = np.concatenate([H.to_bits(s) for s in dW])
+        assert (flat[I * O:] == POISON).all()
+        return {"Y": H.to_bits(Yw)[:, :O], "dX": H.to_bits(dXw)[:, :I], "dW": flat[: I * O].reshape(I, O)}
+
+    debug("gemm_generic", 1)
+    ref = {(kk, dim): run(kk, dim) for kk in ks for dim in (0, 1) if (I if dim else O) % (8 * kk) == 0}
+    debug("gemm_generic", 0)
+    for got in ref.values():
+        for name in ("Y", "dX", "dW"):
+            H.assert_close(name, got[name], want[name])
+    for tile, deep, four_wave, persistent in ((0, 1, 0, -1), (0, 1, 1, 0), (0, 1, 1, 1), (1, 0, -1, -1), (1, 1, -1, -1),
+                                              (2, 0, -1, -1), (2, 1, -1, -1), (3, 0, -1, -1), (3, 1, -1, -1)):
+        for name, value in (("tile", tile), ("deep", deep), ("four_wave", four_wave), ("persistent", persistent)):
+            debug(name, value)
+        for (kk, dim), want_bits in ref.items():
+            _announce("ragged tile", tile, deep, four_wave, persistent, T, I, O, N, "k", kk, "dim", dim)
+            got = run(kk, dim)
+            for name in ("Y", "dX", "dW"):
+                assert np.array_equal(got[name], want_bits[name]), f"{name} differs (tile {tile}, k {kk}, dim {dim})"
+
+
 # ------------------------------------------------ the persistent form of the four-wave kernel
 @pytest.mark.parametrize("dim", [0, 1])
 def test_persistent_kernel_keeps_the_bits_of_one_tile_per_workgroup(H, oracle, debug, dim):
