@@ -698,6 +698,24 @@ GemmProblem dw_gemm(const Resolved &r, int j0, int j1, const void *X, int64_t ld
   return g;
 }
 
+// The whole weight matrix as launch_skinny reads it.
+WeightMap weight_map(const Resolved &r, const ShardTable &tab, const Replicas &rep) {
+  WeightMap w{};
+  w.shards = tab; w.lay = r.layout;
+  w.I = r.I; w.ld_dp = rep.ld;
+  w.k = r.k; w.rows = r.rows;
+  for (size_t j = 0; j < r.sub.size(); ++j)
+    if (r.dp[j])
+      for (int32_t o = r.owner[j]; o < r.k; ++o) {  // (a merged run of DP slices stands under its first one's index)
+        int64_t c0, c1;
+        slice_bounds(r.rows ? r.I : r.O, r.k, o, &c0, &c1);
+        if (c0 >= r.sub[j].c1) break;
+        w.dp_mask |= 1ull << o;
+        w.dp.p[o] = const_cast<void *>(rep.w[o]);
+      }
+  return w;
+}
+
 osdp_status check_replicas(const Resolved &r, const Replicas &rep, bool need_dw) {
   if (!r.any_dp) return OSDP_OK;
   if (!rep.w) return fail(OSDP_ERR_INVALID_ARG, "w_dp is NULL but the plan has slices in DP mode");
@@ -860,6 +878,12 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
   if ((st = check_workspace(r, workspace, workspace_bytes)) != OSDP_OK) return st;
   if ((st = device_ok()) != OSDP_OK) return st;
   if (no_tokens) return OSDP_OK;  // Y is empty: nothing is gathered, nothing is launched
+  if (skinny_takes(r.T, ldx, r.I, r.O)) {  // few tokens: one launch that reads the weights where they lie
+    const double T = r.T, I = r.I, O = r.O;
+    OSDP_HIP(timed(OSDP_KERNEL_GEMM_FWD, 2.0 * T * I * O, 2.0 * (T * I + I * O + T * O), sc,
+                   [&] { return launch_skinny(false, weight_map(r, tab, rep), r.T, X, ldx, Y, ldy, sc); }));
+    return OSDP_OK;
+  }
 
   char *ws = static_cast<char *>(workspace);
   float *acc = reinterpret_cast<float *>(ws + r.slot_bytes * r.slots);  // row slices: Y's fp32 partial sum
@@ -1027,6 +1051,14 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
       const GemmProblem gw = dw_gemm(r, static_cast<int>(l.c0), static_cast<int>(l.c1), X, ldx, dY, lddy, gtab, rep);
       OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DW, gw, static_cast<hipStream_t>(stream_compute)));
     }
+    return OSDP_OK;
+  }
+  if (skinny_takes(r.T, lddy, r.I, r.O)) {  // few tokens: nothing is staged (see forward())
+    const double T = r.T, I = r.I, O = r.O;
+    for (const Slice &l : r.dw)
+      OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DW, dw_gemm(r, static_cast<int>(l.c0), static_cast<int>(l.c1), X, ldx, dY, lddy, gtab, rep), sc));
+    OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 2.0 * T * I * O, 2.0 * (T * O + I * O + T * I), sc,
+                   [&] { return launch_skinny(true, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc); }));
     return OSDP_OK;
   }
   char *ws = static_cast<char *>(workspace);

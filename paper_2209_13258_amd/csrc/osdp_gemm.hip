@@ -12,6 +12,7 @@
 // a split operator bit-identical to the unsplit ones.
 #include "gemm_common.h"
 #include "gemm_dma.h"
+#include "gemm_skinny.h"
 #include "gemm_w4.h"
 #include "gemm_w4p.h"
 
@@ -613,6 +614,78 @@ hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) 
   return hipErrorInvalidValue;
 }
 }  // namespace
+
+namespace {
+template <int BM, int BN, int BK, int kStages, bool kBKc>
+hipError_t launch_skinny_as(SkinnyParams p, hipStream_t stream) {
+  constexpr size_t lds = static_cast<size_t>(kSkinnyWaves) * kStages * (BM + BN) * BK * sizeof(uint16_t);
+  static_assert(lds + 2 * OSDP_MAX_SHARDS * 8 <= 160 * 1024, "the rings do not fit the 160 KB of LDS");
+  auto kernel = gemm_skinny_kernel<BM, BN, BK, kStages, kBKc>;
+  static bool configured[kMaxDevices] = {};
+  const hipError_t e = allow_lds(kernel, lds, configured);
+  if (e != hipSuccess) return e;
+  p.tiles_m = (p.M + BM - 1) / BM;
+  // whole K blocks lie in one shard where shards are row blocks that the blocks (dX: the tiles) divide
+  p.by_lane = p.w.dp_mask != 0 || p.w.lay.rows_per_shard == 0 || p.w.lay.rows_per_shard % (kBKc ? BN : BK) != 0;
+  hipLaunchKernelGGL(kernel, dim3(p.tiles_m * ((p.N + BN - 1) / BN)), dim3(kSkinnyWaves * 64), lds, stream, p);
+  return hipGetLastError();
+}
+}  // namespace
+
+bool skinny_takes(int64_t T, int64_t ld_act, int64_t I, int64_t O) {
+  // (the switches that pick a kernel or a tile for the staged products keep those)
+  const DebugOptions &d = debug_options();
+  return T > 0 && T <= kSkinnyMaxTokens && ld_act < kMaxLd && I < kMaxLd && O < kMaxLd &&
+         d.gemm_generic.load(std::memory_order_relaxed) == 0 && d.tile.load(std::memory_order_relaxed) < 0;
+}
+
+// Rows of a workgroup's tile.  Every workgroup streams (BM + 64) rows' worth of operands, and the launch lasts as long
+// as its fullest CU: all tokens in one tile when the columns alone occupy the CUs (the weights are then read once),
+// smaller tiles, which read them again from the L2, when that leaves CUs idle (128 tokens 256 -> 1024: forward 10.0 us
+// in 16 tiles of 128 rows, 5.7 us in 128 tiles of 16; dX 15.5 against 5.0 us).
+int skinny_rows(int64_t T, int64_t N) {
+  int best = 0;
+  int64_t best_cost = 0;
+  for (int bm : {16, 32, 48, 64, 128}) {
+    const int64_t tiles = ((T + bm - 1) / bm) * ((N + 63) / 64);
+    const int64_t cost = (tiles + kCUs - 1) / kCUs * (bm + 64);
+    if (best == 0 || cost < best_cost) {
+      best = bm;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// As many LDS stages as fit; 128 columns to a workgroup where that still gives every CU one, else 64.
+hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
+                         hipStream_t stream) {
+  SkinnyParams p{};
+  p.M = static_cast<int32_t>(T);
+  p.N = static_cast<int32_t>(dx ? w.I : w.lay.O);
+  p.K = static_cast<int32_t>(dx ? w.lay.O : w.I);
+  p.A = static_cast<const uint16_t *>(act); p.lda = ld_act;
+  p.C = static_cast<uint16_t *>(out); p.ldc = ld_out;
+  p.w = w;
+  const int bm = skinny_rows(T, p.N);
+  if (dx) {
+    if (bm == 16) return launch_skinny_as<16, 64, 64, 3, true>(p, stream);
+    if (bm == 32) return launch_skinny_as<32, 64, 64, 3, true>(p, stream);
+    if (bm <= 64) return launch_skinny_as<64, 64, 64, 2, true>(p, stream);
+    return launch_skinny_as<128, 64, 32, 3, true>(p, stream);
+  }
+  if (p.N > 128 * (kCUs - 1) && T <= 64) {
+    if (T <= 16) return launch_skinny_as<16, 128, 32, 4, false>(p, stream);
+    if (T <= 32) return launch_skinny_as<32, 128, 32, 3, false>(p, stream);
+    if (T <= 48) return launch_skinny_as<48, 128, 32, 3, false>(p, stream);
+    return launch_skinny_as<64, 128, 32, 3, false>(p, stream);
+  }
+  if (bm == 16) return launch_skinny_as<16, 64, 32, 7, false>(p, stream);
+  if (bm == 32) return launch_skinny_as<32, 64, 32, 6, false>(p, stream);
+  if (bm == 48) return launch_skinny_as<48, 64, 32, 5, false>(p, stream);
+  if (bm == 64) return launch_skinny_as<64, 64, 32, 4, false>(p, stream);
+  return launch_skinny_as<128, 64, 32, 3, false>(p, stream);
+}
 
 hipError_t launch_gemm(const GemmProblem &q, hipStream_t stream) {
   if (q.M < 0 || q.N < 0 || q.K < 0) return hipErrorInvalidValue;

@@ -40,6 +40,17 @@ struct ShardLayout {
   int32_t rows_per_shard;  // I / N when N divides I, else 0 (general flat map)
 };
 
+// Where the whole weight matrix lies: in the shards, or for the slices j whose bit is set in dp_mask in the caller's
+// replica (dp.p[j] with leading dimension ld_dp; slices are ranges of columns, or of rows when `rows` is set).
+struct WeightMap {
+  ShardTable shards;
+  ShardLayout lay;
+  ShardTable dp;
+  int64_t I, ld_dp;
+  uint64_t dp_mask;
+  int32_t k, rows;
+};
+
 enum class Epilogue : int32_t {
   kBf16RowMajor = 0,   // C -> bf16, row-major with ldc
   kBf16ShardMajor = 1, // C -> bf16, scattered into the shard-major layout at column offset c0
@@ -92,6 +103,13 @@ struct GemmProblem {
 
 // Enqueue on `stream`.  Returns hipSuccess or the launch error.
 hipError_t launch_gemm(const GemmProblem &p, hipStream_t stream);
+
+// Forward (or, dx set, dX) product of at most kSkinnyMaxTokens tokens with the whole weight matrix, read in place: no
+// slice is staged.  skinny_takes: whether the launch accepts the sizes.
+constexpr int64_t kSkinnyMaxTokens = 128;
+bool skinny_takes(int64_t T, int64_t ld_act, int64_t I, int64_t O);
+hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
+                         hipStream_t stream);
 
 // Whether launch_gemm accepts a two-segment B (B2 / k_split) whose K range is k_first columns from B followed by
 // k_second columns from B2.

@@ -814,6 +814,69 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
                 assert np.array_equal(got[name], want_bits[name]), f"{name} differs (tile {tile}, k {kk}, dim {dim})"
 
 
+# ------------------------------------------------ few tokens: the weights are read where they lie
+@pytest.mark.parametrize("T,I,O,N,k", [
+    (1, 256, 512, 8, 4),       # one row; shards of 32 rows
+    (16, 264, 1000, 11, 5),    # shards of 24 rows: K blocks reach over their ends; 40 columns in the last tile
+    (17, 40, 1056, 3, 2),      # N does not divide I: rows reach over the ends of shards
+    (33, 72, 32776, 4, 1),     # more columns than 256 tiles of 64: tiles of 128, the last of 8 columns
+    (48, 8, 72, 1, 3),         # one K block, of 8
+    (64, 512, 64, 64, 4),      # 64 shards of 8 rows
+    (65, 1032, 520, 2, 1),     # one row beyond a tile; K blocks divide evenly among no four waves
+    (128, 2048, 16448, 8, 4),  # all rows in one tile
+])
+def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
+    """At most 128 tokens: Y and dX are one launch each over the whole weight, read from the shards, whatever the
+    slicing, staging mode and split dimension, and with DP slices from the replica: the oracle's values, the same bits
+    from every plan, nothing written outside the outputs."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(75, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+    base = None
+    for kk, dim, mode in ((1, 0, osdp.OSDP_STAGING_SINGLE), (k, 0, osdp.OSDP_STAGING_DOUBLE), (k, 1, osdp.OSDP_STAGING_SINGLE)):
+        if (I if dim else O) % (8 * kk):
+            continue
+        _announce("few tokens", T, I, O, N, "k", kk, "dim", dim)
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        plan = osdp.Plan([kk], staging=mode, split_dim_per_op=[dim])
+        osdp.osdp_profile_begin(100)
+        op.fwd(kk, plan=plan)
+        op.bwd(kk, plan=plan)
+        st = osdp.osdp_profile_end()
+        assert (st["gemm_fwd"]["launches"], st["gemm_dx"]["launches"], st["gather"]["launches"]) == (1, 1, 0)
+        got = op.results()
+        for name in ("Y", "dX", "dW"):
+            H.assert_close(name, got[name], want[name])
+            if base is not None:
+                assert np.array_equal(got[name], base[name]), f"{name} differs from the unsplit result (k {kk}, dim {dim})"
+        base = base or got
+    L = d["W_shards"][0].size
+    assert (H.to_bits(op.dW[-1])[I * O - (N - 1) * L:] == POISON).all()
+
+
+@pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("T,I,O,N,k,mask", [(7, 256, 512, 4, 4, 0b0110), (40, 264, 528, 4, 3, 0b001), (100, 40, 1200, 3, 5, 0b00000)])
+def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows):
+    """The same with some slices read from their replicas (NaN wherever a source must not be read)."""
+    import paper_2209_13258_amd as osdp
+    if rows:
+        I, O = O, I
+    dim = osdp.OSDP_SPLIT_IN_FEATURES if rows else osdp.OSDP_SPLIT_OUT_FEATURES
+    for full in (False, True):
+        if full and rows:
+            continue
+        _announce("few tokens, DP slices", T, I, O, N, k, bin(mask), rows, full)
+        d, shards, w_dp, ld, rng, used, whole = _mixed_host_case(oracle, 76, T, I, O, N, k, mask, rows, full)
+        want = oracle.linear(d["X"], oracle.shard(used, N), O, dY=d["dY"])
+        dev = _MixedDevice(H, d, shards, w_dp, ld, rng, I, O, rows, whole)
+        dev.run(k, osdp.Plan([k], zdp_mask=[mask], split_dim_per_op=[dim]))
+        got, dW, in_dp, outside = dev.gradient(H, I, O, mask)
+        H.assert_close("Y", got["Y"], want["Y"])
+        H.assert_close("dX", got["dX"], want["dX"])
+        H.assert_close("dW", dW, want["dW"])
+        assert all((a == POISON).all() for a in in_dp + outside)
+
+
 # ------------------------------------------------ the persistent form of the four-wave kernel
 @pytest.mark.parametrize("dim", [0, 1])
 def test_persistent_kernel_keeps_the_bits_of_one_tile_per_workgroup(H, oracle, debug, dim):
