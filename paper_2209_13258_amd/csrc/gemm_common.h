@@ -41,6 +41,9 @@ struct GemmParams {
   int64_t ldb2;
   int32_t k_split;     // 0: none
   int32_t n_split;     // 0: none
+  // B read from the weight shards instead of a staged slice (ldb = O; the shards are in `shards`): each holds seg_k rows
+  // of an N-contiguous B (multiple of 64), or seg_n rows, which are columns of C, of a K-contiguous one.  0: not so.
+  int32_t seg_k, seg_n;
   int32_t k_parts;     // > 1 (fp32 workspace epilogue with ldc = N, no second K segment): the grid is k_parts times the
                        // tiles, part s takes k in [s K / k_parts, (s + 1) K / k_parts) and writes plane s of C ([M x N] fp32 each)
   void *C;
@@ -91,19 +94,31 @@ __device__ __forceinline__ void tile_of_pid(int pid, int tiles_m, int tiles_n, i
   *tn = __builtin_amdgcn_readfirstlane(in_group / gm);
 }
 
+// Columns [n0, n_end) of C that tile column tn covers.  With seg_n tiles do not reach over the end of a shard.
+template <bool kBKc>
+__device__ __forceinline__ void tile_columns(const GemmParams &p, int tn, int BN, int *n0, int *n_end) {
+  *n0 = tn * BN;
+  *n_end = p.N;
+  if (kBKc && p.seg_n) {
+    const int per = (p.seg_n + BN - 1) / BN, s = __builtin_amdgcn_readfirstlane(tn / per);
+    *n0 = s * p.seg_n + (tn - s * per) * BN;
+    *n_end = (s + 1) * p.seg_n;
+  }
+}
+
 // Accumulator layout of one wave: acc[bm][bn][i] is C[m][n] with
 //   m = m_base + 16*bm + l16,  n = n_base + 16*bn + 4*q + i        (l16 = lane % 16, q = lane / 16).
-// Outside the matrix the load repeats the last row / column group (the values are never stored) and the store does
+// Outside the matrix (n_end: the end of the tile's columns) the load repeats the last row / column group (the values are never stored) and the store does
 // nothing; N is a multiple of 8 and n of 4, so the 4 columns are in or out together.
 template <int MB, int NB>
 __device__ __forceinline__ void load_acc_tile(const GemmParams &p, f32x4 (&acc)[MB][NB], int m_base, int n_base,
-                                              int l16, int q) {
+                                              int n_end, int l16, int q) {
 #pragma unroll
   for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
     for (int bn = 0; bn < NB; ++bn) {
       const int m = m_base + bm * 16 + l16, n = n_base + bn * 16 + 4 * q;
-      const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < p.N ? n : p.N - 4);
+      const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < n_end ? n : n_end - 4);
       const float4 c = *reinterpret_cast<const float4 *>(src);
       acc[bm][bn][0] = c.x;
       acc[bm][bn][1] = c.y;
@@ -144,8 +159,8 @@ __device__ __forceinline__ void store_acc4(const GemmParams &p, f32x4 c, int m, 
 // plane_row: added to the row where the tile is stored (launches that run parts of the reduction), not to the bound.
 template <int MB, int NB, int kEpi>
 __device__ __forceinline__ void store_acc_tile(const GemmParams &p, const f32x4 (&acc)[MB][NB], int m_base, int n_base,
-                                               int plane_row, int l16, int q, uint16_t *const *s_tab) {
-  if (m_base + MB * 16 <= p.M && n_base + NB * 16 <= p.N) {  // (the whole wave tile is inside: no test per store)
+                                               int n_end, int plane_row, int l16, int q, uint16_t *const *s_tab) {
+  if (m_base + MB * 16 <= p.M && n_base + NB * 16 <= n_end) {  // (the whole wave tile is inside: no test per store)
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
@@ -158,7 +173,7 @@ __device__ __forceinline__ void store_acc_tile(const GemmParams &p, const f32x4 
 #pragma unroll
     for (int bn = 0; bn < NB; ++bn) {
       const int m = m_base + bm * 16 + l16, n = n_base + bn * 16 + 4 * q;
-      if (m < p.M && n < p.N) store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
+      if (m < p.M && n < n_end) store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
     }
 }
 

@@ -191,39 +191,56 @@ struct OperandSource {
 };
 
 // Both operands of a tile, K block by K block.  Most blocks only move the two base addresses; at `stop` something else
-// is due: B's second K segment begins, the last block is cut short, or the blocks beyond the last one, which the
-// kernels' uniform K loops still ask for, must deliver nothing.
+// is due: B goes on in its next K segment (a second staged slice, or the next shard), the last block is cut short, or
+// the blocks beyond the last one, which the kernels' uniform K loops still ask for, must deliver nothing.
 template <class OpA, class OpB, bool kAK, bool kBKc, int BM, int BN, int kBK>
 struct TileSource {
   OperandSource<OpA, kAK, BM, kBK> a;
   OperandSource<OpB, kBKc, BN, kBK> b;
-  int32_t block, stop;  // the block the sources stand at; the next one at which something is due
-  int32_t n0, nb;       // the tile's first column; its K blocks
+  int32_t block, stop;          // the block the sources stand at; the next one at which something is due
+  int32_t n0, n_end, nb;        // the tile's columns (n_end: where those it may store end); its K blocks
+  int32_t segment, segment_end; // B's K segment; the block where the next one begins
 
-  // Block 0 of the tile at (m0, n0), reducing over k0 .. k0 + K (k0 > 0 only without a second K segment).
-  __device__ __forceinline__ void begin(const GemmParams &p, int m0, int n0_, int64_t k0, int K, int wave, int lane) {
-    n0 = n0_;
+  // Block 0 of the tile of rows m0 .. and tile column tn, reducing over k0 .. k0 + K (k0 > 0 only with one K segment).
+  __device__ __forceinline__ void begin(const GemmParams &p, int m0, int tn, int64_t k0, int K, int wave, int lane) {
+    tile_columns<kBKc>(p, tn, BN, &n0, &n_end);
     nb = (K + kBK - 1) / kBK;
     // B may come in two column segments (two staged slices): the tile lies in one of them
     const bool second = p.n_split && n0 >= p.n_split;
     const uint16_t *base = second ? p.B2 : p.B;
     const int64_t ldb = second ? p.ldb2 : p.ldb;
-    const int nB = second ? n0 - p.n_split : n0;
+    int nB = second ? n0 - p.n_split : n0;
+    if (kBKc && p.seg_n) {
+      const int s = __builtin_amdgcn_readfirstlane(n0 / p.seg_n);
+      base = static_cast<const uint16_t *>(p.shards.p[s]);
+      nB = n0 - s * p.seg_n;
+    }
+    if (!kBKc && p.seg_k) base = static_cast<const uint16_t *>(p.shards.p[0]);
     a.begin(kAK ? p.A + static_cast<int64_t>(m0) * p.lda + k0 : p.A + m0 + k0 * p.lda, p.lda, p.M - m0, wave, lane);
-    b.begin(kBKc ? base + static_cast<int64_t>(nB) * ldb + k0 : base + nB + k0 * ldb, ldb, p.N - n0, wave, lane);
-    block = 0;
+    b.begin(kBKc ? base + static_cast<int64_t>(nB) * ldb + k0 : base + nB + k0 * ldb, ldb, n_end - n0, wave, lane);
+    block = segment = 0;
+    segment_end = kAK && p.k_split ? p.k_split / kBK : (kAK && !kBKc && p.seg_k ? p.seg_k / kBK : 0x7fffffff);
     due(p, K, wave, lane);
   }
   __device__ __forceinline__ void due(const GemmParams &p, int K, int wave, int lane) {
-    if (kAK && block > 0 && block * kBK == p.k_split)
-      b.begin(kBKc ? p.B2 + static_cast<int64_t>(n0) * p.ldb2 : p.B2 + n0, p.ldb2, p.N - n0, wave, lane);
+    if (kAK && block == segment_end) {
+      ++segment;
+      const bool shards = !kBKc && p.seg_k;
+      if (block < nb) {
+        const uint16_t *base = shards ? static_cast<const uint16_t *>(p.shards.p[segment]) : p.B2;
+        const int64_t ldb = shards ? p.ldb : p.ldb2;
+        b.begin(kBKc ? base + static_cast<int64_t>(n0) * ldb : base + n0, ldb, n_end - n0, wave, lane);
+      }
+      segment_end = shards ? segment_end + p.seg_k / kBK : 0x7fffffff;
+    }
     const int left = K - block * kBK;
     if (left < kBK) {
       a.cut(left > 0 ? left : 0, wave, lane);
       b.cut(left > 0 ? left : 0, wave, lane);
     }
     const int tail = K / kBK;  // the first block that is not full: the cut one, or the first beyond the end
-    stop = kAK && p.k_split > block * kBK ? p.k_split / kBK : (block < tail ? tail : (block < nb ? nb : 0x7fffffff));
+    stop = block < tail ? tail : (block < nb ? nb : 0x7fffffff);
+    if (kAK && segment_end < stop) stop = segment_end;
   }
   // After the last load of a block: on to the next.
   __device__ __forceinline__ void next(const GemmParams &p, int K, int wave, int lane) {
@@ -272,18 +289,18 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
     plane_row = part * p.M;
   }
   tile_of_pid(pid, tiles_m, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / (BN / WN)) * WM, wn = (wave % (BN / WN)) * WN;
   const int l16 = lane & 15, q4 = lane >> 4;
 
   TileSource<OpA, OpB, kAK, kBK, BM, BN, BK> src;
-  src.begin(p, m0, n0, k0, K, wave, lane);
-  const int nk = src.nb;
+  src.begin(p, m0, tn, k0, K, wave, lane);
+  const int nk = src.nb, n0 = src.n0, n_end = src.n_end;
 
   f32x4 acc[MB][NB];
   if (kAccIn) {
-    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, l16, q4);
+    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);
   } else {
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)
@@ -404,7 +421,7 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
 
-  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, plane_row, l16, q4, s_tab);
+  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
 }
 
 }  // namespace

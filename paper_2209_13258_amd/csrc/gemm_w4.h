@@ -157,18 +157,18 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
     plane_row = part * p.M;
   }
   tile_of_pid(pid, tiles_m, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
   const int l16 = lane & 15, q4 = lane >> 4;
 
   TileSource<OpA, OpB, kAK, kBKc, BM, BN, 64> src;
-  src.begin(p, m0, n0, k0, K, wave, lane);
-  const int nb = src.nb;
+  src.begin(p, m0, tn, k0, K, wave, lane);
+  const int nb = src.nb, n0 = src.n0, n_end = src.n_end;
 
   f32x4 acc[MB][NB];
   if (kAccIn) {
-    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, l16, q4);
+    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);
   } else {
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)
@@ -273,7 +273,7 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
 
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");
-  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, plane_row, l16, q4, s_tab);
+  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
 }
 
 }  // namespace

@@ -77,7 +77,7 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
     int tm, tn;
     const int part = __builtin_amdgcn_readfirstlane(t / part_tiles);
     tile_of_pid(t - part * part_tiles, tiles_m, tiles_n, &tm, &tn);
-    src.begin(p, tm * BM, tn * BN, static_cast<int64_t>(part) * part_k, part_k, wave, lane);
+    src.begin(p, tm * BM, tn, static_cast<int64_t>(part) * part_k, part_k, wave, lane);
   };
   auto block_issued = [&]() {  // after the last load of a block: on to the next block, of this tile or the next
     if (src.block + 1 == nb && lt + G < tiles) {
@@ -98,7 +98,7 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
   };
 
   // ---- the compute side: tile `ct`, its origin, its accumulators --------------------------------------------
-  int ct = first, cb = 0, m0c = 0, n0c = 0, plane_row = 0;
+  int ct = first, cb = 0, m0c = 0, n0c = 0, n_endc = 0, plane_row = 0;
   f32x4 acc[MB][NB];
 #pragma unroll
   for (int bm = 0; bm < MB; ++bm)
@@ -117,13 +117,13 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
     const int part = __builtin_amdgcn_readfirstlane(t / part_tiles);
     tile_of_pid(t - part * part_tiles, tiles_m, tiles_n, &tm, &tn);
     m0c = tm * BM;
-    n0c = tn * BN;
+    tile_columns<kBKc>(p, tn, BN, &n0c, &n_endc);
     plane_row = part * p.M;  // (the part's plane starts at this row of C)
     static_for<MB * NB>([&](auto idx) {
       constexpr int i = decltype(idx)::value, bn = i / MB, bm = i % MB;  // the order of the K loop's steps
       if constexpr (kAccIn) {
         const int m = m0c + wm + bm * 16 + l16e, n = n0c + wn + bn * 16 + 4 * q4e;
-        const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < p.N ? n : p.N - 4);
+        const float *src = p.acc_in + static_cast<int64_t>(m < p.M ? m : p.M - 1) * p.ld_acc + (n < n_endc ? n : n_endc - 4);
         acc_load(acc[bm][bn], src);
       } else {
         acc_clear(acc[bm][bn], zero);
@@ -200,7 +200,7 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
       static_for<MB * NB>([&](auto idx) {
         constexpr int i = decltype(idx)::value, bm = i / NB, bn = i % NB;
         const int m = m0c + wm + bm * 16 + l16e, n = n0c + wn + bn * 16 + 4 * q4e;
-        if (m < p.M && n < p.N) {
+        if (m < p.M && n < n_endc) {
           if constexpr (kEpi == static_cast<int>(Epilogue::kF32Workspace))  // (stored straight from the accumulators)
             store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
           else

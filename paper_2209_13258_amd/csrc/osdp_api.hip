@@ -716,6 +716,22 @@ WeightMap weight_map(const Resolved &r, const ShardTable &tab, const Replicas &r
   return w;
 }
 
+// Y = X . W or dX = dY . W^T as one product with the whole weight, read from its shards.
+GemmProblem shard_gemm(const Resolved &r, bool is_fwd, const ShardTable &tab, const void *act, int64_t ld_act, void *out, int64_t ld_out) {
+  GemmProblem g{};
+  g.M = static_cast<int32_t>(r.T);
+  g.N = static_cast<int32_t>(is_fwd ? r.O : r.I); g.K = static_cast<int32_t>(is_fwd ? r.I : r.O);
+  g.A = act; g.lda = ld_act; g.a_kcontig = true;
+  g.ldb = r.O; g.b_kcontig = !is_fwd;
+  g.b_shard_rows = r.layout.rows_per_shard; g.shards = tab;
+  g.C = out; g.ldc = ld_out; g.epilogue = Epilogue::kBf16RowMajor;
+  return g;
+}
+
+// Whether that product keeps the bits of the slices' products: concatenating launches over a long reduction are summed
+// in parts, accumulating ones in one chain.
+bool one_chain(const Resolved &r, bool is_fwd) { return is_fwd == r.rows || gemm_forward_parts(r.T, r.D) == 1; }
+
 osdp_status check_replicas(const Resolved &r, const Replicas &rep, bool need_dw) {
   if (!r.any_dp) return OSDP_OK;
   if (!rep.w) return fail(OSDP_ERR_INVALID_ARG, "w_dp is NULL but the plan has slices in DP mode");
@@ -882,6 +898,10 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
     const double T = r.T, I = r.I, O = r.O;
     OSDP_HIP(timed(OSDP_KERNEL_GEMM_FWD, 2.0 * T * I * O, 2.0 * (T * I + I * O + T * O), sc,
                    [&] { return launch_skinny(false, weight_map(r, tab, rep), r.T, X, ldx, Y, ldy, sc); }));
+    return OSDP_OK;
+  }
+  if (!r.any_dp && one_chain(r, true) && gemm_reads_shards(r.T, ldx, r.layout)) {
+    OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, shard_gemm(r, true, tab, X, ldx, Y, ldy), sc));
     return OSDP_OK;
   }
 
@@ -1053,12 +1073,18 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
     }
     return OSDP_OK;
   }
-  if (skinny_takes(r.T, lddy, r.I, r.O)) {  // few tokens: nothing is staged (see forward())
+  // Few tokens: nothing is staged (see forward()), and dW is one launch per destination.
+  const bool skinny = skinny_takes(r.T, lddy, r.I, r.O);
+  if (skinny || (!r.any_dp && one_chain(r, false) && gemm_reads_shards(r.T, lddy, r.layout))) {
     const double T = r.T, I = r.I, O = r.O;
+    if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});
     for (const Slice &l : r.dw)
       OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DW, dw_gemm(r, static_cast<int>(l.c0), static_cast<int>(l.c1), X, ldx, dY, lddy, gtab, rep), sc));
-    OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 2.0 * T * I * O, 2.0 * (T * O + I * O + T * I), sc,
-                   [&] { return launch_skinny(true, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc); }));
+    if (skinny)
+      OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 2.0 * T * I * O, 2.0 * (T * O + I * O + T * I), sc,
+                     [&] { return launch_skinny(true, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc); }));
+    else
+      OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DX, shard_gemm(r, false, tab, dY, lddy, dX, lddx), sc));
     return OSDP_OK;
   }
   char *ws = static_cast<char *>(workspace);

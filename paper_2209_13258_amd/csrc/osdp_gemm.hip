@@ -179,6 +179,10 @@ hipError_t allow_lds(Kernel kernel, size_t lds, bool (&configured)[kMaxDevices])
   return hipSuccess;
 }
 
+int tile_columns_of(const GemmParams &p, int BN) {
+  return p.seg_n ? p.N / p.seg_n * ((p.seg_n + BN - 1) / BN) : (p.N + BN - 1) / BN;
+}
+
 template <int BM, int BN, int WM, int WN, int BK, int kStages, bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_dma(const GemmParams &p, hipStream_t stream) {
   constexpr int kWaves = (BM / WM) * (BN / WN);
@@ -188,7 +192,7 @@ hipError_t launch_dma(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = tile_columns_of(p, BN);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(kWaves * 64), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -203,7 +207,7 @@ hipError_t launch_w4(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
+  const int tiles_m = (p.M + 255) / 256, tiles_n = tile_columns_of(p, 256);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -248,7 +252,7 @@ hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
+  const int tiles_m = (p.M + 255) / 256, tiles_n = tile_columns_of(p, 256);
   const int tiles = tiles_m * tiles_n * (p.k_parts > 1 ? p.k_parts : 1);
   hipLaunchKernelGGL(kernel, dim3(tiles < kCUs ? tiles : kCUs), dim3(256), lds, stream, p, tiles_m, tiles_n);
   t_persistent_launches += 1;
@@ -410,7 +414,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         return launch_dma<128, 128, 64, 64, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
     }
   }
-  if (p.k_split % GBK || p.n_split % GBN) return hipErrorInvalidValue;
+  if (p.k_split % GBK || p.n_split % GBN || p.seg_k || p.seg_n) return hipErrorInvalidValue;
   return launch_generic<kAK, kBK, kEpi, kAccIn>(p, stream);
 }
 
@@ -501,7 +505,7 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
       return hipGetLastError();
     }
   }
-  if (!p.k_split && !p.n_split && fast_path(p.K, 0, 0) && fits_offsets(p)) {
+  if (!p.k_split && !p.n_split && !p.seg_k && !p.seg_n && fast_path(p.K, 0, 0) && fits_offsets(p)) {
     int axis, cut;
     plan_launches(p.M, p.N, p.K, layout_kind(kAK, kBK), &axis, &cut);
     if (axis == 1) {
@@ -519,6 +523,16 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
 }
 
 }  // namespace
+
+bool gemm_reads_shards(int64_t T, int64_t ld_act, const ShardLayout &lay) {
+  const DebugOptions &d = debug_options();
+  const bool forced = d.gemm_generic.load(std::memory_order_relaxed) != 0 || d.tile.load(std::memory_order_relaxed) >= 0 ||
+                      d.fwd_pair.load(std::memory_order_relaxed) >= 0 || d.fused_gather.load(std::memory_order_relaxed) >= 0 ||
+                      d.poison_staging.load(std::memory_order_relaxed) != 0;  // (these ask for the staged schedule)
+  return !forced && T <= kShardReadMaxTokens && lay.rows_per_shard > 0 && lay.rows_per_shard % 64 == 0 && ld_act < kMaxLd && lay.O < kMaxLd;
+}
+
+int gemm_forward_parts(int64_t M, int64_t K) { return forward_k_parts(M, K); }
 
 bool gemm_takes_two_segments(int64_t k_first, int64_t k_second) {
   return k_first > 0 && k_second > 0 && fast_path(static_cast<int>(k_first + k_second), static_cast<int>(k_first), 0);
@@ -582,6 +596,8 @@ hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) 
   p.lay = q.layout; p.c0 = q.c0; p.r0 = q.r0; p.shards = q.shards;
   p.B2 = static_cast<const uint16_t *>(q.B2); p.ldb2 = q.ldb2;
   p.k_split = q.B2 ? q.k_split : 0; p.n_split = q.B2 ? q.n_split : 0;
+  p.seg_k = q.b_kcontig ? 0 : q.b_shard_rows; p.seg_n = q.b_kcontig ? q.b_shard_rows : 0;
+  if (q.b_shard_rows && (!q.a_kcontig || q.acc_in || p.k_split || p.n_split || p.seg_k % 64)) return hipErrorInvalidValue;
   if (*carry) {
     const GatherRequest &g = *q.carry;
     const uint64_t total = static_cast<uint64_t>(g.rows) * (static_cast<uint64_t>(g.w) / 8);

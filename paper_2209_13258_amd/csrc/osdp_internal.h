@@ -81,13 +81,16 @@ struct GemmProblem {
   int64_t ldb2;
   int32_t k_split;
   int32_t n_split;
+  // > 0: B is the whole weight matrix, read from the N weight shards in `shards` (ldb = its row length), each of which
+  // holds this many of its rows (see gemm_reads_shards); B itself is not used.  No accumulator, no second segment.
+  int32_t b_shard_rows;
   void *C;           // row-major outputs; unused for kBf16ShardMajor
   int64_t ldc;
   const float *acc_in;  // fp32 [M x N] with ld_acc added to the product first, or nullptr
   int64_t ld_acc;
   Epilogue epilogue;
   ShardLayout layout;   // kBf16ShardMajor only
-  ShardTable shards;    // kBf16ShardMajor only
+  ShardTable shards;    // kBf16ShardMajor: of the result; b_shard_rows: of the weight
   int64_t c0;           // kBf16ShardMajor only: column offset of C inside the full matrix
   int64_t r0;           // kBf16ShardMajor only: row offset of C inside the full matrix
   // Optional: a gather (into a staging slot this launch does not read) that the launch may take along.  The
@@ -110,6 +113,18 @@ constexpr int64_t kSkinnyMaxTokens = 128;
 bool skinny_takes(int64_t T, int64_t ld_act, int64_t I, int64_t O);
 hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
                          hipStream_t stream);
+
+// Whether a product of T tokens with the whole weight may read it from the shards (GemmProblem::b_shard_rows).
+// Up to four rows of 128-row tiles: the workgroups an XCD runs together walk the rows of a panel of weight columns
+// together (kGroupM in gemm_common.h), so that each weight still crosses from memory into one L2 once, and a staged copy
+// would only add a write and a read of it, and a launch per slice that fills a fraction of the CUs.  With more rows the
+// XCDs share the panels, and the copy, which leaves the slice in one dense piece, is what the sharded layout is for.
+// Measured, 500 tokens 2560 -> 10240 forward at k = 4: 118 us as four gathers and four products, 38 us as one.
+constexpr int64_t kShardReadMaxTokens = 512;
+bool gemm_reads_shards(int64_t T, int64_t ld_act, const ShardLayout &lay);
+
+// Number of parts of the reduction that a concatenating product of M x K is the sum of (1: one chain).
+int gemm_forward_parts(int64_t M, int64_t K);
 
 // Whether launch_gemm accepts a two-segment B (B2 / k_split) whose K range is k_first columns from B followed by
 // k_second columns from B2.

@@ -854,6 +854,39 @@ def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     assert (H.to_bits(op.dW[-1])[I * O - (N - 1) * L:] == POISON).all()
 
 
+@pytest.mark.parametrize("T,I,O,N,k", [
+    (129, 512, 768, 8, 4),        # shards of one K block
+    (257, 640, 1160, 2, 5),         # shards of 320 rows: two and a half tiles of dX
+    (500, 1536, 2568, 4, 3),        # the last tile of columns is 8 wide
+    (512, 1024, 16256, 1, 2),       # one shard; 128 large tiles and more
+])
+def test_up_to_512_tokens_multiply_the_weight_in_its_shards(H, oracle, T, I, O, N, k, debug):
+    """Shards that are whole K blocks, at most 512 tokens: one launch each for Y, dW and dX, with the bits of the staged
+    schedule (forced by one of its switches), and the oracle's values."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(77, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+    for dim in (0, 1):
+        plan = osdp.Plan([k], split_dim_per_op=[dim])
+        got = {}
+        for staged in (1, -1):
+            debug("fused_gather", 0 if staged == 1 else -1)
+            _announce("512 tokens", T, I, O, N, k, "dim", dim, "staged", staged)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            osdp.osdp_profile_begin(1000)
+            op.fwd(k, plan=plan)
+            op.bwd(k, plan=plan)
+            st = osdp.osdp_profile_end()
+            assert (st["gather"]["launches"] == 0) == (staged == -1)
+            if staged == -1:
+                assert (st["gemm_fwd"]["launches"], st["gemm_dw"]["launches"], st["gemm_dx"]["launches"]) == (1, 1, 1)
+            got[staged] = op.results()
+        for name in ("Y", "dX", "dW"):
+            H.assert_close(name, got[-1][name], want[name])
+            if name != ("dX", "Y")[dim] or (I if dim else O) // k % 16 == 0:
+                assert np.array_equal(got[-1][name], got[1][name]), f"{name} differs from the staged schedule (dim {dim})"
+
+
 @pytest.mark.parametrize("rows", [False, True])
 @pytest.mark.parametrize("T,I,O,N,k,mask", [(7, 256, 512, 4, 4, 0b0110), (40, 264, 528, 4, 3, 0b001), (100, 40, 1200, 3, 5, 0b00000)])
 def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows):
