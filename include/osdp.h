@@ -15,7 +15,9 @@
  *                dX               = sum_j dY[:, c0_j:c1_j] . Ws_j^T   (sum)
  *
  * where Ws_j[I x w_j] is slice j gathered from the N shards into a staging
- * buffer.  All three recombine to exactly the unsplit product.
+ * buffer.  All three recombine to exactly the unsplit product.  Where it is faster and gives the same bits, the
+ * library computes the sum from slices of the same size along the other dimension of W instead
+ * (dX[:, r0_j:r1_j] = dY . Wr_j^T below), which needs no partial sum in memory.
  *
  * A plan may instead cut an operator along W's rows (input features), which is
  * the scheme Section 3.3 prints: the input is cut along its last dimension, the
@@ -412,6 +414,10 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
  *   "fused_gather"  -1 | 0   0: every gather is a launch of its own (on stream_copy where the pipeline overlaps);
  *                            otherwise a GEMM launch takes the next slice's gather along wherever it can
  *   "fwd_pair"      -1 .. 1  0: the forward never runs two staged slices in one launch; 1: whenever it can
+ *   "recut"         -1 .. 1  0: a pass that adds its slices up (dX of column slices, Y of row slices) always gathers
+ *                            them along the plan's dimension; otherwise it gathers slices of the same bytes along
+ *                            the other one, which need no fp32 sum in the workspace, where the library estimates
+ *                            that faster and the result bits stay the same; 1: wherever the bits stay the same
  *   "poison_staging" 0 | 1   1: a staging slot is filled with bf16 NaN patterns when a call starts and again as
  *                            soon as the last GEMM that reads its slice has been enqueued (on the compute
  *                            stream, ahead of the event that hands the slot to the next gather): a GEMM that

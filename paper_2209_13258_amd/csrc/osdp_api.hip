@@ -379,6 +379,64 @@ osdp_status resolve(const osdp_shape *shape, const osdp_plan *plan, int32_t op_i
   return OSDP_OK;
 }
 
+// The pass cut the other way round, where its launches would add up through an fp32 sum in the workspace (dX of column
+// slices, Y of row slices): slices of the same number of bytes along the other dimension of W hold the whole reduction
+// of their outputs, so the sum stays in the accumulators, in the same order, and is never written out and read back
+// (launches that start on multiples of 32, the K step of every kernel, add in exactly the same order: the same bits).
+// Taken where the estimate is clearly lower: each trip of a sum of T x D elements costs its 8 bytes an element at
+// 4.5 TB/s (no kernel here hides it: every CU loads and stores its tile in step with the others), against launches
+// whose output is a slice wide, which may leave CUs idle.  Measured, the dX launches of one operator: 4096 tokens,
+// 32768 -> 8192 at k = 8 (a 512 MiB sum) 2360 -> 1560 us; 8192 tokens, 10240 -> 2560 at k = 16 1410 -> 480 us; 8192
+// tokens, 4096 -> 1024 at k = 4 141 -> 87 us.  4096 tokens, 8192 -> 32768 keeps its columns: the sum is a quarter as
+// large, and launches of 2048 output columns would fill half of the CUs.
+// The gathered bytes, the slots and the workspace asked for stay those of the plan's cut.
+bool recut(const osdp_shape *shape, const Resolved &r, bool is_fwd, Resolved *out) {
+  const DebugOptions &d = debug_options();
+  const int forced = d.recut.load(std::memory_order_relaxed);  // testing: 0 never, 1 whenever the slices allow it
+  const std::vector<Slice> &sum = is_fwd ? r.fwd : r.pass;
+  if (forced == 0 || r.any_dp || is_fwd != r.rows || sum.size() < 2 || r.k > r.D) return false;
+  // (the switches that pick a kernel or a schedule for the plan's cut keep that cut)
+  if (forced < 0 && (d.gemm_generic.load(std::memory_order_relaxed) != 0 || d.poison_staging.load(std::memory_order_relaxed) != 0 ||
+                     d.tile.load(std::memory_order_relaxed) >= 0 || d.fwd_pair.load(std::memory_order_relaxed) >= 0 ||
+                     d.fused_gather.load(std::memory_order_relaxed) >= 0 || d.four_wave.load(std::memory_order_relaxed) >= 0 ||
+                     d.persistent.load(std::memory_order_relaxed) >= 0))
+    return false;
+  for (const Slice &l : sum)
+    if (r.sub[l.c0].c0 % 32) return false;
+  const int64_t len = r.rows ? r.I : r.O;  // the plan's split dimension; the other way it is the slices' full length
+  const int64_t unit = r.mode == OSDP_STAGING_HALF ? 16 : 8;
+  for (int64_t j = 0; j < r.k; ++j) {
+    int64_t c0, c1;
+    slice_bounds(r.D, r.k, j, &c0, &c1);
+    if (c0 % 8 || c1 % 8 || (c1 - c0) % unit) return false;
+    const size_t staged = static_cast<size_t>(len) * static_cast<size_t>(r.mode == OSDP_STAGING_HALF ? (c1 - c0) / 2 : c1 - c0) * 2;
+    if (staged > r.slot_bytes) return false;
+  }
+  osdp_shape other_shape = *shape;
+  other_shape.k = r.k;
+  const uint8_t dim = is_fwd ? OSDP_SPLIT_OUT_FEATURES : OSDP_SPLIT_IN_FEATURES;
+  const osdp_plan other_plan = {1, nullptr, nullptr, r.mode, &dim};
+  if (resolve(&other_shape, &other_plan, 0, true, !is_fwd, out) != OSDP_OK) return false;  // (cannot fail: all it asks for holds)
+  if (out->slots != r.slots || out->slot_bytes > r.slot_bytes) return false;
+  out->acc_bytes = out->parts_bytes = 0;  // one chain, as the sum is
+  if (forced == 1) return true;
+  auto us = [&](const Resolved &q, bool adds) {
+    double t = 0.0;
+    for (const Slice &l : is_fwd ? q.fwd : q.pass) {
+      const int64_t span = q.sub[l.c1 - 1].c1 - q.sub[l.c0].c0;
+      t += adds ? gemm_estimate_us(q.T, q.D, span) : gemm_estimate_us(q.T, span, q.D);
+    }
+    if (adds) t += static_cast<double>(sum.size() - 1) * 8.0 * static_cast<double>(q.T) * static_cast<double>(q.D) / 4.5e6;
+    if (!is_fwd)
+      for (const Slice &l : q.dw) {
+        const int64_t span = q.sub[l.c1 - 1].c1 - q.sub[l.c0].c0;
+        t += q.rows ? gemm_estimate_us(span, q.O, q.T) : gemm_estimate_us(q.I, span, q.T);
+      }
+    return t;
+  };
+  return us(*out, false) < 0.95 * us(r, true);
+}
+
 // Staging slots, the fp32 partial sum, the planes of concatenating launches split along K.
 size_t workspace_total(const Resolved &r) { return r.slot_bytes * r.slots + r.acc_bytes + r.parts_bytes; }
 
@@ -775,6 +833,7 @@ struct DebugSwitch {
 const DebugSwitch kSwitches[] = {
     {"gemm_generic", &DebugOptions::gemm_generic, 0, 1}, {"tile", &DebugOptions::tile, -1, 3},
     {"deep", &DebugOptions::deep, -1, 1},                {"split_launch", &DebugOptions::split_launch, -1, 1},
+    {"recut", &DebugOptions::recut, -1, 1},
     {"fwd_pair", &DebugOptions::fwd_pair, -1, 1},        {"poison_staging", &DebugOptions::poison_staging, 0, 1},
     {"persistent", &DebugOptions::persistent, -1, 1},    {"split_k", &DebugOptions::split_k, -1, 1},          {"four_wave", &DebugOptions::four_wave, -1, 1},      {"fused_gather", &DebugOptions::fused_gather, -1, 1},
 };
@@ -904,6 +963,8 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
     OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, shard_gemm(r, true, tab, X, ldx, Y, ldy), sc));
     return OSDP_OK;
   }
+  Resolved other;
+  if (recut(shape, r, true, &other)) r = std::move(other);
 
   char *ws = static_cast<char *>(workspace);
   float *acc = reinterpret_cast<float *>(ws + r.slot_bytes * r.slots);  // row slices: Y's fp32 partial sum
@@ -1087,6 +1148,8 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
       OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DX, shard_gemm(r, false, tab, dY, lddy, dX, lddx), sc));
     return OSDP_OK;
   }
+  Resolved other;
+  if (recut(shape, r, false, &other)) r = std::move(other);
   char *ws = static_cast<char *>(workspace);
   float *acc = reinterpret_cast<float *>(ws + r.slot_bytes * r.slots);  // column slices: dX's fp32 partial sum
   void *planes = r.parts_bytes ? ws + r.slot_bytes * r.slots + r.acc_bytes : nullptr;  // row slices: planes of dX launches split along K

@@ -163,6 +163,7 @@ struct DebugOptions {
   std::atomic<int32_t> deep{-1};           // 0: launches of at most one tile per CU keep the shallow pipelines
   std::atomic<int32_t> split_launch{-1};   // 0: no whole-rounds + remainder launches
   std::atomic<int32_t> fwd_pair{-1};       // 0: the forward never pairs staged slices; 1: whenever the kernel can
+  std::atomic<int32_t> recut{-1};          // 0: a pass that adds slices up keeps the plan's cut; 1: it is cut the other way wherever the slices allow
   std::atomic<int32_t> fused_gather{-1};   // 0: gathers always run as launches of their own (second stream where given)
   std::atomic<int32_t> four_wave{-1};      // 0: 256 x 256 tiles run on the eight-wave kernel; 1: on the four-wave kernel wherever it can
   std::atomic<int32_t> persistent{-1};     // 0: launches of more 256 x 256 tiles than CUs keep the plain four-wave kernel instead of its persistent form; 1: the persistent form for any number of tiles

@@ -16,7 +16,7 @@ def H():
     return gpu_harness
 
 
-DEBUG_DEFAULTS = {"persistent": -1, "split_k": -1, "four_wave": -1, "fused_gather": -1, "gemm_generic": 0, "tile": -1, "deep": -1, "split_launch": -1, "fwd_pair": -1, "poison_staging": 0}
+DEBUG_DEFAULTS = {"persistent": -1, "split_k": -1, "four_wave": -1, "fused_gather": -1, "gemm_generic": 0, "tile": -1, "deep": -1, "split_launch": -1, "fwd_pair": -1, "recut": -1, "poison_staging": 0}
 
 
 @pytest.fixture
@@ -908,6 +908,42 @@ def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows)
         H.assert_close("dX", got["dX"], want["dX"])
         H.assert_close("dW", dW, want["dW"])
         assert all((a == POISON).all() for a in in_dp + outside)
+
+
+@pytest.mark.parametrize("T,I,O,N,k", [
+    (513, 768, 256, 4, 2),         # the fewest tokens that stage slices
+    (700, 1024, 384, 3, 4),        # shards that are not row blocks; row slices of 256, column slices of 96
+    (1100, 4096, 512, 8, 5),       # k divides neither side: row slices of 819.2 are refused, the plan's cut stays
+    (640, 2560, 1280, 8, 4),
+])
+def test_a_pass_cut_the_other_way_keeps_the_bits_of_the_sum(H, oracle, T, I, O, N, k, debug):
+    """dX of column slices and Y of row slices, computed from slices along the other dimension: the bits of the sum
+    over the plan's own slices in every staging mode, nothing read from a slot that holds no live slice, and the
+    oracle's values."""
+    import paper_2209_13258_amd as osdp
+    for dim in (0, 1):
+        rows, cols = (I, O) if dim == 0 else (O, I)
+        d = wl.small_case(78, T, rows, cols, N)
+        want = oracle.linear(d["X"], d["W_shards"], cols, dY=d["dY"])
+        for mode in (osdp.OSDP_STAGING_SINGLE, osdp.OSDP_STAGING_DOUBLE, osdp.OSDP_STAGING_HALF):
+            plan = osdp.Plan([k], staging=mode, split_dim_per_op=[dim])
+            try:
+                osdp.osdp_split_linear_workspace_bytes(T, rows, cols, N, k, True, plan, 0)
+            except osdp.OsdpError:
+                continue  # slices that the plan's own cut refuses
+            got = {}
+            for recut in (0, 1):
+                debug("recut", recut)
+                debug("poison_staging", recut)
+                _announce("the other cut", T, rows, cols, N, k, "dim", dim, "mode", mode, "recut", recut)
+                op = H.Operator(d["X"], d["dY"], d["W_shards"], cols)
+                for _ in range(2):
+                    op.fwd(k, plan=plan)
+                    op.bwd(k, plan=plan)
+                got[recut] = op.results()
+            for name in ("Y", "dX", "dW"):
+                H.assert_close(name, got[1][name], want[name])
+                assert np.array_equal(got[1][name], got[0][name]), f"{name} differs from the plan's own cut (dim {dim}, mode {mode})"
 
 
 # ------------------------------------------------ the persistent form of the four-wave kernel
