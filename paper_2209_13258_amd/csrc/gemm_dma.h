@@ -167,11 +167,13 @@ struct OperandSource {
   uint32_t lane;     // byte offset of this lane in its wave's load 0
   uint32_t ld2;      // bytes from one row to the next
 
-  // The block at `origin`, of a tile with mn_left rows / columns of the matrix from its first one on.
+  // The block at `origin`, of a tile with mn_left rows / columns of the matrix from its first one on.  (kRows, the
+  // tile's own, may be fewer than the LDS layout of Op holds: the surplus lanes fetch nothing.)
   __device__ __forceinline__ void begin(const uint16_t *origin, int64_t ld, int mn_left, int wave, int lane_id) {
+    mn_left = mn_left < kRows ? mn_left : kRows;
     base = uniform64(reinterpret_cast<uint64_t>(origin)) & 0xffffffffffffull;
     ld2 = static_cast<uint32_t>(ld) * 2;
-    bytes = kKC ? static_cast<uint32_t>(mn_left < kRows ? mn_left : kRows) * ld2 : kBK * ld2;
+    bytes = kKC ? static_cast<uint32_t>(mn_left) * ld2 : kBK * ld2;
     lane = static_cast<uint32_t>(Op::lane_src(wave, lane_id, ld) * 2);
     if (!kKC) lane = Op::lane_pos(wave, lane_id) < mn_left ? lane : kOutOfRange;
   }

@@ -16,7 +16,7 @@
 // Same MFMA sequence per output element as every other GEMM kernel of the library (K ascending in steps of 32,
 // v_mfma_f32_16x16x32_bf16, the same lane -> k map), so the result bits are the same.
 //
-// Any M and N, K > 128 (k_split % 64 == 0, n_split % 256 == 0): edges are handled by the range check of the operand
+// Tiles of 32 * MB x 32 * NB, the large one (8 x 8) wherever its rounds are full.  Any M and N, K > 128 (k_split % 64 == 0, n_split % 256 == 0): edges are handled by the range check of the operand
 // loads and guarded stores (OperandSource in gemm_dma.h).
 #pragma once
 #include "gemm_common.h"
@@ -38,11 +38,14 @@ __device__ __forceinline__ void mma_16x16x32_agpr(f32x4 &c, bf16x8 a_rows, bf16x
 
 // One operand's share of a ring slot: 256 rows (or columns) x 64 k, 32 KB, filled by 32 wave-level
 // direct-to-LDS loads of 1 KB, eight per wave.
-template <bool kKC>
+// kBlocks: 16-row blocks of a wave tile, 8 or fewer: of a tile of 32 * kBlocks rows.  A smaller tile keeps the places of
+// the large one in LDS (the swizzles work on runs of 128); what lies beyond its rows is not fetched: of a K-contiguous
+// operand by fewer loads, of the other kind by lanes that are out of range.
+template <bool kKC, int kBlocks>
 struct W4Operand {
   static constexpr int kRows = 256, kBK = 64, kWaves = 4;
-  static constexpr int kElems = kRows * kBK;  // 32 KB
-  static constexpr int kLoads = 8;            // per wave and block
+  static constexpr int kElems = kRows * kBK;         // 32 KB
+  static constexpr int kLoads = kKC ? kBlocks : 8;   // per wave and block
   using Base = DmaOperand<kKC, kRows, kBK, kWaves>;
   // 1 KB chunk that load p of wave w fills.  K-contiguous: chunk c = rows 8c .. 8c+7.  MN-contiguous: chunk c =
   // k-rows 2c, 2c+1, with (c & 1) and ((c >> 2) & 1) fixed over a wave's loads (the source swizzle depends on them).
@@ -71,6 +74,13 @@ struct W4Operand {
   static __device__ __forceinline__ bf16x8 frag(const uint16_t *slot, int mn0, int kk, int lane) { return Base::frag(slot, mn0, kk, lane); }
 };
 
+// Load l of the L per block goes out behind MFMA (l * N) / L + 2 of the N in a K step; l, or -1, for a given MFMA.
+constexpr int w4_load_behind(int i, int N, int L) {
+  for (int l = 0; l < L; ++l)
+    if (l * N / L + 2 == i) return l;
+  return -1;
+}
+
 // kCopy: the launch also carries p.job, the gather of a slice that a later launch will read (the forward GEMM of
 // slice j gathers slice j+1 into the other staging slot; a dW launch, which needs no weights, gathers the slices of
 // the dX pass that follows it).  Every workgroup copies total_vecs / gridDim.x vectors, 256 per K block: one 16-byte
@@ -79,15 +89,14 @@ struct W4Operand {
 // stream it only takes turns with the tiles, and both get slower.  The carried copy is not free either (the kernel
 // is bound by the memory pipe the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a
 // launch of its own); it saves the launch, its gap and every cross-stream event.
-template <bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
-__global__ __launch_bounds__(256, 1)
-void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int BM = 256, BN = 256, WM = 128, WN = 128;
-  constexpr int MB = WM / 16, NB = WN / 16;
-  using OpA = W4Operand<kAK>;
-  using OpB = W4Operand<kBKc>;
+template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy>
+__device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, int tiles_n) {
+  constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
+  using OpA = W4Operand<kAK, MB>;
+  using OpB = W4Operand<kBKc, NB>;
+  static_assert(3 * (MB + NB) <= MB * NB + 1, "the fragment reads of a K step, one behind every third MFMA");
   constexpr int kSlotElems = OpA::kElems + OpB::kElems;  // 64 KB
-  constexpr int L = OpA::kLoads + OpB::kLoads;           // 16 wave-level loads per wave and block
+  constexpr int L = OpA::kLoads + OpB::kLoads;           // wave-level loads per wave and block (16 for 256 x 256)
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t *const *s_tab = nullptr;
   if constexpr (kEpi == static_cast<int>(Epilogue::kBf16ShardMajor)) {
@@ -224,11 +233,11 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
         if constexpr (r < NB) fb[Q][r] = OpB::frag(nB, wn + r * 16, rk, lane);
         else fa[Q][r - NB] = OpA::frag(nA, wm + (r - NB) * 16, rk, lane);
       }
-      if constexpr (kLoad && i % 4 == 2) issue(ls, Int<i / 4>{});
+      if constexpr (kLoad && w4_load_behind(i, MB * NB, L) >= 0) issue(ls, Int<w4_load_behind(i, MB * NB, L)>{});
       // carried gather: in the block's first K step the address of the next piece is worked out; in the second,
       // just behind the barrier where every load has landed, the piece in registers goes out and the next comes in
       // (all three behind one uniform test: once the range is copied the remaining K blocks issue nothing for it)
-      if constexpr (kCopy && !kLoad && i == 40) {
+      if constexpr (kCopy && !kLoad && i == MB * NB * 5 / 8) {
         if (copy_i + 1 < copy_pieces) copy_ptr = copy_src(copy_i + 1, &copy_next_v);
       }
       if constexpr (kCopy && kLoad && i == 0) {
@@ -274,6 +283,19 @@ void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");
   store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
+}
+
+template <bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
+__global__ __launch_bounds__(256, 1)
+void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4_tile<8, 8, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+}
+
+// Tiles of fewer than 256 rows or columns: 32 * MB x 32 * NB.
+template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
+__global__ __launch_bounds__(256, 1)
+void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4_tile<MB, NB, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
 }
 
 }  // namespace

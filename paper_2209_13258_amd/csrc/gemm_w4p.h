@@ -41,15 +41,14 @@ __device__ __forceinline__ f32x4 acc_read(const f32x4 &c) {
   return f32x4{x0, x1, x2, x3};
 }
 
-template <bool kAK, bool kBKc, int kEpi, bool kAccIn>
-__global__ __launch_bounds__(256, 1)
-void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int BM = 256, BN = 256, WM = 128, WN = 128;
-  constexpr int MB = WM / 16, NB = WN / 16;
-  using OpA = W4Operand<kAK>;
-  using OpB = W4Operand<kBKc>;
+template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn>
+__device__ __forceinline__ void gemm_w4p_tiles(const GemmParams &p, int tiles_m, int tiles_n) {
+  constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
+  using OpA = W4Operand<kAK, MB>;
+  using OpB = W4Operand<kBKc, NB>;
+  static_assert(3 * (MB + NB) <= MB * NB + 1, "the fragment reads of a K step, one behind every third MFMA");
   constexpr int kSlotElems = OpA::kElems + OpB::kElems;  // 64 KB
-  constexpr int L = OpA::kLoads + OpB::kLoads;           // 16 wave-level loads per wave and block
+  constexpr int L = OpA::kLoads + OpB::kLoads;           // wave-level loads per wave and block (16 for 256 x 256)
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t *const *s_tab = nullptr;
   if constexpr (kEpi == static_cast<int>(Epilogue::kBf16ShardMajor)) {
@@ -164,9 +163,9 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
         if constexpr (r < NB) fb[Q][r] = OpB::frag(nB, wn + r * 16, rk, lane);
         else fa[Q][r - NB] = OpA::frag(nA, wm + (r - NB) * 16, rk, lane);
       }
-      if constexpr (kLoad && i % 4 == 2) {
-        issue(ls, Int<i / 4>{});
-        if constexpr (i / 4 == L - 1) block_issued();
+      if constexpr (kLoad && w4_load_behind(i, MB * NB, L) >= 0) {
+        issue(ls, Int<w4_load_behind(i, MB * NB, L)>{});
+        if constexpr (w4_load_behind(i, MB * NB, L) == L - 1) block_issued();
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -222,6 +221,19 @@ void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
     }
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
+}
+
+template <bool kAK, bool kBKc, int kEpi, bool kAccIn>
+__global__ __launch_bounds__(256, 1)
+void gemm_w4p_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4p_tiles<8, 8, kAK, kBKc, kEpi, kAccIn>(p, tiles_m, tiles_n);
+}
+
+// Tiles of fewer than 256 rows or columns: 32 * MB x 32 * NB.
+template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn>
+__global__ __launch_bounds__(256, 1)
+void gemm_w4p_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4p_tiles<MB, NB, kAK, kBKc, kEpi, kAccIn>(p, tiles_m, tiles_n);
 }
 
 }  // namespace

@@ -831,7 +831,7 @@ struct DebugSwitch {
   int32_t lo, hi;  // accepted values; the default of the field stands for "not set"
 };
 const DebugSwitch kSwitches[] = {
-    {"gemm_generic", &DebugOptions::gemm_generic, 0, 1}, {"tile", &DebugOptions::tile, -1, 3},
+    {"gemm_generic", &DebugOptions::gemm_generic, 0, 1}, {"tile", &DebugOptions::tile, -1, 5},
     {"deep", &DebugOptions::deep, -1, 1},                {"split_launch", &DebugOptions::split_launch, -1, 1},
     {"recut", &DebugOptions::recut, -1, 1},
     {"fwd_pair", &DebugOptions::fwd_pair, -1, 1},        {"poison_staging", &DebugOptions::poison_staging, 0, 1},

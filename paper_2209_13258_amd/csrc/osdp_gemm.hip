@@ -198,16 +198,19 @@ hipError_t launch_dma(const GemmParams &p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The four-wave 256 x 256 kernel: two K blocks of 64 in LDS (128 KB).
-template <bool kAK, bool kBK, int kEpi, bool kAccIn, bool kCopy>
+// The four-wave kernel, two K blocks of 64 in LDS (128 KB): 256 x 256 tiles, or fewer rows or columns (32 per block).
+template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn, bool kCopy>
 hipError_t launch_w4(const GemmParams &p, hipStream_t stream) {
   constexpr size_t lds = 2 * (256 + 256) * 64 * sizeof(uint16_t);
   static_assert(lds + 2 * OSDP_MAX_SHARDS * 8 <= 160 * 1024, "tile does not fit the 160 KB of LDS");
-  auto kernel = gemm_w4_kernel<kAK, kBK, kEpi, kAccIn, kCopy>;
+  auto kernel = [] {
+    if constexpr (MB == 8 && NB == 8) return gemm_w4_kernel<kAK, kBK, kEpi, kAccIn, kCopy>;
+    else return gemm_w4_small_kernel<MB, NB, kAK, kBK, kEpi, kAccIn, kCopy>;
+  }();
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = (p.M + 255) / 256, tiles_n = tile_columns_of(p, 256);
+  const int tiles_m = (p.M + 32 * MB - 1) / (32 * MB), tiles_n = tile_columns_of(p, 32 * NB);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -245,14 +248,17 @@ constexpr int kCUs = 256;
 thread_local int64_t t_persistent_launches = 0;
 
 // The persistent form of the four-wave kernel: one workgroup per CU walks through the tiles.
-template <bool kAK, bool kBK, int kEpi, bool kAccIn>
+template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
   constexpr size_t lds = 2 * (256 + 256) * 64 * sizeof(uint16_t);
-  auto kernel = gemm_w4p_kernel<kAK, kBK, kEpi, kAccIn>;
+  auto kernel = [] {
+    if constexpr (MB == 8 && NB == 8) return gemm_w4p_kernel<kAK, kBK, kEpi, kAccIn>;
+    else return gemm_w4p_small_kernel<MB, NB, kAK, kBK, kEpi, kAccIn>;
+  }();
   static bool configured[kMaxDevices] = {};
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
-  const int tiles_m = (p.M + 255) / 256, tiles_n = tile_columns_of(p, 256);
+  const int tiles_m = (p.M + 32 * MB - 1) / (32 * MB), tiles_n = tile_columns_of(p, 32 * NB);
   const int tiles = tiles_m * tiles_n * (p.k_parts > 1 ? p.k_parts : 1);
   hipLaunchKernelGGL(kernel, dim3(tiles < kCUs ? tiles : kCUs), dim3(256), lds, stream, p, tiles_m, tiles_n);
   t_persistent_launches += 1;
@@ -272,7 +278,7 @@ long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM
 double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1) {
   const long tiles = tile_count(M, N, BM, BN) * parts;
   const long per_cu = (tiles + kCUs - 1) / kCUs;
-  const bool two_per_cu = BM * BN < 256 * 256;
+  const bool two_per_cu = BM * BN <= 256 * 128;
   const double units = (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5 : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
 }
@@ -306,21 +312,38 @@ struct TileShape {
 // the forward launch over two 256-column slices with K = 4096 64 -> 52 us.  The lone 128x128 workgroup also runs
 // as 8 waves of 32x64 rather than 4 of 64x64, two per SIMD (another 3-10 %; without the deep pipeline it made no
 // difference).
-constexpr TileShape kTiles[4] = {{256, 256, {1.0, 1.0, 1.0}},
-                                 {256, 128, {1.37, 1.40, 1.33}},
-                                 {128, 256, {1.21, 1.23, 1.37}},
-                                 {128, 128, {1.39, 1.20, 1.40}}};
+// The last two run on the four-wave kernel alone, in the layouts where they were measured (0: not offered).  They fill
+// rounds that whole tiles leave partly empty; the smaller the tile the more bytes from L2 each MFMA needs, which is
+// what the penalties are (7 % more for 224 x 256, 30 % more for 256 x 160).  dW of 2560 x 5120 over 16384 tokens: 200
+// tiles of 256 rows 412 us, 240 of 224 rows 382 us.  8192 x 1280 over K = 2560: 160 tiles of 256 columns 60 us, 256
+// tiles of 160 columns 51 us (dX 48 us); where they only replace full rounds the narrow tiles lose (16384 x 2560 over
+// K = 2560 in 4 rounds 240 us, against 196 us for two rounds of large tiles and a remainder).
+constexpr int kTileShapes = 6;
+constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}},
+                                           {256, 128, {1.37, 1.40, 1.33}},
+                                           {128, 256, {1.21, 1.23, 1.37}},
+                                           {128, 128, {1.39, 1.20, 1.40}},
+                                           {224, 256, {0.0, 1.06, 0.0}},
+                                           {256, 160, {1.30, 0.0, 1.28}}};
+constexpr int kNarrowMinK = 2048;
 
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
+
+// Whether tile shape i serves a launch of the layout with K as the reduction of a workgroup: the four-wave kernel's own
+// shapes from where that kernel is the faster one for dW, and else from a K loop that pays for its start-up.
+bool tile_offered(int i, int kind, int K) {
+  return i < 4 || (kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinKdW : kNarrowMinK) &&
+                   debug_options().four_wave.load(std::memory_order_relaxed) != 0);
+}
 
 // Cheapest tile for M x N; a column split must fall on a tile boundary.
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
-int best_tile(int M, int N, int n_split, int kind, double *cost, int parts = 1) {
+int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1) {
   int best = -1;
   double best_cost = 0.0;
-  for (int i = 0; i < 4; ++i) {
-    if (n_split % kTiles[i].bn) continue;
+  for (int i = 0; i < kTileShapes; ++i) {
+    if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts)) continue;
     const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts);
     if (best < 0 || c < best_cost) {
       best = i;
@@ -358,16 +381,36 @@ double combine_estimate_us(int64_t M, int64_t N, int parts) {
   return (4.0 * parts + 2.0) * static_cast<double>(M) * static_cast<double>(N) / 3.0e6 + 8.0;
 }
 
+// The four-wave kernel in the form that suits the number of tiles.
+template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn>
+hipError_t launch_four_wave(const GemmParams &p, hipStream_t stream, bool *carry) {
+  const int parts = p.k_parts > 1 ? p.k_parts : 1;
+  // More tiles than CUs: the persistent form overlaps each tile's start-up with its predecessor's end
+  // (3-12 % per launch).  It takes no gather along: *carry stays as it is and the caller launches the
+  // gather by itself, which measured better on every workload than keeping the plain kernel for its sake.
+  const int pst = debug_options().persistent.load(std::memory_order_relaxed);  // testing: 0 never, 1 for any number of tiles
+  if (pst != 0 && !(parts > 1 && (p.k_split || kAccIn)) && (pst == 1 || tile_count(p.M, p.N, 32 * MB, 32 * NB) * parts > kCUs))
+    return launch_w4p<MB, NB, kAK, kBK, kEpi, kAccIn>(p, stream);
+  if constexpr (!(kAK && kBK)) {  // dX launches read every staged slice there is: they never carry a gather
+    if (*carry) {
+      *carry = false;
+      return launch_w4<MB, NB, kAK, kBK, kEpi, kAccIn, true>(p, stream);
+    }
+  }
+  return launch_w4<MB, NB, kAK, kBK, kEpi, kAccIn, false>(p, stream);
+}
+
 // *carry: the launch has a gather to carry (GemmParams::job is filled in); cleared by the launch that takes it.
 template <bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   constexpr int kind = layout_kind(kAK, kBK);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
   if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
-    int best = best_tile(p.M, p.N, p.n_split, kind, nullptr, parts);
-    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 where it fits the segments of B
-    const bool force = forced >= 0 && forced <= 3;
-    if (force && p.n_split % kTiles[forced].bn == 0) best = forced;
+    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts);
+    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..5 where it fits the layout and the segments of B
+    const bool force = forced >= 0 && forced < kTileShapes;
+    if (force && p.n_split % kTiles[forced].bn == 0 && (forced < 4 || (kTiles[forced].penalty[kind] > 0.0 && p.K / parts >= kW4MinK)))
+      best = forced;
     // A dX launch with a short reduction whose fp32 partial sum comes from or goes to memory is bound by that
     // traffic, and with only a round or two of large tiles every CU loads, computes and stores in step with the
     // others: two smaller workgroups per CU overlap one's loads and stores with the other's MFMAs (8192 x 4096 with
@@ -377,7 +420,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
       best = p.n_split % 256 == 0 ? 2 : 1;
     // A launch of at most one tile per CU cannot hide the latency of its loads behind a second workgroup: it gets
     // the whole LDS for a deeper pipeline instead (twice the bytes in flight).
-    const bool deep = best > 0 && tile_count(p.M, p.N, kTiles[best].bm, kTiles[best].bn) * parts <= kCUs &&
+    const bool deep = best > 0 && best < 4 && tile_count(p.M, p.N, kTiles[best].bm, kTiles[best].bn) * parts <= kCUs &&
                       debug_options().deep.load(std::memory_order_relaxed) != 0;  // testing: 0 keeps the shallow pipelines
     const int fw = debug_options().four_wave.load(std::memory_order_relaxed);  // testing: 0 never, 1 whenever it can
     switch (best) {
@@ -385,20 +428,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         // (dW, both operands MN-contiguous: twice the fragment-read instructions and a serial epilogue per wave;
         // measured through the library, the four-wave kernel is 4-9 % ahead from K = 8192 and 3 % behind at K = 4096)
         if (p.K / parts >= kW4MinK && fw != 0 && (fw == 1 || p.K >= (kind == 1 ? kW4MinKdW : kW4MinK))) {
-          // More tiles than CUs: the persistent form overlaps each tile's start-up with its predecessor's end
-          // (3-12 % per launch).  It takes no gather along: *carry stays as it is and the caller launches the
-          // gather by itself, which measured better on every workload than keeping the plain kernel for its sake.
-          const int pst = debug_options().persistent.load(std::memory_order_relaxed);  // testing: 0 never, 1 for any number of tiles
-          if (pst != 0 && !(parts > 1 && (p.k_split || kAccIn)) &&
-              (pst == 1 || tile_count(p.M, p.N, 256, 256) * parts > kCUs))
-            return launch_w4p<kAK, kBK, kEpi, kAccIn>(p, stream);
-          if constexpr (!(kAK && kBK)) {  // dX launches read every staged slice there is: they never carry a gather
-            if (*carry) {
-              *carry = false;
-              return launch_w4<kAK, kBK, kEpi, kAccIn, true>(p, stream);
-            }
-          }
-          return launch_w4<kAK, kBK, kEpi, kAccIn, false>(p, stream);
+          return launch_four_wave<8, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
         }
         if (kind == 0) return launch_dma<256, 256, 64, 128, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
         return launch_dma<256, 256, 64, 128, 32, 4, kAK, kBK, kEpi, kAccIn>(p, stream);
@@ -412,6 +442,12 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         if (deep) return launch_dma<128, 128, 32, 64, 64, 4, kAK, kBK, kEpi, kAccIn>(p, stream);  // 8 waves of 32 x 64
         if (kind == 1) return launch_dma<128, 128, 64, 64, 32, 4, kAK, kBK, kEpi, kAccIn>(p, stream);
         return launch_dma<128, 128, 64, 64, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
+      case 4:
+        if constexpr (kind == 1) return launch_four_wave<7, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
+        break;
+      case 5:
+        if constexpr (kind != 1) return launch_four_wave<8, 5, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
+        break;
     }
   }
   if (p.k_split % GBK || p.n_split % GBN || p.seg_k || p.seg_n) return hipErrorInvalidValue;
@@ -453,7 +489,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
   double whole = 0.0;
   *axis = -1;
   *cut = 0;
-  best_tile(M, N, 0, kind, &whole);
+  best_tile(M, N, K, 0, kind, &whole);
   // testing: split_launch = 0 keeps every problem in one launch, as does a forced tile shape
   if (debug_options().split_launch.load(std::memory_order_relaxed) == 0 ||
       debug_options().tile.load(std::memory_order_relaxed) >= 0)
@@ -467,7 +503,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cn = static_cast<int>(static_cast<long>(kCUs) * r / tm);
     if (cn <= 0) continue;
     if (cn >= tn) break;
-    best_tile(M, N - cn * 256, 0, kind, &rest);
+    best_tile(M, N - cn * 256, K, 0, kind, &rest);
     const double c = tile_cost(M, cn * 256, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 1; *cut = cn * 256; }
   }
@@ -475,7 +511,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cm = static_cast<int>(static_cast<long>(kCUs) * r / tn);
     if (cm <= 0) continue;
     if (cm >= tm) break;
-    best_tile(M - cm * 256, N, 0, kind, &rest);
+    best_tile(M - cm * 256, N, K, 0, kind, &rest);
     const double c = tile_cost(cm * 256, N, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 0; *cut = cm * 256; }
   }
@@ -548,10 +584,10 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   // forward launch grouping of config 3 slightly worse)
   double cost = 0.0;
   if (M > 0 && fast_path(static_cast<int>(K), 0, 0)) {
-    best_tile(static_cast<int>(M), static_cast<int>(N), 0, 0, &cost);
+    best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost);
     const int parts = forward_parts ? forward_k_parts(M, K) : 1;
     if (parts > 1) {
-      best_tile(static_cast<int>(M), static_cast<int>(N), 0, 0, &cost, parts);
+      best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, parts);
       return cost / parts * 2.0 * static_cast<double>(K) / 5.0e6 + combine_estimate_us(M, N, parts) + 6.0;
     }
     return cost * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;

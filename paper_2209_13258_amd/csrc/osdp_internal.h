@@ -159,7 +159,7 @@ hipError_t launch_fill16(void *dst, size_t bytes, uint16_t pattern, hipStream_t 
 // applies; the environment is consulted once, when the library is loaded, for their initial values.
 struct DebugOptions {
   std::atomic<int32_t> gemm_generic{0};    // 1: every GEMM runs on the bounds-checked kernel
-  std::atomic<int32_t> tile{-1};           // 0..3: force that tile shape where it divides the problem
+  std::atomic<int32_t> tile{-1};           // 0..5: force that tile shape where it serves the launch
   std::atomic<int32_t> deep{-1};           // 0: launches of at most one tile per CU keep the shallow pipelines
   std::atomic<int32_t> split_launch{-1};   // 0: no whole-rounds + remainder launches
   std::atomic<int32_t> fwd_pair{-1};       // 0: the forward never pairs staged slices; 1: whenever the kernel can

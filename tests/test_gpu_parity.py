@@ -946,6 +946,41 @@ def test_a_pass_cut_the_other_way_keeps_the_bits_of_the_sum(H, oracle, T, I, O, 
                 assert np.array_equal(got[1][name], got[0][name]), f"{name} differs from the plan's own cut (dim {dim}, mode {mode})"
 
 
+@pytest.mark.parametrize("T,I,O,N,k", [
+    (520, 448, 320, 4, 1),        # whole tiles of 224 rows of dW; two tiles of 160 columns of Y
+    (1001, 456, 648, 3, 3),       # a tile of 8 rows or columns behind the last whole one; ragged K blocks; slices of 216
+    (576, 2240, 336, 8, 2),       # the last tile of columns is 16 wide; slices of 168
+    (4100, 264, 1288, 1, 1),      # tokens beyond the last tile; one shard
+])
+def test_four_wave_tiles_of_224_rows_and_of_160_columns(H, oracle, T, I, O, N, k, debug):
+    """The four-wave kernel's smaller tiles, one tile per workgroup (with and without a gather to carry) and as a
+    persistent kernel, for both split dimensions (so that every product runs plain and as a sum over slices): the bits
+    of the 128 x 128 tiles, and the oracle's values."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(79, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+    debug("recut", 0)
+    for dim in (0, 1):
+        plan = osdp.Plan([k], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[dim])
+        try:
+            osdp.osdp_split_linear_workspace_bytes(T, I, O, N, k, True, plan, 0)
+        except osdp.OsdpError:
+            continue  # slices that are not whole vectors
+        base = None
+        for tile, persistent in ((3, 0), (4, 0), (4, 1), (5, 0), (5, 1)):
+            debug("tile", tile)
+            debug("persistent", persistent)
+            _announce("smaller four-wave tiles", T, I, O, N, k, "dim", dim, "tile", tile, "persistent", persistent)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            op.fwd(k, plan=plan)
+            op.bwd(k, plan=plan)
+            got = op.results()
+            base = base or got
+            for name in ("Y", "dX", "dW"):
+                H.assert_close(name, got[name], want[name])
+                assert np.array_equal(got[name], base[name]), f"{name} differs from the 128 x 128 tiles (dim {dim}, tile {tile})"
+
+
 # ------------------------------------------------ the persistent form of the four-wave kernel
 @pytest.mark.parametrize("dim", [0, 1])
 def test_persistent_kernel_keeps_the_bits_of_one_tile_per_workgroup(H, oracle, debug, dim):

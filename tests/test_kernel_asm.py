@@ -100,3 +100,19 @@ def test_persistent_four_wave_kernels_use_no_scratch_and_respect_the_mfma_hazard
             assert not [t for t in near if t.startswith(("v_accvgpr_write", "v_accvgpr_mov"))], \
                 f"{name}: an accumulator register is written right in front of an inline MFMA"
         _assert_no_valu_write_in_front_of_its_mfma(name, ins, mfma)
+
+
+def test_four_wave_kernels_of_smaller_tiles_keep_the_same_rules(gemm_asm):
+    """32 * MB x 32 * NB tiles: one K block of 2 * MB * NB MFMAs (the persistent form clears as many again)."""
+    for kernel, counts in (("gemm_w4_small_kernel", (1,)), ("gemm_w4p_small_kernel", (1, 2))):
+        kernels = _kernels(gemm_asm, kernel)
+        assert len(kernels) >= 10, f"the instantiations of {kernel} were not found in the assembly"
+        for name, ins in kernels.items():
+            mb, nb = map(int, re.search(kernel + r"ILi(\d+)ELi(\d+)E", name).groups())
+            mfma = [i for i, t in enumerate(ins) if t.startswith("v_mfma")]
+            assert len(mfma) in [2 * mb * nb * c for c in counts], f"{name}: {len(mfma)} MFMAs"
+            assert not [t for t in ins[mfma[0]:mfma[-1] + 1] if t.startswith("scratch_")], f"{name}: scratch traffic inside the K loop"
+            for i in mfma:
+                assert not [t for t in ins[max(0, i - 3):i] if t.startswith(("v_accvgpr_write", "v_accvgpr_mov"))], \
+                    f"{name}: an accumulator register is written right in front of an inline MFMA"
+            _assert_no_valu_write_in_front_of_its_mfma(name, ins, mfma)
