@@ -271,15 +271,20 @@ constexpr int kW4MinKdW = 8192;
 
 // Estimated cost of covering M x N with BM x BN tiles on 256 CUs: tiles per CU times the tile's area, with a
 // penalty for the lower MFMA efficiency of smaller tiles.  Tiles that run two to a CU were measured in pairs; a
-// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  A tile that sticks out of the
-// matrix costs what a full one does.
+// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  A launch of one to two such
+// tiles per CU lasts nearly as its number of tiles: what it waits for is the memory that the CUs share (128 x 128 over
+// K = 2560: 320 tiles 38 us, 480 tiles 52 us).  A tile that sticks out of the matrix costs what a full one does.
+// lone > 0: the penalty of a launch of at most one tile per CU, which has the CU's whole LDS for its pipeline.
 long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
-double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1) {
+double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, double lone = 0.0) {
   const long tiles = tile_count(M, N, BM, BN) * parts;
   const long per_cu = (tiles + kCUs - 1) / kCUs;
   const bool two_per_cu = BM * BN <= 256 * 128;
-  const double units = (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5 : static_cast<double>(per_cu);
+  if (two_per_cu && per_cu == 1 && lone > 0.0) return lone * BM * BN;
+  const double units = (two_per_cu && per_cu == 2)  ? 0.4 + 0.8 * static_cast<double>(tiles) / kCUs
+                       : (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5
+                                                    : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
 }
 
@@ -298,6 +303,7 @@ bool fits_offsets(const GemmParams &p) { return p.lda < kMaxLd && p.ldb < kMaxLd
 struct TileShape {
   int bm, bn;
   double penalty[3];
+  double lone[3];  // the same for a launch of at most one tile per CU
 };
 // 8192^3 on MI355X, forward / dW / dX in PFLOP/s, eight-wave kernels: 256x256 1.22 / 1.23 / 1.26; 256x128 (two
 // workgroups per CU) 1.04 / 0.90 / 1.09; 128x256 (two per CU) 1.19 / 1.02 / 1.06; 128x128 (two per CU) 1.03 / 1.05 /
@@ -319,12 +325,14 @@ struct TileShape {
 // tiles of 160 columns 51 us (dX 48 us); where they only replace full rounds the narrow tiles lose (16384 x 2560 over
 // K = 2560 in 4 rounds 240 us, against 196 us for two rounds of large tiles and a remainder).
 constexpr int kTileShapes = 6;
-constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}},
-                                           {256, 128, {1.37, 1.40, 1.33}},
-                                           {128, 256, {1.21, 1.23, 1.37}},
-                                           {128, 128, {1.39, 1.20, 1.40}},
-                                           {224, 256, {0.0, 1.06, 0.0}},
-                                           {256, 160, {1.30, 0.0, 1.28}}};
+// lone: K = 2560 to 10240 against 256 x 256 tiles of the same K, one to a CU.  In place of two 128 x 128 tiles a CU, one
+// of 256 x 128 took 2048 x 4096 over K = 4096 from 76 to 65 us (dX 69 to 64), 3001 x 2560 over K = 2560 from 52 to 45.
+constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}, {1.0, 1.0, 1.0}},
+                                           {256, 128, {1.37, 1.40, 1.33}, {1.19, 1.15, 1.16}},
+                                           {128, 256, {1.21, 1.23, 1.37}, {1.21, 1.20, 1.22}},
+                                           {128, 128, {1.39, 1.20, 1.40}, {1.60, 1.55, 1.60}},
+                                           {224, 256, {0.0, 1.06, 0.0}, {0.0, 1.06, 0.0}},
+                                           {256, 160, {1.30, 0.0, 1.28}, {1.30, 0.0, 1.28}}};
 constexpr int kNarrowMinK = 2048;
 
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
@@ -339,12 +347,14 @@ bool tile_offered(int i, int kind, int K) {
 // Cheapest tile for M x N; a column split must fall on a tile boundary.
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
-int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1) {
+int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, bool acc_in = false) {
+  // (a lone tile that starts from a sum in memory has nothing to cover that load with: 98 us against 86 in pairs)
+  const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
   int best = -1;
   double best_cost = 0.0;
   for (int i = 0; i < kTileShapes; ++i) {
     if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts)) continue;
-    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts);
+    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0);
     if (best < 0 || c < best_cost) {
       best = i;
       best_cost = c;
@@ -406,7 +416,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   constexpr int kind = layout_kind(kAK, kBK);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
   if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
-    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts);
+    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts, kAccIn);
     const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..5 where it fits the layout and the segments of B
     const bool force = forced >= 0 && forced < kTileShapes;
     if (force && p.n_split % kTiles[forced].bn == 0 && (forced < 4 || (kTiles[forced].penalty[kind] > 0.0 && p.K / parts >= kW4MinK)))
