@@ -401,8 +401,9 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
  * but "split_k" changes a result bit.  Initial values come from the environment variables
  * OSDP_DEBUG_<NAME IN CAPITALS>, read once when the library is first used.
  *   "gemm_generic"   0 | 1   1: every GEMM runs on the bounds-checked kernel
- *   "tile"          -1 .. 5  force tile shape 256x256, 256x128, 128x256, 128x128, 224x256 (dW only), 256x160 (not
- *                            dW) where it divides the launch
+ *   "tile"          -1 .. 3  force tile shape 256x256, 256x128, 128x256, 128x128 where it divides the launch
+ *   "small_tile"    -1 .. 1  0: the four-wave kernel runs 256x256 tiles only; 1: tiles of 224x256 (dW) and 256x160
+ *                            (forward, dX) wherever they serve the launch
  *   "deep"          -1 | 0   0: launches of at most one tile per CU keep the shallow LDS pipelines
  *   "split_launch"  -1 | 0   0: no launch is cut into whole rounds of large tiles + remainder
  *   "split_k"       -1 | 0   0: forward products are never summed in parts of the reduction (the one switch that

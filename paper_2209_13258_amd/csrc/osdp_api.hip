@@ -123,8 +123,11 @@ osdp_status check_shape(const osdp_shape *s) {
 // (the halves of one slice; neighbouring slices inside one full-layout replica) need no staging and so no
 // separation: they are merged into one sub-slice, which only removes launches (the size query, which cannot
 // know, answers for the unmerged plan and is never below what the merged one needs).
+//
+// `ranges_only`: the caller gathers a slice and launches no product: no launches are planned (a microsecond of the
+// 9 that a call with a small slice takes).
 osdp_status resolve(const osdp_shape *shape, const osdp_plan *plan, int32_t op_index, bool overlap_possible,
-                    bool is_bwd, Resolved *r, bool allow_dp = false, const Replicas *rep = nullptr) {
+                    bool is_bwd, Resolved *r, bool allow_dp = false, const Replicas *rep = nullptr, bool ranges_only = false) {
   osdp_status st = check_shape(shape);
   if (st != OSDP_OK) return st;
   int64_t k = shape->k;
@@ -240,6 +243,7 @@ osdp_status resolve(const osdp_shape *shape, const osdp_plan *plan, int32_t op_i
   const size_t slice_bytes = static_cast<size_t>(D) * static_cast<size_t>(wmax) * 2;
   r->slot_bytes = round_up(slice_bytes, kSlotAlign);
   r->peak_staging = slice_bytes * static_cast<size_t>(std::min<int64_t>(r->slots, n_gathered));
+  if (ranges_only) return OSDP_OK;
   const int64_t n = static_cast<int64_t>(r->sub.size());
   auto width = [&](int64_t j) { return r->sub[j].c1 - r->sub[j].c0; };
   auto span = [&](int64_t a, int64_t b) { return r->sub[b - 1].c1 - r->sub[a].c0; };
@@ -831,9 +835,9 @@ struct DebugSwitch {
   int32_t lo, hi;  // accepted values; the default of the field stands for "not set"
 };
 const DebugSwitch kSwitches[] = {
-    {"gemm_generic", &DebugOptions::gemm_generic, 0, 1}, {"tile", &DebugOptions::tile, -1, 5},
+    {"gemm_generic", &DebugOptions::gemm_generic, 0, 1}, {"tile", &DebugOptions::tile, -1, 3},
     {"deep", &DebugOptions::deep, -1, 1},                {"split_launch", &DebugOptions::split_launch, -1, 1},
-    {"recut", &DebugOptions::recut, -1, 1},
+    {"recut", &DebugOptions::recut, -1, 1},             {"small_tile", &DebugOptions::small_tile, -1, 1},
     {"fwd_pair", &DebugOptions::fwd_pair, -1, 1},        {"poison_staging", &DebugOptions::poison_staging, 0, 1},
     {"persistent", &DebugOptions::persistent, -1, 1},    {"split_k", &DebugOptions::split_k, -1, 1},          {"four_wave", &DebugOptions::four_wave, -1, 1},      {"fused_gather", &DebugOptions::fused_gather, -1, 1},
 };
@@ -914,7 +918,7 @@ static osdp_status gather_one(const osdp_shape *shape, uint8_t split_dim, int32_
                               void *staging, void *stream) {
   Resolved r;
   osdp_plan plan = {1, nullptr, nullptr, OSDP_STAGING_SINGLE, &split_dim};
-  osdp_status st = resolve(shape, &plan, 0, false, false, &r);
+  osdp_status st = resolve(shape, &plan, 0, false, false, &r, false, nullptr, /*ranges_only=*/true);
   if (st != OSDP_OK) return st;
   if (slice_j < 0 || slice_j >= r.k) return fail(OSDP_ERR_INVALID_ARG, "slice %d outside [0, %d)", slice_j, r.k);
   ShardTable tab;

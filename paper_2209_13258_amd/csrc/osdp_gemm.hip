@@ -298,7 +298,7 @@ bool fast_path(int K, int k_split, int n_split) {
 constexpr int64_t kMaxLd = 1 << 22;
 bool fits_offsets(const GemmParams &p) { return p.lda < kMaxLd && p.ldb < kMaxLd && p.ldb2 < kMaxLd; }
 
-// Tile shapes of the unchecked kernel and their measured cost per unit of tile area relative to 256 x 256, for
+// Tile shapes of the direct-to-LDS kernels and their measured cost per unit of tile area relative to 256 x 256, for
 // the three operand layouts (forward, dW, dX).
 struct TileShape {
   int bm, bn;
@@ -340,8 +340,10 @@ constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig &&
 // Whether tile shape i serves a launch of the layout with K as the reduction of a workgroup: the four-wave kernel's own
 // shapes from where that kernel is the faster one for dW, and else from a K loop that pays for its start-up.
 bool tile_offered(int i, int kind, int K) {
-  return i < 4 || (kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinKdW : kNarrowMinK) &&
-                   debug_options().four_wave.load(std::memory_order_relaxed) != 0);
+  if (i < 4) return true;
+  return kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinKdW : kNarrowMinK) &&
+         debug_options().four_wave.load(std::memory_order_relaxed) != 0 &&
+         debug_options().small_tile.load(std::memory_order_relaxed) != 0;
 }
 
 // Cheapest tile for M x N; a column split must fall on a tile boundary.
@@ -417,10 +419,14 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
   if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
     int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts, kAccIn);
-    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..5 where it fits the layout and the segments of B
-    const bool force = forced >= 0 && forced < kTileShapes;
-    if (force && p.n_split % kTiles[forced].bn == 0 && (forced < 4 || (kTiles[forced].penalty[kind] > 0.0 && p.K / parts >= kW4MinK)))
-      best = forced;
+    const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 where it fits the segments of B
+    bool force = forced >= 0 && forced <= 3;
+    if (force && p.n_split % kTiles[forced].bn == 0) best = forced;
+    constexpr int small = kind == 1 ? 4 : 5;
+    if (debug_options().small_tile.load(std::memory_order_relaxed) == 1 && p.n_split % kTiles[small].bn == 0 && p.K / parts >= kW4MinK) {
+      best = small;  // testing
+      force = true;
+    }
     // A dX launch with a short reduction whose fp32 partial sum comes from or goes to memory is bound by that
     // traffic, and with only a round or two of large tiles every CU loads, computes and stores in step with the
     // others: two smaller workgroups per CU overlap one's loads and stores with the other's MFMAs (8192 x 4096 with

@@ -16,7 +16,7 @@ def H():
     return gpu_harness
 
 
-DEBUG_DEFAULTS = {"persistent": -1, "split_k": -1, "four_wave": -1, "fused_gather": -1, "gemm_generic": 0, "tile": -1, "deep": -1, "split_launch": -1, "fwd_pair": -1, "recut": -1, "poison_staging": 0}
+DEBUG_DEFAULTS = {"persistent": -1, "split_k": -1, "four_wave": -1, "fused_gather": -1, "gemm_generic": 0, "tile": -1, "deep": -1, "split_launch": -1, "fwd_pair": -1, "recut": -1, "small_tile": -1, "poison_staging": 0}
 
 
 @pytest.fixture
@@ -967,10 +967,11 @@ def test_four_wave_tiles_of_224_rows_and_of_160_columns(H, oracle, T, I, O, N, k
         except osdp.OsdpError:
             continue  # slices that are not whole vectors
         base = None
-        for tile, persistent in ((3, 0), (4, 0), (4, 1), (5, 0), (5, 1)):
+        for tile, small, persistent in ((3, 0, 0), (-1, 1, 0), (-1, 1, 1)):
             debug("tile", tile)
+            debug("small_tile", small)
             debug("persistent", persistent)
-            _announce("smaller four-wave tiles", T, I, O, N, k, "dim", dim, "tile", tile, "persistent", persistent)
+            _announce("smaller four-wave tiles", T, I, O, N, k, "dim", dim, "tile", tile, "small", small, "persistent", persistent)
             op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
             op.fwd(k, plan=plan)
             op.bwd(k, plan=plan)
@@ -978,7 +979,7 @@ def test_four_wave_tiles_of_224_rows_and_of_160_columns(H, oracle, T, I, O, N, k
             base = base or got
             for name in ("Y", "dX", "dW"):
                 H.assert_close(name, got[name], want[name])
-                assert np.array_equal(got[name], base[name]), f"{name} differs from the 128 x 128 tiles (dim {dim}, tile {tile})"
+                assert np.array_equal(got[name], base[name]), f"{name} differs from the 128 x 128 tiles (dim {dim}, persistent {persistent})"
 
 
 # ------------------------------------------------ the persistent form of the four-wave kernel
