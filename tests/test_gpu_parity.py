@@ -854,6 +854,25 @@ def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     assert (H.to_bits(op.dW[-1])[I * O - (N - 1) * L:] == POISON).all()
 
 
+@pytest.mark.parametrize("I,O", [(520, 1056),      # 33 K blocks of 32: the waves' ranges depend on how they are cut
+                                 (1096, 16384)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
+def test_few_tokens_sum_in_an_order_that_the_reduction_length_alone_decides(H, I, O):
+    """At most 128 tokens: a row of Y, dX has the same bits in a call of any number of rows (whose tiles and K blocks
+    differ), for an operator and for its mirror image."""
+    for rows, cols in ((I, O), (O, I)):
+        d = wl.small_case(82, 128, rows, cols, 8)
+        ref = None
+        for T in (128, 65, 64, 33, 17, 1):
+            _announce("few tokens, rows of a larger call", T, rows, cols)
+            op = H.Operator(d["X"][:T], d["dY"][:T], d["W_shards"], cols)
+            op.fwd(1)
+            op.bwd(1)
+            got = op.results()
+            ref = ref or got
+            for name in ("Y", "dX"):
+                assert np.array_equal(got[name], ref[name][:T]), f"{name} of {T} tokens differs from the rows of 128"
+
+
 @pytest.mark.parametrize("T,I,O,N,k", [
     (129, 512, 768, 8, 4),        # shards of one K block
     (257, 640, 1160, 2, 5),         # shards of 320 rows: two and a half tiles of dX
