@@ -680,6 +680,38 @@ def test_per_slice_modes_are_bit_identical_to_all_zdp(H, oracle, rows, T, I, O, 
 
 
 @pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("T,I,O,N,k", [(100, 512, 320, 8, 8),    # few tokens
+                                       (256, 512, 320, 8, 8),    # slices of 40: sums that no multiple of 16 cuts
+                                       (512, 1024, 288, 8, 4),   # slices of 72
+                                       (300, 512, 384, 8, 8),    # slices of 48: a multiple of 16 but not of 32
+                                       (640, 512, 320, 8, 8)])   # more tokens than are multiplied with the shards in place
+def test_per_slice_modes_sum_in_the_order_of_the_all_zdp_plan(H, oracle, rows, T, I, O, N, k):
+    """A replica array for every DP slice (nothing is merged) and one launch per slice: the slices' products are added up
+    in the same order whatever the modes, also where a slice does not end on a K step of the matrix cores."""
+    import paper_2209_13258_amd as osdp
+    if rows:
+        I, O = O, I
+    dim = osdp.OSDP_SPLIT_IN_FEATURES if rows else osdp.OSDP_SPLIT_OUT_FEATURES
+    d = wl.small_case(64, T, I, O, N)
+    base = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+    plan0 = osdp.Plan([k], staging=osdp.OSDP_STAGING_SINGLE, split_dim_per_op=[dim])
+    base.fwd(k, plan=plan0)
+    base.bwd(k, plan=plan0)
+    ref = base.results()
+    W = np.concatenate(d["W_shards"])[: I * O].reshape(I, O)
+    rng = [(oracle.row_slice_range(I, k, j) if rows else oracle.slice_range(O, k, j)) for j in range(k)]
+    ld = O if rows else rng[0][1] - rng[0][0]
+    for mask in (0, 0b0101, (1 << k) - 2):
+        _announce("mixed order of sums", T, I, O, bin(mask), "rows" if rows else "cols")
+        w_dp = [None if (mask >> j) & 1 else (W[a:b] if rows else W[:, a:b]).copy() for j, (a, b) in enumerate(rng)]
+        dev = _MixedDevice(H, d, d["W_shards"], w_dp, ld, rng, I, O, rows, None)
+        dev.run(k, osdp.Plan([k], staging=osdp.OSDP_STAGING_SINGLE, zdp_mask=[mask], split_dim_per_op=[dim]))
+        got, dW, _, _ = dev.gradient(H, I, O, mask)
+        for name, value in (("Y", got["Y"]), ("dX", got["dX"]), ("dW", dW)):
+            assert np.array_equal(value, ref[name]), f"{name} differs from the all-ZDP plan (mask {mask:b})"
+
+
+@pytest.mark.parametrize("rows", [False, True])
 def test_config2_one_of_four_slices_zdp(H, oracle, rows):
     """The paper's example at full size (config 2, k = 4): one slice ZDP, three DP; sampled entries."""
     import paper_2209_13258_amd as osdp
