@@ -31,26 +31,99 @@ struct SkinnyParams {
   int64_t ldc;
   WeightMap w;
   int32_t tiles_m;       // row tiles; more than one only where that spreads a small product over more CUs
-  int32_t by_lane;       // some K block may reach over the end of a shard or of a slice (else the tables are not needed)
+  int32_t by_lane;       // some K block may lie in more than one array: lanes need the tables
 };
+
+// n / d for 0 <= n < 2^45 and a quotient below 2^22, exactly: what the division in 64 bits rounds away (2^-53 of the
+// quotient) is less than the 1 / d that keeps a quotient from the next integer.  A fraction of an integer division's cost.
+__device__ __forceinline__ int32_t quotient(int64_t n, int64_t d) {
+  return static_cast<int32_t>(static_cast<double>(n) / static_cast<double>(d));
+}
+
+// The slice that holds row or column x (slice j is [floor(j len / k), floor((j + 1) len / k))), and where it begins.
+// Only plans with slices in DP mode ask: k <= 64, and len < 2^22, so 32 bits hold every product.
+__device__ __forceinline__ uint32_t slice_of(const WeightMap &w, uint32_t x, uint32_t len) {
+  return ((x + 1) * static_cast<uint32_t>(w.k) - 1) / len;
+}
+__device__ __forceinline__ uint32_t slice_begin(const WeightMap &w, uint32_t j, uint32_t len) {
+  return j * len / static_cast<uint32_t>(w.k);
+}
 
 // Element (r, c) of the weight matrix, for any lane by itself: 8 elements from a column that is a multiple of 8 on lie
 // together.  The tables sit in LDS, where lanes may index them freely.
 __device__ __forceinline__ const uint16_t *locate(const WeightMap &w, const uint16_t *const *shards, const uint16_t *const *dp,
-                                                  int64_t r, int64_t c) {
+                                                  uint32_t r, uint32_t c) {
   if (w.dp_mask) {
-    const int64_t len = w.rows ? w.I : w.lay.O, x = w.rows ? r : c;
-    const int64_t j = ((x + 1) * w.k - 1) / len;  // the slice with floor(j len / k) <= x < floor((j + 1) len / k)
+    const uint32_t len = static_cast<uint32_t>(w.rows ? w.I : w.lay.O), x = w.rows ? r : c, j = slice_of(w, x, len);
     if ((w.dp_mask >> j) & 1ull) {
-      const int64_t first = j * len / w.k;
-      return dp[j] + (w.rows ? (r - first) * w.ld_dp + c : r * w.ld_dp + (c - first));
+      const int64_t d = x - slice_begin(w, j, len);
+      return dp[j] + (w.rows ? d * w.ld_dp + c : r * w.ld_dp + d);
     }
   }
-  const int64_t f = r * w.lay.O + c;
-  const int64_t s = w.lay.rows_per_shard > 0 ? static_cast<int64_t>(static_cast<uint32_t>(r) / static_cast<uint32_t>(w.lay.rows_per_shard))
-                                             : f / w.lay.L;
+  const int64_t f = static_cast<int64_t>(r) * w.lay.O + c;
+  const int64_t s = w.lay.rows_per_shard > 0 ? static_cast<int64_t>(r / static_cast<uint32_t>(w.lay.rows_per_shard)) : quotient(f, w.lay.L);
   return shards[s] + (f - s * w.lay.L);
 }
+
+// Where a wave's K blocks of the weight come from: as long as they lie in one array (one shard, or one slice's replica)
+// they are boxes of one matrix, and only the base address moves.  Everything is common to the wave.
+struct WeightRun {
+  uint64_t base = 0;  // the block's first element
+  uint32_t ld2 = 0;   // bytes from one of its rows to the next
+  int32_t left = 0;   // blocks from this one on that lie in the same array
+
+  // Looks the block of `rows` x `cols` elements at (r, c) up; the next blocks lie `step` further along the reduction, the
+  // rows (kBKc: the columns).  left = 0: the block lies in more than one array, or in a replica whose row length is
+  // beyond the loads' 32-bit offsets.
+  template <bool kBKc>
+  __device__ __forceinline__ void find(const WeightMap &w, int r, int c, int rows, int cols, int step) {
+    const uint32_t along = static_cast<uint32_t>(kBKc ? cols : rows);
+    uint32_t room = 0x7fffffff;  // elements along the reduction from the block's first one to the end of its array
+    if (w.dp_mask) {
+      const uint32_t len = static_cast<uint32_t>(w.rows ? w.I : w.lay.O);
+      const uint32_t x = static_cast<uint32_t>(w.rows ? r : c), j = __builtin_amdgcn_readfirstlane(slice_of(w, x, len));
+      const uint32_t end = __builtin_amdgcn_readfirstlane(slice_begin(w, j + 1, len));
+      if ((w.rows != 0) != kBKc) room = end - x;  // (the slices cut the reduction)
+      const bool inside = x + static_cast<uint32_t>(w.rows ? rows : cols) <= end;
+      if ((w.dp_mask >> j) & 1ull) {
+        const int64_t d = x - __builtin_amdgcn_readfirstlane(slice_begin(w, j, len));
+        base = reinterpret_cast<uint64_t>(w.dp.p[j]) + static_cast<uint64_t>(w.rows ? d * w.ld_dp + c : r * w.ld_dp + d) * 2;
+        ld2 = static_cast<uint32_t>(w.ld_dp) * 2;
+        left = inside && w.ld_dp < (1 << 22) ? static_cast<int32_t>((room - along) / step) + 1 : 0;
+        return;
+      }
+      if (!inside) {
+        left = 0;
+        return;
+      }
+    }
+    const uint32_t per_shard = static_cast<uint32_t>(w.lay.rows_per_shard);
+    int64_t first;  // the block's first element, in its shard
+    uint32_t s;
+    if (per_shard > 0) {
+      s = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r) / per_shard);
+      const uint32_t row = r - s * per_shard, rows_left = per_shard - row;
+      if (rows_left < static_cast<uint32_t>(rows)) {
+        left = 0;
+        return;
+      }
+      if (!kBKc && rows_left < room) room = rows_left;
+      first = static_cast<int64_t>(row) * w.lay.O + c;
+    } else {
+      const int64_t f = static_cast<int64_t>(r) * w.lay.O + c;
+      s = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(quotient(f, w.lay.L)));
+      first = f - s * w.lay.L;
+      const int64_t behind = w.lay.L - first;  // what of the shard follows from there
+      int64_t fits;
+      if (kBKc) fits = behind - static_cast<int64_t>(rows - 1) * w.lay.O;
+      else fits = behind < cols ? 0 : quotient(behind - cols, w.lay.O) + 1;
+      if (fits < room) room = fits < 0 ? 0 : static_cast<uint32_t>(fits);
+    }
+    base = reinterpret_cast<uint64_t>(w.shards.p[s]) + static_cast<uint64_t>(first) * 2;
+    ld2 = static_cast<uint32_t>(w.lay.O) * 2;
+    left = room >= along ? static_cast<int32_t>((room - along) / step) + 1 : 0;
+  }
+};
 
 // A wave-level direct-to-LDS load from 64 addresses of their own.
 __device__ __forceinline__ void dma16_from(const void *src, uint32_t dst) {
@@ -139,54 +212,69 @@ void gemm_skinny_kernel(SkinnyParams p) {
   const uint32_t lda2 = static_cast<uint32_t>(p.lda) * 2, bytesA = static_cast<uint32_t>(m_left) * lda2;
   const uint32_t offA[2] = {lane_offset(OpA{}, 0, lda2), lane_offset(OpA{}, 1, lda2)};
 
-  // The weight.  A block that lies in one shard is a matrix with a base address and the row length O, and is fetched
-  // like any operand; one that reaches over the end of a shard, or of a matrix with slices in DP mode, is fetched lane
-  // by lane.  `first` is the flat index of the block's first element, `shard_end` where its shard ends.
-  const int64_t O = p.w.lay.O, L64 = p.w.lay.L;
-  const uint32_t ld2 = static_cast<uint32_t>(O) * 2;
+  // The weight.  A block that lies in one array is fetched like any operand, and mostly the next one does too: plans with
+  // slices in DP mode run at the rate of those without.  A block that reaches over the end of a shard or of a slice is
+  // fetched lane by lane, which the address arithmetic bounds (128 tokens 4096 -> 16384, every slice in DP mode: dX and dW
+  // 286 us with all blocks by lane, 104 us like this).  In dX the blocks hold the same rows all along: where a row lies in
+  // one array, each lane finds its rows once (128 tokens 1024 -> 4096, 64 shards of 16 rows: dX and dW 51 -> 28 us).
   const int n_left = p.N - n0 < BN ? p.N - n0 : BN;
-  int64_t first = kBKc ? static_cast<int64_t>(n0) * O + static_cast<int64_t>(b0) * BK : static_cast<int64_t>(b0) * BK * O + n0;
-  int shard = -1;  // (none yet: the first block finds its own)
-  int64_t shard_end = 0;
-  uint64_t shard_base = 0;
-  uint32_t offB[2] = {lane_offset(OpB{}, 0, ld2), lane_offset(OpB{}, 1, ld2)};
-  if (!kBKc) {
-    if (OpB::pos(lane, 0) >= n_left) offB[0] = kOutOfRange;
-    if (OpB::pos(lane, OpB::kPermStep) >= n_left) offB[1] = kOutOfRange;
-  }
+  WeightRun run;
+  uint32_t offB[2] = {0, 0};
+  bool by_row = false;
+  const uint16_t *lane_row[kBKc ? LB : 1];
   auto issue_weight = [&](int b, uint32_t dst) {
     const int k0 = b * BK, k_left = b < b1 ? (p.K - k0 < BK ? p.K - k0 : BK) : 0;
     const int rows = kBKc ? n_left : k_left, cols = kBKc ? k_left : n_left;  // of the block that are in the matrix
-    if (first >= shard_end && shard + 1 < p.w.lay.N) {
-      do {
-        ++shard;
-        shard_end += L64;
-      } while (first >= shard_end && shard + 1 < p.w.lay.N);
-      shard_base = reinterpret_cast<uint64_t>(p.w.shards.p[shard]);
+    if (__builtin_expect(run.left == 0 && k_left > 0 && !by_row, 0)) {
+      run.template find<kBKc>(p.w, kBKc ? n0 : k0, kBKc ? k0 : n0, rows, cols, BK);
+      run.base = uniform64(run.base) & 0xffffffffffffull;
+      run.left = __builtin_amdgcn_readfirstlane(run.left);
+      run.ld2 = __builtin_amdgcn_readfirstlane(run.ld2);
+      offB[0] = lane_offset(OpB{}, 0, run.ld2);
+      offB[1] = lane_offset(OpB{}, 1, run.ld2);
+      if (!kBKc) {
+        if (OpB::pos(lane, 0) >= n_left) offB[0] = kOutOfRange;
+        if (OpB::pos(lane, OpB::kPermStep) >= n_left) offB[1] = kOutOfRange;
+      }
+      if constexpr (kBKc) {
+        if (run.left == 0 && p.w.lay.rows_per_shard > 0 && (p.w.dp_mask == 0 || p.w.rows)) {
+          by_row = true;
+          static_for<LB>([&](auto idx) {
+            constexpr int i = decltype(idx)::value;
+            const int row = i * OpB::kRowsPerLoad + OpB::row(lane);
+            lane_row[i] = locate(p.w, s_shards, s_dp, n0 + (row < n_left ? row : n_left - 1), 0);
+          });
+        }
+      }
     }
-    const int64_t last = first + static_cast<int64_t>(rows - 1) * O + cols;
-    if (!p.by_lane || (p.w.dp_mask == 0 && last <= shard_end) || k_left == 0) {
-      const uint64_t base = (shard_base + static_cast<uint64_t>(first - (shard_end - L64)) * 2) & 0xffffffffffffull;
-      const osdp_u32x4 rsrc = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base))),
-                               static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base >> 32))),
-                               static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(k_left == 0 ? 0 : rows * ld2)), 0x00020000u};
+    if (__builtin_expect(run.left > 0 || k_left == 0, 1)) {
+      const osdp_u32x4 rsrc = {static_cast<uint32_t>(run.base), static_cast<uint32_t>(run.base >> 32),
+                               k_left == 0 ? 0 : rows * run.ld2, 0x00020000u};
       static_for<LB>([&](auto idx) {
         constexpr int i = decltype(idx)::value;
         uint32_t lane_off = offB[(i / OpB::kPermStep) & 1];
         if (kBKc && k_left < BK) lane_off = OpB::pos(lane, i) < k_left ? lane_off : kOutOfRange;
-        dma16<i * 1024>(rsrc, lane_off + static_cast<uint32_t>(i * OpB::kRowsPerLoad) * ld2, dst);
+        dma16<i * 1024>(rsrc, lane_off + static_cast<uint32_t>(i * OpB::kRowsPerLoad) * run.ld2, dst);
+      });
+      run.base += kBKc ? BK * 2 : BK * run.ld2;
+      run.left -= 1;
+    } else if (kBKc && by_row) {
+      static_for<LB>([&](auto idx) {
+        constexpr int i = decltype(idx)::value;
+        const int row = i * OpB::kRowsPerLoad + OpB::row(lane), pos = OpB::pos(lane, i);
+        const void *src = &kZeros;
+        if (row < rows && pos < cols) src = lane_row[kBKc ? i : 0] + k0 + pos;
+        dma16_from(src, dst + i * 1024);
       });
     } else {
 #pragma unroll 1
       for (int i = 0; i < LB; ++i) {
         const int row = i * OpB::kRowsPerLoad + OpB::row(lane), pos = OpB::pos(lane, i);
         const void *src = &kZeros;
-        if (row < rows && pos < cols)
-          src = locate(p.w, s_shards, s_dp, static_cast<int64_t>(kBKc ? n0 : k0) + row, static_cast<int64_t>(kBKc ? k0 : n0) + pos);
+        if (row < rows && pos < cols) src = locate(p.w, s_shards, s_dp, (kBKc ? n0 : k0) + row, (kBKc ? k0 : n0) + pos);
         dma16_from(src, dst + i * 1024);
       }
     }
-    first += kBKc ? BK : BK * O;
   };
   const uint32_t ring = lds_address(smem) + wave * (kStages * kStageBytes);
   auto issue = [&](int b, int stage) {

@@ -856,6 +856,7 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
     (64, 512, 64, 64, 4),      # 64 shards of 8 rows
     (65, 1032, 520, 2, 1),     # one row beyond a tile; K blocks divide evenly among no four waves
     (128, 2048, 16448, 8, 4),  # all rows in one tile
+    (128, 520, 1280, 64, 4),   # 64 shards of eight rows and an eighth
 ])
 def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     """At most 128 tokens: Y and dX are one launch each over the whole weight, read from the shards, whatever the
@@ -887,7 +888,7 @@ def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
 
 
 @pytest.mark.parametrize("I,O", [(520, 1056),      # 33 K blocks of 32: the waves' ranges depend on how they are cut
-                                 (1096, 16384)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
+                                 (1096, 16360)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
 def test_few_tokens_sum_in_an_order_that_the_reduction_length_alone_decides(H, I, O):
     """At most 128 tokens: a row of Y, dX has the same bits in a call of any number of rows (whose tiles and K blocks
     differ), for an operator and for its mirror image."""
@@ -939,7 +940,10 @@ def test_up_to_512_tokens_multiply_the_weight_in_its_shards(H, oracle, T, I, O, 
 
 
 @pytest.mark.parametrize("rows", [False, True])
-@pytest.mark.parametrize("T,I,O,N,k,mask", [(7, 256, 512, 4, 4, 0b0110), (40, 264, 528, 4, 3, 0b001), (100, 40, 1200, 3, 5, 0b00000)])
+@pytest.mark.parametrize("T,I,O,N,k,mask", [(7, 256, 512, 4, 4, 0b0110), (40, 264, 528, 4, 3, 0b001), (100, 40, 1200, 3, 5, 0b00000),
+                                            (33, 520, 1280, 64, 4, 0b0101),   # shards that end inside rows
+                                            (128, 512, 1024, 64, 4, 0b0010),  # shards of 8 rows: every block lies in several
+                                            (65, 1096, 2200, 8, 1, 0b0)])     # one replica, no staging; shards of 137 rows
 def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows):
     """The same with some slices read from their replicas (NaN wherever a source must not be read)."""
     import paper_2209_13258_amd as osdp
@@ -959,6 +963,50 @@ def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows)
         H.assert_close("dX", got["dX"], want["dX"])
         H.assert_close("dW", dW, want["dW"])
         assert all((a == POISON).all() for a in in_dp + outside)
+
+
+@pytest.mark.parametrize("T", [20, 140])   # the few-token kernel; the kernels that take a DP slice as an operand
+@pytest.mark.parametrize("rows", [False, True])
+def test_replica_rows_beyond_32_bit_offsets(H, oracle, T, rows, debug):
+    """ld_dp from 2^22 on, where the direct-to-LDS loads' 32-bit offsets end: the bits of the same replica at a small
+    ld_dp, in plans with one slice of two in DP mode and with both.  From 129 tokens on the bounds-checked kernel takes
+    over, here also for launches over a DP and a gathered slice (by k where they sum, by column where they concatenate)."""
+    import paper_2209_13258_amd as osdp
+    debug("fwd_pair", 1)
+    I, O, N, k = 256 if rows else 128, 256, 4, 2
+    d = wl.small_case(83, T, I, O, N)
+    W = np.concatenate(d["W_shards"]).reshape(I, O)
+    rng = [(oracle.row_slice_range(I, k, j) if rows else oracle.slice_range(O, k, j)) for j in range(k)]
+    dim = osdp.OSDP_SPLIT_IN_FEATURES if rows else osdp.OSDP_SPLIT_OUT_FEATURES
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+    for mask in (0b01, 0b00):
+        plan = osdp.Plan([k], staging=osdp.OSDP_STAGING_DOUBLE, zdp_mask=[mask], split_dim_per_op=[dim])
+        got = {}
+        for ld in (O, (1 << 22) + 8):
+            _announce("replica row length", ld, "T", T, "rows" if rows else "cols", bin(mask))
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            w_dp, dw_dp = [None] * k, [None] * k
+            for j, (a, b) in enumerate(rng):
+                if (mask >> j) & 1:
+                    continue
+                part = H.to_dev(W[a:b] if rows else W[:, a:b])
+                h, w = part.shape
+                w_dp[j], dw_dp[j] = (torch.empty(((h - 1) * ld + w,), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+                w_dp[j].as_strided((h, w), (ld, 1)).copy_(part)
+            op.workspace(k, False, plan)
+            op.workspace(k, True, plan)
+            osdp.osdp_split_linear_fwd_mixed(op.X, op.W, w_dp, ld, op.Y, k, op.ws, plan=plan)
+            osdp.osdp_split_linear_bwd_mixed(op.X, op.dY, op.W, w_dp, ld, op.dX, op.dW, dw_dp, k, op.ws, plan=plan)
+            got[ld] = op.results()
+            for j, (a, b) in enumerate(rng):
+                if dw_dp[j] is not None:
+                    h, w = (b - a, O) if rows else (I, b - a)
+                    got[ld]["dW"][slice(a, b) if rows else slice(None), slice(None) if rows else slice(a, b)] = \
+                        H.to_bits(dw_dp[j].as_strided((h, w), (ld, 1)))
+            for name in ("Y", "dX", "dW"):
+                H.assert_close(name, got[ld][name], want[name])
+        for name in ("Y", "dX", "dW"):
+            assert np.array_equal(got[O][name], got[(1 << 22) + 8][name]), f"{name} depends on ld_dp (mask {mask:b})"
 
 
 @pytest.mark.parametrize("T,I,O,N,k", [
