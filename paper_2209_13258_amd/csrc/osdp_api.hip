@@ -957,7 +957,7 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
   if ((st = check_workspace(r, workspace, workspace_bytes)) != OSDP_OK) return st;
   if ((st = device_ok()) != OSDP_OK) return st;
   if (no_tokens) return OSDP_OK;  // Y is empty: nothing is gathered, nothing is launched
-  if (skinny_takes(r.T, ldx, r.I, r.O)) {  // few tokens: one launch that reads the weights where they lie
+  if (skinny_takes(false, r.T, ldx, r.layout, r.I)) {  // few tokens: one launch that reads the weights where they lie
     const double T = r.T, I = r.I, O = r.O;
     OSDP_HIP(timed(OSDP_KERNEL_GEMM_FWD, 2.0 * T * I * O, 2.0 * (T * I + I * O + T * O), sc,
                    [&] { return launch_skinny(false, weight_map(r, tab, rep), r.T, X, ldx, Y, ldy, sc); }));
@@ -1139,7 +1139,7 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
     return OSDP_OK;
   }
   // Few tokens: nothing is staged (see forward()), and dW is one launch per destination.
-  const bool skinny = skinny_takes(r.T, lddy, r.I, r.O);
+  const bool skinny = skinny_takes(true, r.T, lddy, r.layout, r.I);
   if (skinny || (!r.any_dp && one_chain(r, false) && gemm_reads_shards(r.T, lddy, r.layout))) {
     const double T = r.T, I = r.I, O = r.O;
     if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});

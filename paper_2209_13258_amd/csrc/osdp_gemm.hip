@@ -576,12 +576,16 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
 
 }  // namespace
 
+namespace {
+bool shards_are_k_blocks(const ShardLayout &lay) { return lay.rows_per_shard > 0 && lay.rows_per_shard % 64 == 0; }
+}  // namespace
+
 bool gemm_reads_shards(int64_t T, int64_t ld_act, const ShardLayout &lay) {
   const DebugOptions &d = debug_options();
   const bool forced = d.gemm_generic.load(std::memory_order_relaxed) != 0 || d.tile.load(std::memory_order_relaxed) >= 0 ||
                       d.fwd_pair.load(std::memory_order_relaxed) >= 0 || d.fused_gather.load(std::memory_order_relaxed) >= 0 ||
                       d.poison_staging.load(std::memory_order_relaxed) != 0;  // (these ask for the staged schedule)
-  return !forced && T <= kShardReadMaxTokens && lay.rows_per_shard > 0 && lay.rows_per_shard % 64 == 0 && ld_act < kMaxLd && lay.O < kMaxLd;
+  return !forced && T <= kShardReadMaxTokens && shards_are_k_blocks(lay) && ld_act < kMaxLd && lay.O < kMaxLd;
 }
 
 int gemm_forward_parts(int64_t M, int64_t K) { return forward_k_parts(M, K); }
@@ -700,11 +704,14 @@ hipError_t launch_skinny_as(SkinnyParams p, hipStream_t stream) {
 }
 }  // namespace
 
-bool skinny_takes(int64_t T, int64_t ld_act, int64_t I, int64_t O) {
+bool skinny_takes(bool dx, int64_t T, int64_t ld_act, const ShardLayout &lay, int64_t I) {
   // (the switches that pick a kernel or a tile for the staged products keep those)
   const DebugOptions &d = debug_options();
-  return T > 0 && T <= kSkinnyMaxTokens && ld_act < kMaxLd && I < kMaxLd && O < kMaxLd &&
-         d.gemm_generic.load(std::memory_order_relaxed) == 0 && d.tile.load(std::memory_order_relaxed) < 0;
+  if (T <= 0 || T > kSkinnyMaxTokens || ld_act >= kMaxLd || I >= kMaxLd || lay.O >= kMaxLd ||
+      d.gemm_generic.load(std::memory_order_relaxed) != 0 || d.tile.load(std::memory_order_relaxed) >= 0)
+    return false;
+  const int64_t N = dx ? I : lay.O, K = dx ? lay.O : I;
+  return !(T > kSkinnyMaxWideTokens && N > kSkinnyMaxColumns && shards_are_k_blocks(lay) && forward_k_parts(T, K) == 1);
 }
 
 // Rows of a workgroup's tile.  Every workgroup streams (BM + 64) rows' worth of operands, and the launch lasts as long

@@ -107,10 +107,16 @@ struct GemmProblem {
 // Enqueue on `stream`.  Returns hipSuccess or the launch error.
 hipError_t launch_gemm(const GemmProblem &p, hipStream_t stream);
 
-// Forward (or, dx set, dX) product of at most kSkinnyMaxTokens tokens with the whole weight matrix, read in place: no
-// slice is staged.  skinny_takes: whether the launch accepts the sizes.
-constexpr int64_t kSkinnyMaxTokens = 128;
-bool skinny_takes(int64_t T, int64_t ld_act, int64_t I, int64_t O);
+// Forward (or, dx set, dX) product of at most kSkinnyMaxTokens tokens with the whole weight, read in place: no
+// slice is staged.  skinny_takes: whether the launch is the one for the sizes.
+// From 65 tokens and more than 8192 output columns on, the tiles of the other kernels are the faster ones: every
+// workgroup of the few-token kernel streams all tokens and 64 columns, in as many rounds as there are 256 of them
+// (128 tokens 4096 -> 24576: 74 us against 37 us in 128 x 128 tiles over the shards, 1024 -> 20480 29 against 15; with 8192
+// columns 27 us against 34).  They need shards of whole K blocks, or slices that lie in replicas; other shards would be
+// staged, slice by slice, and stay with the few-token kernel, as do reductions that the others sum in parts.  The rule does
+// not ask for the modes of the slices or the granularity: plans of one operator add up in the same order.
+constexpr int64_t kSkinnyMaxTokens = 128, kSkinnyMaxWideTokens = 64, kSkinnyMaxColumns = 8192;
+bool skinny_takes(bool dx, int64_t T, int64_t ld_act, const ShardLayout &lay, int64_t I);
 hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
                          hipStream_t stream);
 

@@ -684,6 +684,7 @@ def test_per_slice_modes_are_bit_identical_to_all_zdp(H, oracle, rows, T, I, O, 
                                        (256, 512, 320, 8, 8),    # slices of 40: sums that no multiple of 16 cuts
                                        (512, 1024, 288, 8, 4),   # slices of 72
                                        (300, 512, 384, 8, 8),    # slices of 48: a multiple of 16 but not of 32
+                                       (72, 256, 8320, 4, 8),    # few tokens, but wide: slices of 1040
                                        (640, 512, 320, 8, 8)])   # more tokens than are multiplied with the shards in place
 def test_per_slice_modes_sum_in_the_order_of_the_all_zdp_plan(H, oracle, rows, T, I, O, N, k):
     """A replica array for every DP slice (nothing is merged) and one launch per slice: the slices' products are added up
@@ -857,6 +858,9 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
     (65, 1032, 520, 2, 1),     # one row beyond a tile; K blocks divide evenly among no four waves
     (128, 2048, 16448, 8, 4),  # all rows in one tile
     (128, 520, 1280, 64, 4),   # 64 shards of eight rows and an eighth
+    (65, 256, 8200, 4, 5),     # the fewest tokens and columns that go in tiles over the shards
+    (64, 8256, 256, 1, 2),     # one token fewer; one shard
+    (100, 8320, 264, 2, 1),    # dX in such tiles, over shards of 4160 rows
 ])
 def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     """At most 128 tokens: Y and dX are one launch each over the whole weight, read from the shards, whatever the
@@ -890,8 +894,8 @@ def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
 @pytest.mark.parametrize("I,O", [(520, 1056),      # 33 K blocks of 32: the waves' ranges depend on how they are cut
                                  (1096, 16360)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
 def test_few_tokens_sum_in_an_order_that_the_reduction_length_alone_decides(H, I, O):
-    """At most 128 tokens: a row of Y, dX has the same bits in a call of any number of rows (whose tiles and K blocks
-    differ), for an operator and for its mirror image."""
+    """At most 128 tokens on the few-token kernel: a row of Y, dX has the same bits in a call of any number of rows (whose
+    tiles and K blocks differ), for an operator and for its mirror image."""
     for rows, cols in ((I, O), (O, I)):
         d = wl.small_case(82, 128, rows, cols, 8)
         ref = None
