@@ -790,6 +790,44 @@ GemmProblem shard_gemm(const Resolved &r, bool is_fwd, const ShardTable &tab, co
   return g;
 }
 
+// A concatenating product of at most kSkinnyMaxTokens tokens whose gathered slices are neighbours, as are those in DP
+// mode, in one replica: one launch over the shards and one over the replica.  With one gathered slice a single launch over
+// both, the slice staged, is the faster one, and with more than two runs so are pairs of slices: each run is a launch of
+// its own that fills a part of the CUs (128 tokens 4096 -> 16384, k = 8, us in runs / staged: four slices of each kind
+// 63 / 118, one gathered 65 / 42, kinds in turn 244 / 160).  dX takes whole shards only.  Empty: staged.
+std::vector<Slice> runs_in_place(const Resolved &r, bool is_fwd) {
+  std::vector<Slice> runs;
+  if (is_fwd == r.rows) return runs;
+  const int64_t n = static_cast<int64_t>(r.sub.size());
+  for (int64_t j = 0; j < n; ++j) {
+    if (j > 0 && !r.dp[j] && !r.dp[j - 1]) runs.back().c1 = j + 1;
+    else runs.push_back({j, j + 1});
+  }
+  bool in_place = runs.size() == 2;
+  for (const Slice &l : runs) {
+    if (r.dp[l.c0]) continue;
+    in_place = in_place && r.owner[l.c0] != r.owner[l.c1 - 1];
+    if (!is_fwd) in_place = in_place && r.sub[l.c0].c0 % r.layout.rows_per_shard == 0 && r.sub[l.c1 - 1].c1 % r.layout.rows_per_shard == 0;
+  }
+  return in_place ? runs : std::vector<Slice>{};
+}
+
+GemmProblem run_gemm(const Resolved &r, bool is_fwd, const Slice &l, const ShardTable &tab, const Replicas &rep, const void *act,
+                     int64_t ld_act, void *out, int64_t ld_out) {
+  const int j0 = static_cast<int>(l.c0);
+  if (r.dp[j0])
+    return weight_gemm(r, is_fwd, j0, j0 + 1, weights_of(r, rep, j0, nullptr), WeightView{nullptr, 0}, act, ld_act, out, ld_out,
+                       nullptr, 0, 1);
+  const int64_t c0 = r.sub[j0].c0, c1 = r.sub[l.c1 - 1].c1;
+  GemmProblem g = shard_gemm(r, is_fwd, tab, act, ld_act, static_cast<uint16_t *>(out) + c0, ld_out);
+  g.N = static_cast<int32_t>(c1 - c0);
+  if (is_fwd)  // columns [c0, c1) of every shard
+    for (int32_t s = 0; s < r.N; ++s) g.shards.p[s] = static_cast<uint16_t *>(tab.p[s]) + c0;
+  else         // the shards that hold rows [c0, c1)
+    for (int32_t s = 0, s0 = static_cast<int32_t>(c0 / r.layout.rows_per_shard); s0 + s < r.N; ++s) g.shards.p[s] = tab.p[s0 + s];
+  return g;
+}
+
 // Whether that product keeps the bits of the slices' products: concatenating launches over a long reduction are summed
 // in parts, accumulating ones in one chain.
 bool one_chain(const Resolved &r, bool is_fwd) { return is_fwd == r.rows || gemm_forward_parts(r.T, r.D) == 1; }
@@ -967,6 +1005,11 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
     OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, shard_gemm(r, true, tab, X, ldx, Y, ldy), sc));
     return OSDP_OK;
   }
+  if (r.any_dp && r.T <= kSkinnyMaxTokens && one_chain(r, true) && gemm_reads_shards(r.T, ldx, r.layout)) {
+    const std::vector<Slice> runs = runs_in_place(r, true);
+    for (const Slice &l : runs) OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, run_gemm(r, true, l, tab, rep, X, ldx, Y, ldy), sc));
+    if (!runs.empty()) return OSDP_OK;
+  }
   Resolved other;
   if (recut(shape, r, true, &other)) r = std::move(other);
 
@@ -1140,7 +1183,10 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
   }
   // Few tokens: nothing is staged (see forward()), and dW is one launch per destination.
   const bool skinny = skinny_takes(true, r.T, lddy, r.layout, r.I);
-  if (skinny || (!r.any_dp && one_chain(r, false) && gemm_reads_shards(r.T, lddy, r.layout))) {
+  const bool in_place = !skinny && one_chain(r, false) && gemm_reads_shards(r.T, lddy, r.layout);
+  std::vector<Slice> runs;
+  if (in_place && r.any_dp && r.T <= kSkinnyMaxTokens) runs = runs_in_place(r, false);
+  if (skinny || (in_place && (!r.any_dp || !runs.empty()))) {
     const double T = r.T, I = r.I, O = r.O;
     if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});
     for (const Slice &l : r.dw)
@@ -1148,8 +1194,9 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
     if (skinny)
       OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 2.0 * T * I * O, 2.0 * (T * O + I * O + T * I), sc,
                      [&] { return launch_skinny(true, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc); }));
-    else
+    else if (runs.empty())
       OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DX, shard_gemm(r, false, tab, dY, lddy, dX, lddx), sc));
+    for (const Slice &l : runs) OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DX, run_gemm(r, false, l, tab, rep, dY, lddy, dX, lddx), sc));
     return OSDP_OK;
   }
   Resolved other;

@@ -684,7 +684,7 @@ def test_per_slice_modes_are_bit_identical_to_all_zdp(H, oracle, rows, T, I, O, 
                                        (256, 512, 320, 8, 8),    # slices of 40: sums that no multiple of 16 cuts
                                        (512, 1024, 288, 8, 4),   # slices of 72
                                        (300, 512, 384, 8, 8),    # slices of 48: a multiple of 16 but not of 32
-                                       (72, 256, 8320, 4, 8),    # few tokens, but wide: slices of 1040
+                                       (72, 256, 8448, 4, 8),    # few tokens, but wide: slices of 1056
                                        (640, 512, 320, 8, 8)])   # more tokens than are multiplied with the shards in place
 def test_per_slice_modes_sum_in_the_order_of_the_all_zdp_plan(H, oracle, rows, T, I, O, N, k):
     """A replica array for every DP slice (nothing is merged) and one launch per slice: the slices' products are added up
@@ -860,7 +860,7 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
     (128, 520, 1280, 64, 4),   # 64 shards of eight rows and an eighth
     (65, 256, 8200, 4, 5),     # the fewest tokens and columns that go in tiles over the shards
     (64, 8256, 256, 1, 2),     # one token fewer; one shard
-    (100, 8320, 264, 2, 1),    # dX in such tiles, over shards of 4160 rows
+    (100, 8448, 264, 2, 1),    # dX in such tiles, over shards of 4224 rows
 ])
 def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     """At most 128 tokens: Y and dX are one launch each over the whole weight, read from the shards, whatever the
@@ -967,6 +967,48 @@ def test_few_tokens_with_slices_in_dp_mode(H, oracle, T, I, O, N, k, mask, rows)
         H.assert_close("dX", got["dX"], want["dX"])
         H.assert_close("dW", dW, want["dW"])
         assert all((a == POISON).all() for a in in_dp + outside)
+
+
+@pytest.mark.parametrize("rows", [False, True])
+def test_few_tokens_and_wide_outputs_with_slices_in_dp_mode(H, oracle, rows):
+    """65 tokens on, more than 8192 output columns: gathered slices side by side and DP slices in one replica are one launch
+    each over the shards and the replica, the other plans are staged.  The same bits from all of them, nothing read from a
+    source that does not count, nothing written outside the outputs."""
+    import paper_2209_13258_amd as osdp
+    T, I, O, N, k = 100, 256, 8448, 4, 4
+    if rows:
+        I, O = O, I
+    dim = osdp.OSDP_SPLIT_IN_FEATURES if rows else osdp.OSDP_SPLIT_OUT_FEATURES
+    d0 = wl.small_case(84, T, I, O, N)
+    base = H.Operator(d0["X"], d0["dY"], d0["W_shards"], O)
+    base.fwd(k, plan=osdp.Plan([k], split_dim_per_op=[dim]))
+    base.bwd(k, plan=osdp.Plan([k], split_dim_per_op=[dim]))
+    ref = base.results()
+    want = oracle.linear(d0["X"], d0["W_shards"], O, dY=d0["dY"])
+    W = np.concatenate(d0["W_shards"]).reshape(I, O)
+    rng = [(oracle.row_slice_range(I, k, j) if rows else oracle.slice_range(O, k, j)) for j in range(k)]
+    for mask, in_place in ((0b0011, True), (0b1100, True), (0b0111, True), (0b0001, False), (0b0101, False)):
+        shards, full = W.copy(), W.copy()       # (both full-layout; NaN where a source must not be read)
+        for j, (a, b) in enumerate(rng):
+            (full if (mask >> j) & 1 else shards)[slice(a, b) if rows else slice(None), slice(None) if rows else slice(a, b)] = POISON
+        shards = [s.copy() for s in shards.reshape(N, -1)]
+        w_dp = [None if (mask >> j) & 1 else (full, a * O if rows else a) for j, (a, b) in enumerate(rng)]
+        for mode in (osdp.OSDP_STAGING_SINGLE, osdp.OSDP_STAGING_DOUBLE, osdp.OSDP_STAGING_HALF):
+            _announce("wide, DP slices", bin(mask), "rows" if rows else "cols", "mode", mode)
+            dev = _MixedDevice(H, d0, shards, w_dp, O, rng, I, O, rows, full)
+            osdp.osdp_profile_begin(1000)
+            dev.run(k, osdp.Plan([k], staging=mode, zdp_mask=[mask], split_dim_per_op=[dim]))
+            st = osdp.osdp_profile_end()
+            got, dW, in_dp, outside = dev.gradient(H, I, O, mask)
+            for name, value in (("Y", got["Y"]), ("dX", got["dX"]), ("dW", dW)):
+                H.assert_close(name, value, want[name])
+                assert np.array_equal(value, ref[name]), f"{name} differs from the all-ZDP plan (mask {mask:04b}, mode {mode})"
+            assert all((a == POISON).all() for a in in_dp + outside)
+            if mode == osdp.OSDP_STAGING_HALF and mask != 0b0111:
+                continue    # (halves of different DP slices are not merged: more than two runs)
+            # (the other pass adds up, over few columns: one launch over the weight in place, without gathers)
+            assert not in_place or st["gemm_dx" if rows else "gemm_fwd"]["launches"] == 2
+            assert in_place == (st["gather"]["launches"] + st["gather_carried"]["launches"] == 0)
 
 
 @pytest.mark.parametrize("T", [20, 140])   # the few-token kernel; the kernels that take a DP slice as an operand
