@@ -832,6 +832,19 @@ GemmProblem run_gemm(const Resolved &r, bool is_fwd, const Slice &l, const Shard
 // in parts, accumulating ones in one chain.
 bool one_chain(const Resolved &r, bool is_fwd) { return is_fwd == r.rows || gemm_forward_parts(r.T, r.D) == 1; }
 
+// Forward over the shards in place: with shards of a single K block (64 rows) every block of every tile begins in another
+// array, 0.18 us a switch that a staged copy does not have.  256 tokens, unsplit, us in place / staged: 4096 -> 1024 over 64
+// shards 43.8 / 40.3, 4096 -> 4096 44.0 / 47.4; 2048 -> 512 over 32 shards 25.0 / 23.4; with four slices to gather in
+// place always was the faster one (4096 -> 512: 44 / 72), as it was with 128 rows to a shard.  (A gather in front of a
+// launch costs 3 us less than one between two.)
+bool switches_pay(const Resolved &r) {
+  if (r.layout.rows_per_shard > 64) return true;
+  double copies = 0.0;
+  for (size_t j = 0; j < r.sub.size(); ++j)
+    if (!r.dp[j]) copies += gather_estimate_us(r.D * (r.sub[j].c1 - r.sub[j].c0)) - 3.0;
+  return 0.18 * r.N < copies;
+}
+
 osdp_status check_replicas(const Resolved &r, const Replicas &rep, bool need_dw) {
   if (!r.any_dp) return OSDP_OK;
   if (!rep.w) return fail(OSDP_ERR_INVALID_ARG, "w_dp is NULL but the plan has slices in DP mode");
@@ -1001,11 +1014,12 @@ static osdp_status forward(const osdp_shape *shape, const osdp_plan *plan, int32
                    [&] { return launch_skinny(false, weight_map(r, tab, rep), r.T, X, ldx, Y, ldy, sc); }));
     return OSDP_OK;
   }
-  if (!r.any_dp && one_chain(r, true) && gemm_reads_shards(r.T, ldx, r.layout)) {
+  const bool in_place = one_chain(r, true) && gemm_reads_shards(r.T, ldx, r.layout) && switches_pay(r);
+  if (in_place && !r.any_dp) {
     OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, shard_gemm(r, true, tab, X, ldx, Y, ldy), sc));
     return OSDP_OK;
   }
-  if (r.any_dp && r.T <= kSkinnyMaxTokens && one_chain(r, true) && gemm_reads_shards(r.T, ldx, r.layout)) {
+  if (in_place && r.any_dp && r.T <= kSkinnyMaxTokens) {
     const std::vector<Slice> runs = runs_in_place(r, true);
     for (const Slice &l : runs) OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_FWD, run_gemm(r, true, l, tab, rep, X, ldx, Y, ldy), sc));
     if (!runs.empty()) return OSDP_OK;

@@ -1011,6 +1011,28 @@ def test_few_tokens_and_wide_outputs_with_slices_in_dp_mode(H, oracle, rows):
             assert in_place == (st["gather"]["launches"] + st["gather_carried"]["launches"] == 0)
 
 
+def test_shards_of_one_k_block_are_staged_where_the_copy_is_the_cheaper_one(H):
+    """Forward over 32 shards of 64 rows: unsplit and narrow it is gathered first, in four slices or wide it is not; the
+    same bits from both."""
+    import paper_2209_13258_amd as osdp
+    T, I, N = 200, 2048, 32
+    for O, ks in ((512, ((1, 1), (4, 0))), (4096, ((1, 0), (4, 0)))):
+        d = wl.small_case(85, T, I, O, N)
+        ref = None
+        for k, gathers in ks:
+            _announce("shards of one K block", T, I, O, N, k)
+            op = H.Operator(d["X"], None, d["W_shards"], O)
+            op.workspace(k, False)
+            osdp.osdp_profile_begin(100)
+            op.fwd(k)
+            st = osdp.osdp_profile_end()
+            assert (st["gemm_fwd"]["launches"], st["gather"]["launches"]) == (1, gathers)
+            Y = H.to_bits(op.Y)
+            assert not np.isnan(H.widen(Y)).any()
+            ref = Y if ref is None else ref
+            assert np.array_equal(Y, ref)
+
+
 @pytest.mark.parametrize("T", [20, 140])   # the few-token kernel; the kernels that take a DP slice as an operand
 @pytest.mark.parametrize("rows", [False, True])
 def test_replica_rows_beyond_32_bit_offsets(H, oracle, T, rows, debug):
