@@ -301,9 +301,7 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   const int nk = src.nb, n0 = src.n0, n_end = src.n_end;
 
   f32x4 acc[MB][NB];
-  if (kAccIn) {
-    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);
-  } else {
+  if constexpr (!kAccIn) {
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
@@ -338,6 +336,9 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   // (Every block runs the same code: loads of blocks beyond the last one are issued too, and deliver zeros nobody uses.)
 #pragma unroll
   for (int s = 0; s < kStages - 1; ++s) issue_range(s, 0, L);
+  // The sum to go on from is asked for behind them, so that both are under way together.  (Loads return in order, so the
+  // wait below also covers part of these; the compiler waits for the rest where the first MFMA reads them.)
+  if constexpr (kAccIn) load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);
   wait_vmcnt<(kStages - 2) * L>();
   __builtin_amdgcn_s_barrier();
 
@@ -370,9 +371,11 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   //     and the workgroup barrier taken there, so that the last micro-step's MFMAs cover the first fragment
   //     reads of block it+1.
   // `par` is the parity of the block's first K step: A fragments of K step kk sit in fa[(par + kk) & 1].
+  // load_: whether loads go out (see the loop below).
   int cur = 0, nxt = kStages - 1;
-  auto block = [&](auto par) {
+  auto block = [&](auto par, auto load_) {
     constexpr int P = decltype(par)::value;
+    constexpr bool kLoad = decltype(load_)::value != 0;
     const int next_stage = (cur + 1 == kStages) ? 0 : cur + 1;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -389,7 +392,7 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
         if (((P + KS) & 1) == 0) read_a(next_stage, 0, Int<0>{}); else read_a(next_stage, 0, Int<1>{});
         read_b(next_stage, 0, 0, Int<0>{});
       }
-      if (u < kIssueSteps) issue_range(nxt, u * L / kIssueSteps, (u + 1) * L / kIssueSteps);
+      if (kLoad && u < kIssueSteps) issue_range(nxt, u * L / kIssueSteps, (u + 1) * L / kIssueSteps);
       __builtin_amdgcn_sched_barrier(0);
       if (((P + kk) & 1) == 0) {
         if (h == 0) mfmas(Int<0>{}, Int<0>{}, Int<0>{}); else mfmas(Int<0>{}, Int<1>{}, Int<1>{});
@@ -401,7 +404,7 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
         // loads issued after the last load of block it+1: the full blocks it+2 .. it+kStages-2 and the
         // shares of block it+kStages-1 issued so far in this block
         constexpr int kYounger = (kStages >= 3) ? (kStages - 3) * L + (U - 1) * L / kIssueSteps : 0;
-        wait_vmcnt<kYounger>();
+        wait_vmcnt<kLoad ? kYounger : 0>();
         __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0): this wave's LDS reads are done
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -413,12 +416,22 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
 
   read_a(0, 0, Int<0>{});
   read_b(0, 0, 0, Int<0>{});
-  if (KS % 2 == 0) {
-    for (int it = 0; it < nk; ++it) block(Int<0>{});
+  // Launches that pass a sum on are short (a slice's worth of k) and many: blocks beyond the last one, which elsewhere are
+  // asked for and deliver zeros, would be half as much as what counts, so these end with blocks that load nothing (the
+  // backward of 8192 -> 2048 over 768 tokens in 16 slices: 204 us, with this and the sum asked for behind the first
+  // blocks 198; 640 tokens 4096 -> 2048 128 and 125).
+  constexpr bool kShort = (kAccIn || kEpi == static_cast<int>(Epilogue::kF32Workspace)) && KS % 2 == 0;
+  if constexpr (kShort) {
+    const int ahead = nk - (kStages - 1);
+    int it = 0;
+    for (; it < ahead; ++it) block(Int<0>{}, Int<1>{});
+    for (; it < nk; ++it) block(Int<0>{}, Int<0>{});
+  } else if constexpr (KS % 2 == 0) {
+    for (int it = 0; it < nk; ++it) block(Int<0>{}, Int<1>{});
   } else {  // an odd number of K steps per block: the A fragment buffers swap roles from block to block
     for (int it = 0; it < nk; it += 2) {
-      block(Int<0>{});
-      if (it + 1 < nk) block(Int<1>{});
+      block(Int<0>{}, Int<1>{});
+      if (it + 1 < nk) block(Int<1>{}, Int<1>{});
     }
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
