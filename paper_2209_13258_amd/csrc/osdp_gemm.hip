@@ -271,9 +271,12 @@ constexpr int kW4MinKdW = 8192;
 
 // Estimated cost of covering M x N with BM x BN tiles on 256 CUs: tiles per CU times the tile's area, with a
 // penalty for the lower MFMA efficiency of smaller tiles.  Tiles that run two to a CU were measured in pairs; a
-// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  A launch of one to two such
-// tiles per CU lasts nearly as its number of tiles: what it waits for is the memory that the CUs share (128 x 128 over
-// K = 2560: 320 tiles 38 us, 480 tiles 52 us).  A tile that sticks out of the matrix costs what a full one does.
+// CU's odd last tile runs alone and slower, which is priced as one and a half tiles.  A launch of one to two tiles of
+// 128 x 128 per CU lasts nearly as its number of tiles: what it waits for is the memory that the CUs share (K = 2560: 320
+// tiles 38 us, 480 tiles 52 us).  Of tiles of 256 x 128 and 128 x 256 one and a quarter a CU last nearly as long as two
+// (1.5 + 0.25 x; us against 256 x 256, one to a CU: 4096 x 2688 over K = 2688 73 and 72 against 65, dX 74 and 75 against 62;
+// 2048 x 6144 over 6912 178 and 172 against 155; 768 x 14592 over 9984 305 and 274 against 239; dW of 2048 x 5632 over 16384
+// tokens 392 and 421 against 374).  A tile that sticks out of the matrix costs what a full one does.
 // lone > 0: the penalty of a launch of at most one tile per CU, which has the CU's whole LDS for its pipeline.
 long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
@@ -282,7 +285,8 @@ double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, do
   const long per_cu = (tiles + kCUs - 1) / kCUs;
   const bool two_per_cu = BM * BN <= 256 * 128;
   if (two_per_cu && per_cu == 1 && lone > 0.0) return lone * BM * BN;
-  const double units = (two_per_cu && per_cu == 2)  ? 0.4 + 0.8 * static_cast<double>(tiles) / kCUs
+  const double x = static_cast<double>(tiles) / kCUs;
+  const double units = (two_per_cu && per_cu == 2)  ? (BM * BN > 128 * 128 ? 1.5 + 0.25 * x : 0.4 + 0.8 * x)
                        : (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5
                                                     : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
