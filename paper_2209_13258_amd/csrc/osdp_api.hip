@@ -428,7 +428,7 @@ bool recut(const osdp_shape *shape, const Resolved &r, bool is_fwd, Resolved *ou
     double t = 0.0;
     for (const Slice &l : is_fwd ? q.fwd : q.pass) {
       const int64_t span = q.sub[l.c1 - 1].c1 - q.sub[l.c0].c0;
-      t += adds ? gemm_estimate_us(q.T, q.D, span) : gemm_estimate_us(q.T, span, q.D);
+      t += adds ? gemm_planned_us(q.T, q.D, span, !is_fwd) : gemm_planned_us(q.T, span, q.D, !is_fwd);
     }
     if (adds) t += static_cast<double>(sum.size() - 1) * 8.0 * static_cast<double>(q.T) * static_cast<double>(q.D) / 4.5e6;
     if (!is_fwd)

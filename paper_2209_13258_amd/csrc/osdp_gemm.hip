@@ -621,6 +621,13 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   return rounds * GBM * GBN * 5.0 * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;  // the checked kernel is about 5x slower per tile
 }
 
+double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx) {
+  if (M <= 0 || !fast_path(static_cast<int>(K), 0, 0)) return gemm_estimate_us(M, N, K);
+  int axis, cut;
+  const double cost = plan_launches(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), dx ? 2 : 0, &axis, &cut);
+  return cost * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;
+}
+
 int64_t gemm_persistent_launches() { return t_persistent_launches; }
 
 size_t gemm_forward_parts_bytes(int64_t M, int64_t N, int64_t K) {

@@ -145,6 +145,10 @@ bool gemm_takes_two_column_segments(int64_t n_first, int64_t n_second, int64_t K
 // tokens meet a long reduction.
 double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts = false);
 
+// The same for a forward or (dx) dX product of one segment as launch_gemm runs it, whole rounds and a remainder as two
+// launches where that is faster.
+double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx);
+
 // Launches of the calling thread that ran as the persistent four-wave kernel so far (for the profile).
 int64_t gemm_persistent_launches();
 

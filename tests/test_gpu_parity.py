@@ -1113,6 +1113,34 @@ def test_a_pass_cut_the_other_way_keeps_the_bits_of_the_sum(H, oracle, T, I, O, 
                 assert np.array_equal(got[1][name], got[0][name]), f"{name} differs from the plan's own cut (dim {dim}, mode {mode})"
 
 
+@pytest.mark.parametrize("T,I,O,k,dim,other", [
+    (4096, 17408, 6144, 4, 1, False),   # sums of 384 large tiles run as whole rounds and a remainder: the plan's cut
+    (4096, 32768, 8192, 8, 0, True),    # dX: a sum of 512 MiB, seven trips of it
+    (8192, 10240, 2560, 16, 0, True),
+])
+def test_the_estimate_cuts_a_pass_the_other_way_where_that_is_faster(H, T, I, O, k, dim, other, debug):
+    """The library's own choice between the sum over the plan's slices and slices along the other dimension."""
+    import paper_2209_13258_amd as osdp
+    plan = osdp.Plan([k], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[dim])
+    kind = "gemm_fwd" if dim else "gemm_dx"
+    X, dY = (torch.zeros((T, n), dtype=torch.bfloat16, device="cuda") for n in (I, O))
+    W = [torch.zeros((I * O // 8,), dtype=torch.bfloat16, device="cuda") for _ in range(8)]
+    out, dW = torch.empty((T, O if dim else I), dtype=torch.bfloat16, device="cuda"), [torch.empty_like(w) for w in W]
+    ws = torch.empty(osdp.osdp_split_linear_workspace_bytes(T, I, O, 8, k, not dim, plan)[0], dtype=torch.uint8, device="cuda")
+    nbytes = {}
+    for recut in (0, 1, -1):
+        debug("recut", recut)
+        _announce("cut by estimate", T, I, O, k, dim, recut)
+        osdp.osdp_profile_begin(100)
+        if dim:
+            osdp.osdp_split_linear_fwd(X, W, out, k, ws, plan=plan)
+        else:
+            osdp.osdp_split_linear_bwd(X, dY, W, out, dW, k, ws, plan=plan)
+        nbytes[recut] = osdp.osdp_profile_end()[kind]["bytes"]
+    assert nbytes[1] < nbytes[0]
+    assert nbytes[-1] == nbytes[1 if other else 0]
+
+
 @pytest.mark.parametrize("T,I,O,N,k", [
     (520, 448, 320, 4, 1),        # whole tiles of 224 rows of dW; two tiles of 160 columns of Y
     (1001, 456, 648, 3, 3),       # a tile of 8 rows or columns behind the last whole one; ragged K blocks; slices of 216
