@@ -47,6 +47,34 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point(H, oracle, rows):
         H.assert_close("Y", got, oracle.linear(d["X"], d["W_shards"], O, want=("Y",))["Y"])
 
 
+@pytest.mark.parametrize("rows", [False, True])
+def test_two_staging_calls_in_a_row_match_the_workspace_entry_point(H, oracle, rows):
+    """The same with calls that really use the array: enough tokens that slices are staged in it, and with row slices
+    the fp32 partial sum (the pass is kept from being cut the other way, which needs none)."""
+    import paper_2209_13258_amd as osdp
+    dim = osdp.OSDP_SPLIT_IN_FEATURES if rows else osdp.OSDP_SPLIT_OUT_FEATURES
+    stream = torch.cuda.Stream()
+    osdp.osdp_debug_option("recut", 0)
+    try:
+        for seed, (T, I, O, N, k, mode) in enumerate([(768, 1024, 2048, 8, 4, osdp.OSDP_STAGING_DOUBLE),
+                                                      (530, 264, 528, 4, 3, osdp.OSDP_STAGING_SINGLE),
+                                                      (530, 288, 576, 4, 3, osdp.OSDP_STAGING_HALF)]):
+            print("no-alloc forward, staged", T, I, O, N, k, "rows" if rows else "columns", flush=True)
+            d = wl.small_case(125 + seed, T, I, O, N)
+            plan = osdp.Plan([k], staging=mode, split_dim_per_op=[dim])
+            osdp.osdp_profile_begin(1000)
+            got, want = _fwd_pair(H, d, O, k, plan, stream)
+            st = osdp.osdp_profile_end()
+            assert st["gather"]["launches"] + st["gather_carried"]["launches"] >= 2 * 2, "nothing was staged"
+            if rows:
+                # two calls' operands and results alone would be fewer bytes: the partial sum went out and came back
+                assert st["gemm_fwd"]["bytes"] > 2 * 2 * (T * I + I * O + T * O) + 2 * 4 * T * O
+            assert np.array_equal(got, want), "the no-workspace forward differs from osdp_split_linear_fwd"
+            H.assert_close("Y", got, oracle.linear(d["X"], d["W_shards"], O, want=("Y",))["Y"])
+    finally:
+        osdp.osdp_debug_option("recut", -1)
+
+
 def test_sizes_beyond_the_array_are_refused_before_anything_runs(H):
     import paper_2209_13258_amd as osdp
     T, I, O, N = 128, 8192, 8192, 8            # unsplit: one slot of 128 MiB
