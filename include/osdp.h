@@ -54,8 +54,10 @@
  *     state in the library.  Two calls that use the same workspace or outputs
  *     must be ordered by the caller's streams like any other GPU work.
  *   - Calls enqueue work and return.  When a call returns, synchronising
- *     stream_compute alone makes every output valid, and stream_copy has been
- *     ordered after the last use of the workspace.  Inputs must be ready on
+ *     stream_compute alone makes every output valid.  A call that put work on
+ *     stream_copy has ordered it behind the last use of the workspace; by default
+ *     calls run on stream_compute alone, and work of the caller's on stream_copy
+ *     that reuses the workspace has to wait for it.  Inputs must be ready on
  *     stream_compute when the call is made.
  *   - The forward, backward and gather calls can be captured into a HIP graph on
  *     stream_compute (after one eager call, which sets kernel attributes): they enqueue
@@ -105,7 +107,9 @@ typedef struct {
   int32_t k; /* slice granularity; 0 == 1 == unsplit               */
 } osdp_shape;
 
-/* How the slice-sized staging area is used. */
+/* How the slice-sized staging area is used, by calls that stage slices.  Few tokens do not: up to 128 are multiplied with
+ * the weights where they lie (shards or replicas), up to 512 with the shards where those are row blocks of a multiple of 64
+ * rows and every slice is gathered; the workspace asked for is the same. */
 typedef enum {
   OSDP_STAGING_AUTO = 0,   /* DOUBLE when two distinct streams are given and k > 1, else SINGLE */
   OSDP_STAGING_SINGLE = 1, /* one slot of one slice (size/k): gather and GEMM alternate, no overlap */
@@ -204,8 +208,12 @@ OSDP_API osdp_status osdp_split_linear_workspace_bytes(const osdp_shape *shape, 
  * multiple of 16).  With column slices, T <= 4096 and I >= 16384 (few output tiles per slice, a long reduction)
  * the product is the sum over min(I / 8192, 8) parts of the input features, each part accumulated on its own and
  * the parts added in ascending order in fp32 before the one rounding to bf16 (when that number of parts times 64
- * divides I): the unsplit operator (k = 1) is computed the same way, so this too is independent of k.  (Row slices always
- * continue one accumulator chain.) */
+ * divides I): the unsplit operator (k = 1) is computed the same way, so this too is independent of k.  Row slices
+ * continue one accumulator chain.
+ * Few tokens, T <= 128: whatever the slices, Y is the fp32 sum, in ascending order, of four parts of the input features,
+ * each accumulated on its own and ceil(ceil(I / 64) / 4) * 64 long (the last ones as long as what is left), rounded once.
+ * Not so, but as above, from T = 65 on when O > 8192, the shards are row blocks of a multiple of 64 rows and I is not
+ * summed in parts of 8192, and for ldx >= 2^22.  The rule looks at T, I, O and N only: Y is independent of k here too. */
 OSDP_API osdp_status osdp_split_linear_fwd(const osdp_shape *shape, const osdp_plan *plan, int32_t op_index,
                                   const void *X, int64_t ldx, const void *const *w_shards,
                                   void *Y, int64_t ldy, void *workspace, size_t workspace_bytes,
@@ -240,7 +248,9 @@ OSDP_API osdp_status osdp_split_linear_fwd_noalloc(const osdp_shape *shape, cons
  * With row slices: dW[r0_j:r1_j, :] = X[:, r0_j:r1_j]^T . dY and dX[:, r0_j:r1_j] = dY . Wr_j^T, no sum.
  * dW is bit-identical for every k and split dimension; dX is too when every slice width is a
  * multiple of 16 (row slices: always; with T <= 4096 and O >= 16384 their dX is summed in parts of 8192 output
- * features, like the forward product of column slices, whatever k). */
+ * features, like the forward product of column slices, whatever k).  Few tokens, T <= 128: dX is the sum of four parts of
+ * the output features, by the rule of the forward product with I and O exchanged, and independent of k and the split
+ * dimension. */
 OSDP_API osdp_status osdp_split_linear_bwd(const osdp_shape *shape, const osdp_plan *plan, int32_t op_index,
                                   const void *X, int64_t ldx, const void *dY, int64_t lddy,
                                   const void *const *w_shards, void *dX, int64_t lddx,
@@ -397,19 +407,21 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
                                       uint8_t *modes, osdp_search_result *result);
 
 /* ---- test and debug switches ------------------------------------------------
- * Process-wide switches for tests and for hunting stream races; none of them
- * but "split_k" changes a result bit.  Initial values come from the environment variables
+ * Process-wide switches for tests and for hunting stream races.  Result bits change with
+ * "split_k", and for T <= 128 with "gemm_generic" = 1 and "tile" >= 0, which turn the sum of four parts
+ * into that of more tokens; with no other.  Initial values come from the environment variables
  * OSDP_DEBUG_<NAME IN CAPITALS>, read once when the library is first used.
  *   "gemm_generic"   0 | 1   1: every GEMM runs on the bounds-checked kernel
- *   "tile"          -1 .. 3  force tile shape 256x256, 256x128, 128x256, 128x128 where it divides the launch
+ *   "tile"          -1 .. 3  force tile shape 256x256, 256x128, 128x256, 128x128 (in launches over two column ranges of
+ *                            the weight: where it fits them)
  *   "small_tile"    -1 .. 1  0: the four-wave kernel runs 256x256 tiles only; 1: tiles of 224x256 (dW) and 256x160
  *                            (forward, dX) wherever they serve the launch
  *   "deep"          -1 | 0   0: launches of at most one tile per CU keep the shallow LDS pipelines
  *   "split_launch"  -1 | 0   0: no launch is cut into whole rounds of large tiles + remainder
- *   "split_k"       -1 | 0   0: forward products are never summed in parts of the reduction (the one switch that
- *                            changes result bits: those of the products that are otherwise summed in parts)
+ *   "split_k"       -1 | 0   0: forward products are never summed in parts of the reduction (this
+ *                            changes the bits of the products that are otherwise summed in parts)
  *   "four_wave"     -1 .. 1  0: 256x256 tiles always run on the eight-wave kernel; 1: on the four-wave kernel
- *                            whenever it takes the launch (K >= 192), also where the eight-wave one measured faster
+ *                            whenever it takes the launch (K > 128), also where the eight-wave one measured faster
  *   "persistent"    -1 .. 1  0: a launch of more 256x256 tiles than CUs keeps the four-wave kernel of one tile per
  *                            workgroup; otherwise one workgroup per CU walks through the tiles; 1: the walking
  *                            form also for launches of fewer tiles
@@ -425,7 +437,8 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
  *                            stream, ahead of the event that hands the slot to the next gather): a GEMM that
  *                            runs ahead of its gather, or a gather that lands on a slice still in use,
  *                            then shows up as NaN or wrong outputs instead of going unnoticed because the
- *                            stale bytes happened to be right.  Costs one fill per slot use.
+ *                            stale bytes happened to be right.  Costs one fill per slot use.  Calls of 129 to 512
+ *                            tokens stage their slices under it; up to 128 tokens use no slot.
  * -1 restores the library's own choice.  OSDP_ERR_INVALID_ARG for unknown names or values. */
 OSDP_API osdp_status osdp_debug_option(const char *name, int32_t value);
 

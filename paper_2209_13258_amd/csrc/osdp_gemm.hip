@@ -5,7 +5,7 @@
 // bf16 operands, fp32 accumulation on the gfx950 matrix cores
 // (v_mfma_f32_16x16x32_bf16), bf16 round-to-nearest-even outputs.
 //
-// Every kernel in this file feeds each output element the same sequence of
+// Every kernel in this file but the few-token one (gemm_skinny.h) feeds each output element the same sequence of
 // MFMA operations: K is walked in ascending blocks of 32, and inside a block
 // logical k = 8*q + e sits in lane group q, element e of both operands.  Tile
 // shape therefore never changes a result bit, which is what makes Y and dW of
@@ -311,7 +311,7 @@ struct TileShape {
 };
 // 8192^3 on MI355X, forward / dW / dX in PFLOP/s, eight-wave kernels: 256x256 1.22 / 1.23 / 1.26; 256x128 (two
 // workgroups per CU) 1.04 / 0.90 / 1.09; 128x256 (two per CU) 1.19 / 1.02 / 1.06; 128x128 (two per CU) 1.03 / 1.05 /
-// 1.03.  The 256x256 tile runs on the four-wave kernel (gemm_w4.h) whenever K >= 192: 1.43 / 1.30 / 1.45 on the
+// 1.03.  The 256x256 tile runs on the four-wave kernel (gemm_w4.h) whenever K > 128: 1.43 / 1.30 / 1.45 on the
 // same problem, which is what the penalties of the other shapes are relative to.
 // K block and LDS stages of the eight-wave kernels per layout, also measured: forward (transposing reads of B) runs
 // best with K blocks of 64 in two stages, dW and dX on the 256x256 tile and dW on the 128x128 tile with K blocks of
@@ -354,7 +354,8 @@ bool tile_offered(int i, int kind, int K) {
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
 int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, bool acc_in = false) {
-  // (a lone tile that starts from a sum in memory has nothing to cover that load with: 98 us against 86 in pairs)
+  // (a lone tile that starts from a sum in memory has only its first K blocks to cover that load with: 2048 x 4096 over K =
+  // 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
   const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
   int best = -1;
   double best_cost = 0.0;

@@ -126,6 +126,8 @@ hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act
 // would only add a write and a read of it, and a launch per slice that fills a fraction of the CUs.  With more rows the
 // XCDs share the panels, and the copy, which leaves the slice in one dense piece, is what the sharded layout is for.
 // Measured, 500 tokens 2560 -> 10240 forward at k = 4: 118 us as four gathers and four products, 38 us as one.
+// (256 to 512 tokens, 1024 to 16384 features, 8 to 64 shards, k = 1 and 4: 1.05 to 2.5 times as fast as staged, but for
+// unsplit forwards over shards of 64 rows, see switches_pay; more than 512 tokens have not been timed in place.)
 constexpr int64_t kShardReadMaxTokens = 512;
 bool gemm_reads_shards(int64_t T, int64_t ld_act, const ShardLayout &lay);
 
