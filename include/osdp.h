@@ -211,7 +211,7 @@ OSDP_API osdp_status osdp_split_linear_workspace_bytes(const osdp_shape *shape, 
  * divides I): the unsplit operator (k = 1) is computed the same way, so this too is independent of k.  Row slices
  * continue one accumulator chain.
  * Few tokens, T <= 128: whatever the slices, Y is the fp32 sum, in ascending order, of four parts of the input features,
- * each accumulated on its own and ceil(ceil(I / 64) / 4) * 64 long (the last ones as long as what is left), rounded once.
+ * each accumulated on its own and ceil(ceil(I / 32) / 4) * 32 long (the last ones as long as what is left), rounded once.
  * Not so, but as above, from T = 65 on when O > 8192, the shards are row blocks of a multiple of 64 rows and I is not
  * summed in parts of 8192, and for ldx >= 2^22.  The rule looks at T, I, O and N only: Y is independent of k here too. */
 OSDP_API osdp_status osdp_split_linear_fwd(const osdp_shape *shape, const osdp_plan *plan, int32_t op_index,
@@ -249,8 +249,8 @@ OSDP_API osdp_status osdp_split_linear_fwd_noalloc(const osdp_shape *shape, cons
  * dW is bit-identical for every k and split dimension; dX is too when every slice width is a
  * multiple of 16 (row slices: always; with T <= 4096 and O >= 16384 their dX is summed in parts of 8192 output
  * features, like the forward product of column slices, whatever k).  Few tokens, T <= 128: dX is the sum of four parts of
- * the output features, by the rule of the forward product with I and O exchanged, and independent of k and the split
- * dimension. */
+ * the output features, ceil(ceil(O / 64) / 4) * 64 long, by the rule of the forward product with I and O exchanged, and
+ * independent of k and the split dimension. */
 OSDP_API osdp_status osdp_split_linear_bwd(const osdp_shape *shape, const osdp_plan *plan, int32_t op_index,
                                   const void *X, int64_t ldx, const void *dY, int64_t lddy,
                                   const void *const *w_shards, void *dX, int64_t lddx,

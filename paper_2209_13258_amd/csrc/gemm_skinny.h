@@ -8,8 +8,8 @@
 // staged at all.  What counts is the bytes in flight: a workgroup owns BN output columns, its four waves take a quarter
 // of the reduction each, and every wave streams its own K blocks through its own ring of LDS stages with no barrier
 // until the four partial sums meet at the end, added in ascending order of k and rounded once.  The quarters end on
-// multiples of 64 whatever the K block of the tile, so the order of the sum depends on the reduction length alone: not on
-// the tile (the number of tokens and of columns), the slicing, the place of a slice or where the weights lie.
+// multiples of 32 (dX: 64) whatever the K block of the tile, so the order of the sum depends on the reduction length alone:
+// not on the tile (the number of tokens and of columns), the slicing, the place of a slice or where the weights lie.
 //
 // MFMA as in the other kernels (16 x 16 x 32, k ascending); rows beyond T arrive as zeros.
 //
@@ -198,9 +198,10 @@ void gemm_skinny_kernel(SkinnyParams p) {
   const int n0 = tn * BN, m0 = (id - tn * p.tiles_m) * BM;
   const int m_left = p.M - m0 < BM ? p.M - m0 : BM;
 
-  // this wave's K blocks: a quarter of the reduction in units of 64
-  static_assert(64 % BK == 0, "the waves' ranges are whole K blocks");
-  const int blocks = (p.K + BK - 1) / BK, per = ((p.K + 63) / 64 + kSkinnyWaves - 1) / kSkinnyWaves * (64 / BK);
+  // this wave's K blocks: a quarter of the reduction, in units of the largest K block of any tile
+  constexpr int kUnit = kBKc ? 64 : 32;
+  static_assert(kUnit % BK == 0, "the waves' ranges are whole K blocks");
+  const int blocks = (p.K + BK - 1) / BK, per = ((p.K + kUnit - 1) / kUnit + kSkinnyWaves - 1) / kSkinnyWaves * (kUnit / BK);
   const int b0 = wave * per, b1 = b0 + per < blocks ? b0 + per : blocks;
 
   // byte offset of this lane in load 0 of a block with rows of ld2 bytes; `h`: which of the two permutations
