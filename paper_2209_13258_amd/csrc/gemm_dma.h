@@ -416,11 +416,11 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
 
   read_a(0, 0, Int<0>{});
   read_b(0, 0, 0, Int<0>{});
-  // Launches that pass a sum on are short (a slice's worth of k) and many: blocks beyond the last one, which elsewhere are
+  // Launches that go on from a sum are short (a slice's worth of k) and many: blocks beyond the last one, which elsewhere are
   // asked for and deliver zeros, would be half as much as what counts, so these end with blocks that load nothing (the
   // backward of 8192 -> 2048 over 768 tokens in 16 slices: 204 us, with this and the sum asked for behind the first
-  // blocks 198; 640 tokens 4096 -> 2048 128 and 125).
-  constexpr bool kShort = (kAccIn || kEpi == static_cast<int>(Epilogue::kF32Workspace)) && KS % 2 == 0;
+  // blocks 198; 640 tokens 4096 -> 2048 128 and 125).  Over a long reduction the second loop costs what it saves.
+  constexpr bool kShort = kAccIn && KS % 2 == 0;
   if constexpr (kShort) {
     const int ahead = nk - (kStages - 1);
     int it = 0;

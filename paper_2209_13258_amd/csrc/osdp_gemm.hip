@@ -280,13 +280,14 @@ constexpr int kW4MinKdW = 8192;
 // lone > 0: the penalty of a launch of at most one tile per CU, which has the CU's whole LDS for its pipeline.
 long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
-double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, double lone = 0.0) {
+// by_number: 256 x 128 tiles, too, are priced by their number from one to two a CU.
+double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, double lone = 0.0, bool by_number = false) {
   const long tiles = tile_count(M, N, BM, BN) * parts;
   const long per_cu = (tiles + kCUs - 1) / kCUs;
   const bool two_per_cu = BM * BN <= 256 * 128;
   if (two_per_cu && per_cu == 1 && lone > 0.0) return lone * BM * BN;
   const double x = static_cast<double>(tiles) / kCUs;
-  const double units = (two_per_cu && per_cu == 2)  ? (BM * BN > 128 * 128 ? 1.5 + 0.25 * x : 0.4 + 0.8 * x)
+  const double units = (two_per_cu && per_cu == 2)  ? (BM * BN > 128 * 128 && !by_number ? 1.5 + 0.25 * x : 0.4 + 0.8 * x)
                        : (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5
                                                     : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
@@ -357,11 +358,14 @@ int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int part
   // (a lone tile that starts from a sum in memory has only its first K blocks to cover that load with: 2048 x 4096 over K =
   // 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
   const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
+  // (dW of fewer tokens, whose 256 x 256 tiles run on the eight-wave kernel: 5120 x 2048 over 1024 36 us in 320 tiles of 128 x
+  // 256, 41 in 160 large ones; 15360 x 768 over 1664 52 in 360, 55 in 180)
+  const bool by_number = kind == 1 && K / parts < kW4MinKdW;
   int best = -1;
   double best_cost = 0.0;
   for (int i = 0; i < kTileShapes; ++i) {
     if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts)) continue;
-    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0);
+    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0, by_number);
     if (best < 0 || c < best_cost) {
       best = i;
       best_cost = c;
