@@ -1,6 +1,8 @@
 // Device-side pieces shared by the GEMM kernels of libosdp: parameter block, bf16 rounding,
 // the workgroup -> tile map, accumulator load and the three epilogues.
 #pragma once
+#include <utility>
+
 #include "osdp_internal.h"
 
 namespace osdp {
@@ -8,6 +10,22 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// Compile-time integers as lambda arguments.
+template <int v>
+struct Int {
+  static constexpr int value = v;
+};
+// f(Int<0>{}), f(Int<1>{}), ..., f(Int<N-1>{}): a loop whose index is a compile-time constant in every iteration, so
+// that register arrays are never indexed at run time and nothing depends on the optimiser's unrolling.
+template <class F, int... Is>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>) {
+  (f(Int<Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
+}
 
 // One matrix-core step of every GEMM kernel here: a 16 x 16 block of C gains the product over 32 consecutive k.
 // Lane l supplies 8 consecutive k (8 * (l / 16) ..) of row / column l % 16 of each operand.  The operands are
@@ -57,17 +75,14 @@ struct GemmParams {
   GatherJob job;       // only read by kernels instantiated to carry one
 };
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, f);
-  const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;  // nearest even; carries into the exponent correctly
-  const uint32_t quiet = (u >> 16) | 0x0040u;                        // NaN stays NaN
-  return static_cast<uint16_t>((u & 0x7fffffffu) > 0x7f800000u ? quiet : rounded);
-}
-
+// Two fp32 values rounded to bf16, nearest even, in one instruction (v_cvt_pk_bf16_f32): in integer arithmetic the same
+// rounding takes about ten instructions a value, a third of what an epilogue used to execute.  The same bits for all 2^32
+// inputs (NaN stays NaN, quiet, with the upper bits of its payload).
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return static_cast<uint32_t>(f32_to_bf16_rne(lo)) | (static_cast<uint32_t>(f32_to_bf16_rne(hi)) << 16);
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, v);
 }
-
 
 // Tile index of this workgroup.  Workgroups are dealt round-robin to the 8 XCDs, each with its
 // own L2, so consecutive logical tile ids are first mapped onto one XCD; logical ids then walk
@@ -156,25 +171,103 @@ __device__ __forceinline__ void store_acc4(const GemmParams &p, f32x4 c, int m, 
   store_global8(dst, o);
 }
 
-// plane_row: added to the row where the tile is stored (launches that run parts of the reduction), not to the bound.
-template <int MB, int NB, int kEpi>
-__device__ __forceinline__ void store_acc_tile(const GemmParams &p, const f32x4 (&acc)[MB][NB], int m_base, int n_base,
-                                               int n_end, int plane_row, int l16, int q, uint16_t *const *s_tab) {
-  if (m_base + MB * 16 <= p.M && n_base + NB * 16 <= n_end) {  // (the whole wave tile is inside: no test per store)
-#pragma unroll
-    for (int bm = 0; bm < MB; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < NB; ++bn)
-        store_acc4<kEpi>(p, acc[bm][bn], plane_row + m_base + bm * 16 + l16, n_base + bn * 16 + 4 * q, s_tab);
+// One wave's share of the result, 16 * MB x 16 * NB from row m_base and column n_base on; read(bm, bn) gives a block's
+// accumulators (indices are compile-time).  Rows from p.M and columns from n_end on are left out.  plane_row: added to the
+// row where the tile is stored (launches that run parts of the reduction), not to the bound.
+//
+// An epilogue is straight-line code that every wave runs once a tile, so its length is what it costs: fetched for the first
+// time, it runs as fast as the instructions arrive.  One row block therefore takes one address, and everything else is an
+// immediate offset; where a row lies in the shards is worked out once and then carried from row block to row block (the
+// division, once per block of 16 x 16 in either layout, was what made the kernels 180 KB long).  bf16 results of two
+// neighbouring blocks change lanes (v_permlane16_swap) so that a lane holds 8 columns: 16 bytes a store, 64 a row.
+// 4096 x 4096 over K = 512 in 256 x 256 tiles, one to a CU, forward / dX / dW into shards: 28.4 / 28.0 / 51.5 us before,
+// 23.8 / 22.8 / 34.9 now (dW with the gather it carries); 8192^3 in four rounds 768 / 776 / 819 and 765 / 764 / 765.
+template <int MB, int NB, int kEpi, class Read>
+__device__ __forceinline__ void store_tile(const GemmParams &p, Read &&read, int m_base, int n_base, int n_end,
+                                           int plane_row, int l16, int q, uint16_t *const *s_tab) {
+  const int m = m_base + l16;
+  if constexpr (kEpi == static_cast<int>(Epilogue::kF32Workspace)) {
+    float *dst = static_cast<float *>(p.C) + static_cast<int64_t>(plane_row + m) * p.ldc + n_base + 4 * q;
+    static_for<MB>([&](auto bm_) {
+      constexpr int bm = decltype(bm_)::value;
+      const bool row = m + 16 * bm < p.M;
+      static_for<NB>([&](auto bn_) {
+        constexpr int bn = decltype(bn_)::value;
+        if (row && n_base + 16 * bn + 4 * q < n_end) {
+          const f32x4 c = read(Int<bm>{}, Int<bn>{});
+          *reinterpret_cast<float4 *>(dst + 16 * bn) = float4{c[0], c[1], c[2], c[3]};
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      dst += static_cast<int64_t>(16) * p.ldc;
+    });
     return;
   }
-#pragma unroll
-  for (int bm = 0; bm < MB; ++bm)
-#pragma unroll
-    for (int bn = 0; bn < NB; ++bn) {
-      const int m = m_base + bm * 16 + l16, n = n_base + bn * 16 + 4 * q;
-      if (m < p.M && n < n_end) store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
+  constexpr bool kShards = kEpi == static_cast<int>(Epilogue::kBf16ShardMajor);
+  // Blocks 2 i and 2 i + 1 side by side: lane group q has columns 8 * (q / 2) .. of block 2 i + (q & 1); a last block
+  // without a neighbour keeps its four columns a lane.
+  const int col = 16 * (q & 1) + 8 * (q >> 1), tail = 16 * (NB - 1) + 4 * q;
+  uint16_t *dst = nullptr;   // where column n_base + col of the lane's row goes
+  int64_t off = 0;           // shards: its offset in shard s
+  int s = 0;
+  if constexpr (kShards) {
+    const int64_t row = m + p.r0, c = p.c0 + n_base + col;
+    if (p.lay.rows_per_shard > 0) {
+      s = static_cast<int>(static_cast<uint32_t>(row) / static_cast<uint32_t>(p.lay.rows_per_shard));
+      off = (row - static_cast<int64_t>(s) * p.lay.rows_per_shard) * p.lay.O + c;
+    } else {
+      const uint64_t f = static_cast<uint64_t>(row * p.lay.O + c);
+      s = static_cast<int>(f / static_cast<uint64_t>(p.lay.L));
+      off = static_cast<int64_t>(f - static_cast<uint64_t>(s) * static_cast<uint64_t>(p.lay.L));
     }
+  } else {
+    dst = static_cast<uint16_t *>(p.C) + static_cast<int64_t>(m) * p.ldc + n_base + col;
+  }
+  static_for<MB>([&](auto bm_) {
+    constexpr int bm = decltype(bm_)::value;
+    const bool row = m + 16 * bm < p.M;  // (rows ascend: a lane outside stays outside, and its place is not looked up)
+    if constexpr (kShards) {
+      if (row) {
+        while (off >= p.lay.L) {
+          off -= p.lay.L;
+          ++s;
+        }
+        dst = s_tab[s] + off;
+      }
+    }
+    // columns `by` further on (of a general flat map they may lie in a later shard)
+    auto place = [&](int by) {
+      uint16_t *at = dst + by;
+      if constexpr (kShards) {
+        if (off + by >= p.lay.L) {
+          int64_t o = off + by;
+          int t = s;
+          while (o >= p.lay.L) {
+            o -= p.lay.L;
+            ++t;
+          }
+          at = s_tab[t] + o;
+        }
+      }
+      return at;
+    };
+    static_for<NB / 2>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      const f32x4 c = read(Int<bm>{}, Int<2 * i>{}), d = read(Int<bm>{}, Int<2 * i + 1>{});
+      const auto lo = __builtin_amdgcn_permlane16_swap(pack_bf16x2(c[0], c[1]), pack_bf16x2(d[0], d[1]), false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(pack_bf16x2(c[2], c[3]), pack_bf16x2(d[2], d[3]), false, false);
+      if (row && n_base + 32 * i + col < n_end) store_global16(place(32 * i), uint4{lo[0], hi[0], lo[1], hi[1]});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (NB % 2) {
+      const f32x4 c = read(Int<bm>{}, Int<NB - 1>{});
+      if (row && n_base + tail < n_end)
+        store_global8(place(tail - col), uint2{pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])});
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kShards) off += static_cast<int64_t>(16) * p.lay.O;
+    else dst += static_cast<int64_t>(16) * p.ldc;
+  });
 }
 
 }  // namespace

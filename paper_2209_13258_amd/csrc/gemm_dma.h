@@ -23,8 +23,6 @@
 //       w ^ (k & 3) and its 32-byte halves are swapped when bit 3 of k is set, so that the k-rows the
 //       lane groups of one ds_read_b64_tr_b16 phase touch fall into different bank groups.
 #pragma once
-#include <utility>
-
 #include "gemm_common.h"
 
 namespace osdp {
@@ -34,22 +32,6 @@ typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef const __attribute__((address_space(1))) void *global_void_ptr;
 typedef __attribute__((ext_vector_type(4))) short dma_s16x4;
 typedef __attribute__((ext_vector_type(8))) short dma_s16x8;
-
-// Compile-time integers as lambda arguments.
-template <int v>
-struct Int {
-  static constexpr int value = v;
-};
-// f(Int<0>{}), f(Int<1>{}), ..., f(Int<N-1>{}): a loop whose index is a compile-time constant in every iteration, so
-// that register arrays are never indexed at run time and nothing depends on the optimiser's unrolling.
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>) {
-  (f(Int<Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
-}
 
 // A 64-bit value that is the same in every lane, as the compiler can see.
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
@@ -436,7 +418,8 @@ void gemm_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
 
-  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
+  store_tile<MB, NB, kEpi>(p, [&](auto bm, auto bn) { return acc[decltype(bm)::value][decltype(bn)::value]; }, m0 + wm, n0 + wn,
+                           n_end, plane_row, l16, q4, s_tab);
 }
 
 }  // namespace

@@ -36,6 +36,21 @@ __device__ __forceinline__ void mma_16x16x32_agpr(f32x4 &c, bf16x8 a_rows, bf16x
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b_cols), "v"(a_rows));
 }
 
+// The four values of an accumulator block, read where this stands and nowhere else: read by the compiler's own
+// copies they may move to the head of the epilogue, all 256 at once, into registers the K loop's fragments hold.
+__device__ __forceinline__ f32x4 acc_read(const f32x4 &c) {
+  float x0, x1, x2, x3;
+  asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
+               : "=v"(x0), "=v"(x1), "=v"(x2), "=v"(x3) : "a"(c[0]), "a"(c[1]), "a"(c[2]), "a"(c[3]));
+  return f32x4{x0, x1, x2, x3};
+}
+
+// What an epilogue takes of it: fp32 results are stored straight from the accumulators.
+template <int kEpi>
+__device__ __forceinline__ f32x4 acc_value(const f32x4 &c) {
+  return kEpi == static_cast<int>(Epilogue::kF32Workspace) ? c : acc_read(c);
+}
+
 // One operand's share of a ring slot: 256 rows (or columns) x 64 k, 32 KB, filled by 32 wave-level
 // direct-to-LDS loads of 1 KB, eight per wave.
 // kBlocks: 16-row blocks of a wave tile, 8 or fewer: of a tile of 32 * kBlocks rows.  A smaller tile keeps the places of
@@ -282,7 +297,8 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
 
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");
-  store_acc_tile<MB, NB, kEpi>(p, acc, m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
+  store_tile<MB, NB, kEpi>(p, [&](auto bm, auto bn) { return acc_value<kEpi>(acc[decltype(bm)::value][decltype(bn)::value]); },
+                           m0 + wm, n0 + wn, n_end, plane_row, l16, q4, s_tab);
 }
 
 template <bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>

@@ -32,15 +32,6 @@ __device__ __forceinline__ void acc_load(f32x4 &c, const float *src) {
   asm volatile("global_load_dwordx4 %0, %1, off" : "+a"(c) : "v"(src) : "memory");
 }
 
-// The four values of an accumulator block, read where this stands and nowhere else: read by the compiler's own
-// copies they may move to the head of the epilogue, all 256 at once, into registers the K loop's fragments hold.
-__device__ __forceinline__ f32x4 acc_read(const f32x4 &c) {
-  float x0, x1, x2, x3;
-  asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
-               : "=v"(x0), "=v"(x1), "=v"(x2), "=v"(x3) : "a"(c[0]), "a"(c[1]), "a"(c[2]), "a"(c[3]));
-  return f32x4{x0, x1, x2, x3};
-}
-
 template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn>
 __device__ __forceinline__ void gemm_w4p_tiles(const GemmParams &p, int tiles_m, int tiles_n) {
   constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
@@ -194,19 +185,10 @@ __device__ __forceinline__ void gemm_w4p_tiles(const GemmParams &p, int tiles_m,
       // computed ahead of the loop they would sit in registers that the K loop has no room for.
       int l16e = l16, q4e = q4;
       asm volatile("" : "+v"(l16e), "+v"(q4e));
-      // one 16 x 16 block at a time (a scheduling fence after each): read all at once, the 256 values would push
-      // the K loop's fragments out of their registers
-      static_for<MB * NB>([&](auto idx) {
-        constexpr int i = decltype(idx)::value, bm = i / NB, bn = i % NB;
-        const int m = m0c + wm + bm * 16 + l16e, n = n0c + wn + bn * 16 + 4 * q4e;
-        if (m < p.M && n < n_endc) {
-          if constexpr (kEpi == static_cast<int>(Epilogue::kF32Workspace))  // (stored straight from the accumulators)
-            store_acc4<kEpi>(p, acc[bm][bn], plane_row + m, n, s_tab);
-          else
-            store_acc4<kEpi>(p, acc_read(acc[bm][bn]), plane_row + m, n, s_tab);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
+      // (a block or two at a time, a scheduling fence after each: read all at once, the 256 values would push the K
+      // loop's fragments out of their registers)
+      store_tile<MB, NB, kEpi>(p, [&](auto bm, auto bn) { return acc_value<kEpi>(acc[decltype(bm)::value][decltype(bn)::value]); },
+                               m0c + wm, n0c + wn, n_endc, plane_row, l16e, q4e, s_tab);
       ct += G;
       if (ct < tiles) begin_tile(ct, l16e, q4e);
       // The fragments read ahead for the next K step are read again here, so that none of them has to outlive the

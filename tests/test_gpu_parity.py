@@ -847,6 +847,41 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
                 assert np.array_equal(got[name], want_bits[name]), f"{name} differs (tile {tile}, k {kk}, dim {dim})"
 
 
+@pytest.mark.parametrize("I,O,N", [
+    (40, 264, 33),    # shards of 320: every row reaches over an end, at a column that changes with the row
+    (264, 520, 60),   # 2288, 4.4 rows
+    (24, 264, 53),    # 120: the last shard ends in padding
+    (64, 136, 64),    # whole rows, one a shard: a row block of a tile lies in 16 of them
+    (8, 1064, 56),    # 152: the columns of a wave lie in two shards
+])
+def test_gradients_in_shards_of_any_length(H, oracle, I, O, N, debug):
+    """dW leaves the kernels in runs of 8 columns whose shard is carried along from row block to row block, not worked out
+    for each: shards that end inside a row and shards of few rows, every tile shape, against the checked kernel (which
+    divides for every run) bit for bit and against the oracle; padding stays as it was."""
+    T = 200
+    d = wl.small_case(75, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+
+    def run():
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        op.bwd(1)
+        torch.cuda.synchronize()
+        flat = np.concatenate([H.to_bits(s) for s in op.dW])
+        assert (flat[I * O:] == POISON).all()
+        return flat[: I * O].reshape(I, O)
+
+    debug("gemm_generic", 1)
+    ref = run()
+    debug("gemm_generic", 0)
+    H.assert_close("dW", ref, want["dW"])
+    for switches in ({"tile": 0, "four_wave": 0}, {"tile": 0, "four_wave": 1, "persistent": 0}, {"tile": 0, "four_wave": 1, "persistent": 1},
+                     {"small_tile": 1}, {"tile": 1}, {"tile": 2}, {"tile": 3}, {"tile": 3, "deep": 0}):
+        for name, value in {**DEBUG_DEFAULTS, **switches}.items():
+            debug(name, value)
+        _announce("shards of any length", I, O, N, switches)
+        assert np.array_equal(run(), ref), switches
+
+
 # ------------------------------------------------ few tokens: the weights are read where they lie
 @pytest.mark.parametrize("T,I,O,N,k", [
     (1, 256, 512, 8, 4),       # one row; shards of 32 rows
