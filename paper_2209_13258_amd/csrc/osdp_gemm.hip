@@ -267,7 +267,6 @@ hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
 
 constexpr int kShortK = 1024;
 constexpr int kW4MinK = 129;  // the four-wave kernel's K loop assumes at least three K blocks of 64
-constexpr int kW4MinKdW = 8192;
 
 // Estimated cost of covering M x N with BM x BN tiles on 256 CUs: tiles per CU times the tile's area, with a
 // penalty for the lower MFMA efficiency of smaller tiles.  Tiles that run two to a CU were measured in pairs; a
@@ -280,14 +279,13 @@ constexpr int kW4MinKdW = 8192;
 // lone > 0: the penalty of a launch of at most one tile per CU, which has the CU's whole LDS for its pipeline.
 long tile_count(int M, int N, int BM, int BN) { return static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
-// by_number: 256 x 128 tiles, too, are priced by their number from one to two a CU.
-double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, double lone = 0.0, bool by_number = false) {
+double tile_cost(int M, int N, int BM, int BN, double penalty, int parts = 1, double lone = 0.0) {
   const long tiles = tile_count(M, N, BM, BN) * parts;
   const long per_cu = (tiles + kCUs - 1) / kCUs;
   const bool two_per_cu = BM * BN <= 256 * 128;
   if (two_per_cu && per_cu == 1 && lone > 0.0) return lone * BM * BN;
   const double x = static_cast<double>(tiles) / kCUs;
-  const double units = (two_per_cu && per_cu == 2)  ? (BM * BN > 128 * 128 && !by_number ? 1.5 + 0.25 * x : 0.4 + 0.8 * x)
+  const double units = (two_per_cu && per_cu == 2)  ? (BM * BN > 128 * 128 ? 1.5 + 0.25 * x : 0.4 + 0.8 * x)
                        : (two_per_cu && per_cu % 2) ? static_cast<double>(per_cu) + 0.5
                                                     : static_cast<double>(per_cu);
   return units * BM * BN * penalty;
@@ -343,10 +341,10 @@ constexpr int kNarrowMinK = 2048;
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
 
 // Whether tile shape i serves a launch of the layout with K as the reduction of a workgroup: the four-wave kernel's own
-// shapes from where that kernel is the faster one for dW, and else from a K loop that pays for its start-up.
+// shapes from a K loop that pays for its start-up.
 bool tile_offered(int i, int kind, int K) {
   if (i < 4) return true;
-  return kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinKdW : kNarrowMinK) &&
+  return kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinK : kNarrowMinK) &&
          debug_options().four_wave.load(std::memory_order_relaxed) != 0 &&
          debug_options().small_tile.load(std::memory_order_relaxed) != 0;
 }
@@ -358,14 +356,11 @@ int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int part
   // (a lone tile that starts from a sum in memory has only its first K blocks to cover that load with: 2048 x 4096 over K =
   // 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
   const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
-  // (dW of fewer tokens, whose 256 x 256 tiles run on the eight-wave kernel: 5120 x 2048 over 1024 36 us in 320 tiles of 128 x
-  // 256, 41 in 160 large ones; 15360 x 768 over 1664 52 in 360, 55 in 180)
-  const bool by_number = kind == 1 && K / parts < kW4MinKdW;
   int best = -1;
   double best_cost = 0.0;
   for (int i = 0; i < kTileShapes; ++i) {
     if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts)) continue;
-    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0, by_number);
+    const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0);
     if (best < 0 || c < best_cost) {
       best = i;
       best_cost = c;
@@ -450,9 +445,10 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
     const int fw = debug_options().four_wave.load(std::memory_order_relaxed);  // testing: 0 never, 1 whenever it can
     switch (best) {
       case 0:
-        // (dW, both operands MN-contiguous: twice the fragment-read instructions and a serial epilogue per wave;
-        // measured through the library, the four-wave kernel is 4-9 % ahead from K = 8192 and 3 % behind at K = 4096)
-        if (p.K / parts >= kW4MinK && fw != 0 && (fw == 1 || p.K >= (kind == 1 ? kW4MinKdW : kW4MinK))) {
+        // (256 x 256 tiles of the eight-wave kernel are left where the four-wave kernel's loop does not fit.  dW ran on them
+        // below 8192 tokens as long as the four-wave epilogue into shards took 25 us a tile; now, eight / four waves, 8192 x
+        // 8192 over 4096 / 1024 / 256 tokens 417 / 378, 133 / 117, 59 / 50 us; 2560 x 10240 over 3001 and 1500 160 / 130, 83 / 74)
+        if (p.K / parts >= kW4MinK && fw != 0) {
           return launch_four_wave<8, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
         }
         if (kind == 0) return launch_dma<256, 256, 64, 128, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
