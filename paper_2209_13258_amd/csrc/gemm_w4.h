@@ -51,49 +51,68 @@ __device__ __forceinline__ f32x4 acc_value(const f32x4 &c) {
   return kEpi == static_cast<int>(Epilogue::kF32Workspace) ? c : acc_read(c);
 }
 
-// One operand's share of a ring slot: 256 rows (or columns) x 64 k, 32 KB, filled by 32 wave-level
-// direct-to-LDS loads of 1 KB, eight per wave.
-// kBlocks: 16-row blocks of a wave tile, 8 or fewer: of a tile of 32 * kBlocks rows.  A smaller tile keeps the places of
-// the large one in LDS (the swizzles work on runs of 128); what lies beyond its rows is not fetched: of a K-contiguous
-// operand by fewer loads, of the other kind by lanes that are out of range.
+// One operand's share of a ring slot: 32 * kBlocks rows (or columns) x 64 k, filled by wave-level direct-to-LDS loads of
+// 1 KB.  kBlocks: 16-row blocks of a wave tile, of a tile of 32 * kBlocks rows.  A K-contiguous operand takes as many rows as
+// the tile has; the other kind, whose swizzle works on runs of 128, takes 128 or 256 columns, and the lanes of those beyond
+// the tile are out of range.
 template <bool kKC, int kBlocks>
 struct W4Operand {
-  static constexpr int kRows = 256, kBK = 64, kWaves = 4;
-  static constexpr int kElems = kRows * kBK;         // 32 KB
-  static constexpr int kLoads = kKC ? kBlocks : 8;   // per wave and block
-  using Base = DmaOperand<kKC, kRows, kBK, kWaves>;
-  // 1 KB chunk that load p of wave w fills.  K-contiguous: chunk c = rows 8c .. 8c+7.  MN-contiguous: chunk c =
-  // k-rows 2c, 2c+1, with (c & 1) and ((c >> 2) & 1) fixed over a wave's loads (the source swizzle depends on them).
+  static constexpr int kRows = kKC ? 32 * kBlocks : (kBlocks > 4 ? 256 : 128), kBK = 64, kWaves = 4;
+  static constexpr int kElems = kRows * kBK;         // 32 KB for 256 rows
+  static constexpr int kLoads = kElems / 2048;       // per wave and block
+  using Base = DmaOperand<kKC, kKC ? 256 : kRows, kBK, kWaves>;
+  static constexpr int kPerChunk = 512 / (kKC ? kBK : kRows);  // rows, or k-rows, that 1 KB holds
+  // 1 KB chunk that load p of wave w fills.  K-contiguous: chunk c = rows 8c .. 8c+7.  MN-contiguous: chunk c = k-rows
+  // 2c, 2c+1 (256 columns), with (c & 1) and ((c >> 2) & 1) fixed over a wave's loads (the source swizzle depends on them),
+  // or k-rows 4c .. 4c+3 (128 columns), with (c >> 1) & 1 fixed.
   static __device__ __forceinline__ constexpr int chunk(int w, int p) {
-    return kKC ? p * 4 + w : (w & 1) + 2 * (p & 1) + 4 * (w >> 1) + 8 * (p >> 1);
+    return kKC || kRows == 128 ? p * 4 + w : (w & 1) + 2 * (p & 1) + 4 * (w >> 1) + 8 * (p >> 1);
   }
   static __device__ __forceinline__ int64_t lane_src(int w, int lane, int64_t ld) {
     if (kKC) {
-      const int row = chunk(w, 0) * 8 + lane / 8;
-      const int c = (lane % 8) ^ Base::swz_k(row);
+      const int row = chunk(w, 0) * kPerChunk + lane / Base::CPR;
+      const int c = (lane % Base::CPR) ^ Base::swz_k(row);
       return static_cast<int64_t>(row) * ld + c * 8;
     } else {
-      const int krow = chunk(w, 0) * 2 + lane / 32;
-      return static_cast<int64_t>(krow) * ld + (((lane % 32) * 8) ^ Base::swz_mn(krow));
+      constexpr int kVecs = kRows / 8;
+      const int krow = chunk(w, 0) * kPerChunk + lane / kVecs;
+      return static_cast<int64_t>(krow) * ld + (((lane % kVecs) * 8) ^ Base::swz_mn(krow));
     }
   }
   static __device__ __forceinline__ int lane_pos(int w, int lane) {  // k (K-contiguous) or mn of those 16 bytes
-    return kKC ? ((lane % 8) ^ Base::swz_k(chunk(w, 0) * 8 + lane / 8)) * 8
-               : ((lane % 32) * 8) ^ Base::swz_mn(chunk(w, 0) * 2 + lane / 32);
+    if (kKC) return ((lane % Base::CPR) ^ Base::swz_k(chunk(w, 0) * kPerChunk + lane / Base::CPR)) * 8;
+    constexpr int kVecs = kRows / 8;
+    return ((lane % kVecs) * 8) ^ Base::swz_mn(chunk(w, 0) * kPerChunk + lane / kVecs);
   }
   static __device__ __forceinline__ constexpr int first_chunk(int w) { return chunk(w, 0); }
   static __device__ __forceinline__ constexpr int chunk_step(int p) { return chunk(0, p) - chunk(0, 0); }
-  static __device__ __forceinline__ constexpr int load_rows(int p) {
-    return chunk_step(p) * (kKC ? 8 : 2);
-  }
+  static __device__ __forceinline__ constexpr int load_rows(int p) { return chunk_step(p) * kPerChunk; }
   static __device__ __forceinline__ bf16x8 frag(const uint16_t *slot, int mn0, int kk, int lane) { return Base::frag(slot, mn0, kk, lane); }
 };
 
-// Load l of the L per block goes out behind MFMA (l * N) / L + 2 of the N in a K step; l, or -1, for a given MFMA.
+// Fragment read r of the MB + NB of a K step goes out behind MFMA r * w4_read_step, B's block 0 first, then all of A's, then
+// the rest of B's: the order in which the next step's MFMAs ask for them.
+constexpr int w4_read_step(int MB, int NB) { return 3 * (MB + NB) <= MB * NB + 1 ? 3 : (2 * (MB + NB) <= MB * NB - 4 ? 2 : 1); }
+constexpr int w4_read_behind(int i, int MB, int NB) {
+  const int step = w4_read_step(MB, NB), first = step > 1 ? 1 : 0;
+  return i % step == first % step && i / step < MB + NB ? i / step : -1;
+}
+
+// Load l of the L per block goes out behind MFMA (l * N) / L + 2 (+ 1 where they are as close as that) of the N in a K step;
+// l, or -1, for a given MFMA.
 constexpr int w4_load_behind(int i, int N, int L) {
   for (int l = 0; l < L; ++l)
-    if (l * N / L + 2 == i) return l;
+    if (l * N / L + (N >= 3 * L || (L - 1) * N / L + 2 < N ? 2 : 1) == i) return l;
   return -1;
+}
+// Every read and every load has its place.
+constexpr bool w4_all_placed(int MB, int NB, int L) {
+  int reads = 0, loads = 0;
+  for (int i = 0; i < MB * NB; ++i) {
+    reads += w4_read_behind(i, MB, NB) >= 0;
+    loads += w4_load_behind(i, MB * NB, L) >= 0;
+  }
+  return reads == MB + NB && loads == L;
 }
 
 // kCopy: the launch also carries p.job, the gather of a slice that a later launch will read (the forward GEMM of
@@ -104,14 +123,17 @@ constexpr int w4_load_behind(int i, int N, int L) {
 // stream it only takes turns with the tiles, and both get slower.  The carried copy is not free either (the kernel
 // is bound by the memory pipe the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a
 // launch of its own); it saves the launch, its gap and every cross-stream event.
-template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy>
+template <int MB, int NB, int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy>
 __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, int tiles_n) {
   constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
   using OpA = W4Operand<kAK, MB>;
   using OpB = W4Operand<kBKc, NB>;
-  static_assert(3 * (MB + NB) <= MB * NB + 1, "the fragment reads of a K step, one behind every third MFMA");
+  // The loads of block b + kAhead go out in block b's second step.  With two slots they fill the slot that every wave has
+  // just read the last fragments of; with more, the one before it, and nobody waits for those reads.
+  constexpr int kAhead = kSlots == 2 ? 2 : kSlots - 1;
   constexpr int kSlotElems = OpA::kElems + OpB::kElems;  // 64 KB
   constexpr int L = OpA::kLoads + OpB::kLoads;           // wave-level loads per wave and block (16 for 256 x 256)
+  static_assert(w4_all_placed(MB, NB, L), "a K step must hold the next one's fragment reads and a block's loads");
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t *const *s_tab = nullptr;
   if constexpr (kEpi == static_cast<int>(Epilogue::kBf16ShardMajor)) {
@@ -191,9 +213,7 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
   const int nb = src.nb, n0 = src.n0, n_end = src.n_end;
 
   f32x4 acc[MB][NB];
-  if (kAccIn) {
-    load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);
-  } else {
+  if constexpr (!kAccIn) {
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)
 #pragma unroll
@@ -215,12 +235,12 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
     if constexpr (i == L - 1) src.next(p, K, wave, lane);
   };
   bf16x8 fa[2][MB], fb[2][NB];
-  asm volatile("s_nop 7");  // accumulator writes (VALU) settle before the first MFMA reads them
 
-  // prologue: blocks 0 and 1 go in flight; block 0 is awaited and the fragments of its first K step read
-  static_for<L>([&](auto i) { issue(0, i); });
-  static_for<L>([&](auto i) { issue(1, i); });
-  wait_vmcnt<L>();
+  // prologue: the first blocks go in flight; block 0 is awaited and the fragments of its first K step read
+  static_for<kAhead>([&](auto b) { static_for<L>([&](auto i) { issue(decltype(b)::value, i); }); });
+  if constexpr (kAccIn) load_acc_tile<MB, NB>(p, acc, m0 + wm, n0 + wn, n_end, l16, q4);  // (the sum is asked for behind them)
+  asm volatile("s_nop 7");  // accumulator writes (VALU) settle before the first MFMA reads them
+  wait_vmcnt<(kAhead - 1) * L>();
   __builtin_amdgcn_s_barrier();
   if constexpr (kCopy) {  // piece 0 of the carried gather (the barrier has published the shard table)
     copy_ptr = copy_src(0, &copy_v);
@@ -243,10 +263,11 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
     static_for<MB * NB>([&](auto idx) {
       constexpr int i = decltype(idx)::value, bn = i / MB, bm = i % MB;
       mma_16x16x32_agpr(acc[bm][bn], fa[P][bm], fb[P][bn]);
-      if constexpr (i % 3 == 1 && i / 3 < MB + NB) {
-        constexpr int r = i / 3;
-        if constexpr (r < NB) fb[Q][r] = OpB::frag(nB, wn + r * 16, rk, lane);
-        else fa[Q][r - NB] = OpA::frag(nA, wm + (r - NB) * 16, rk, lane);
+      if constexpr (w4_read_behind(i, MB, NB) >= 0) {
+        constexpr int r = w4_read_behind(i, MB, NB);
+        if constexpr (r == 0) fb[Q][0] = OpB::frag(nB, wn, rk, lane);
+        else if constexpr (r <= MB) fa[Q][r - 1] = OpA::frag(nA, wm + (r - 1) * 16, rk, lane);
+        else fb[Q][r - MB] = OpB::frag(nB, wn + (r - MB) * 16, rk, lane);
       }
       if constexpr (kLoad && w4_load_behind(i, MB * NB, L) >= 0) issue(ls, Int<w4_load_behind(i, MB * NB, L)>{});
       // carried gather: in the block's first K step the address of the next piece is worked out; in the second,
@@ -269,20 +290,22 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
     });
   };
 
-  // Every block runs the same code: the last two blocks still issue their load instructions (with every lane out of
-  // range) and the last still reads fragments nobody uses.  The host sends K > 128: three blocks or more.
-  int cur = 0;
+  // Every block runs the same code: the last ones still issue their load instructions (with every lane out of
+  // range) and the last still reads fragments nobody uses.
+  int cur = 0, fill = kSlots == 2 ? 0 : kAhead;
+  auto after = [](int slot) { return slot + 1 == kSlots ? 0 : slot + 1; };
   for (int b = 0; b < nb; ++b) {
-    const uint16_t *sc = smem + cur * kSlotElems, *sn = smem + (cur ^ 1) * kSlotElems;
+    const uint16_t *sc = smem + cur * kSlotElems, *sn = smem + after(cur) * kSlotElems;
     // first K step; its shadow reads the second step's fragments of this block
     kstep(Int<0>{}, Int<0>{}, sc, 1, 0);
-    // block b is now fully in registers or consumed, and block b+1 must be in LDS
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+    // block b + 1 must be in LDS, and (two slots) block b fully in registers or consumed
+    wait_vmcnt<(kAhead - 2) * L>();
+    if constexpr (kSlots == 2) __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    kstep(Int<1>{}, Int<1>{}, sn, 0, cur);
-    cur ^= 1;
+    kstep(Int<1>{}, Int<1>{}, sn, 0, fill);
+    cur = after(cur);
+    fill = after(fill);
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
   if constexpr (kCopy) {
@@ -304,14 +327,27 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
 template <bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  gemm_w4_tile<8, 8, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+  gemm_w4_tile<8, 8, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
 }
 
 // Tiles of fewer than 256 rows or columns: 32 * MB x 32 * NB.
 template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  gemm_w4_tile<MB, NB, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+  gemm_w4_tile<MB, NB, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+}
+
+// Tiles of 128 x 128, two workgroups to a CU with two slots each, or one with four (launches of at most one tile per CU).
+// Waves of 64 x 64.  Against eight waves of 32 x 64 (one workgroup to a CU) and a loop of micro-steps over half the B
+// blocks (two) they read a third less out of LDS, or the same with fewer instructions.  What bounds them is the card's power
+// (K = 8192, 512 tiles: 119 us on random data, 94 on zeros) and the bytes through LDS.  us before / now, forward, dW, dX:
+// 2048 x 2048 over K = 8192 68.3 / 65.4, 73.1 / 72.1, 64.8 / 62.1; 2048 x 8192 over 4096 132 / 122, 135 / 132, 129 / 119; the
+// prompt of 500 tokens 2560 -> 10240 35.8 / 33.8.  Tiles of 256 x 128 in waves of 128 x 64 lose to the eight-wave kernel's
+// (4096 x 2048 over K = 4096: 62 against 57 us): with one wave to a SIMD and three slots nothing hides the barriers.
+template <int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn>
+__global__ __launch_bounds__(256, kSlots == 2 ? 2 : 1)
+void gemm_w4_128_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4_tile<4, 4, kSlots, kAK, kBKc, kEpi, kAccIn, false>(p, tiles_m, tiles_n);
 }
 
 }  // namespace

@@ -37,9 +37,9 @@ __device__ __forceinline__ void gemm_w4p_tiles(const GemmParams &p, int tiles_m,
   constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
   using OpA = W4Operand<kAK, MB>;
   using OpB = W4Operand<kBKc, NB>;
-  static_assert(3 * (MB + NB) <= MB * NB + 1, "the fragment reads of a K step, one behind every third MFMA");
   constexpr int kSlotElems = OpA::kElems + OpB::kElems;  // 64 KB
   constexpr int L = OpA::kLoads + OpB::kLoads;           // wave-level loads per wave and block (16 for 256 x 256)
+  static_assert(w4_all_placed(MB, NB, L), "a K step must hold the next one's fragment reads and a block's loads");
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t *const *s_tab = nullptr;
   if constexpr (kEpi == static_cast<int>(Epilogue::kBf16ShardMajor)) {
@@ -149,10 +149,11 @@ __device__ __forceinline__ void gemm_w4p_tiles(const GemmParams &p, int tiles_m,
     static_for<MB * NB>([&](auto idx) {
       constexpr int i = decltype(idx)::value, bn = i / MB, bm = i % MB;
       mma_16x16x32_agpr(acc[bm][bn], fa[P][bm], fb[P][bn]);
-      if constexpr (i % 3 == 1 && i / 3 < MB + NB) {
-        constexpr int r = i / 3;
-        if constexpr (r < NB) fb[Q][r] = OpB::frag(nB, wn + r * 16, rk, lane);
-        else fa[Q][r - NB] = OpA::frag(nA, wm + (r - NB) * 16, rk, lane);
+      if constexpr (w4_read_behind(i, MB, NB) >= 0) {
+        constexpr int r = w4_read_behind(i, MB, NB);
+        if constexpr (r == 0) fb[Q][0] = OpB::frag(nB, wn, rk, lane);
+        else if constexpr (r <= MB) fa[Q][r - 1] = OpA::frag(nA, wm + (r - 1) * 16, rk, lane);
+        else fb[Q][r - MB] = OpB::frag(nB, wn + (r - MB) * 16, rk, lane);
       }
       if constexpr (kLoad && w4_load_behind(i, MB * NB, L) >= 0) {
         issue(ls, Int<w4_load_behind(i, MB * NB, L)>{});

@@ -201,7 +201,7 @@ hipError_t launch_dma(const GemmParams &p, hipStream_t stream) {
 // The four-wave kernel, two K blocks of 64 in LDS (128 KB): 256 x 256 tiles, or fewer rows or columns (32 per block).
 template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn, bool kCopy>
 hipError_t launch_w4(const GemmParams &p, hipStream_t stream) {
-  constexpr size_t lds = 2 * (256 + 256) * 64 * sizeof(uint16_t);
+  constexpr size_t lds = 2 * (W4Operand<kAK, MB>::kElems + W4Operand<kBK, NB>::kElems) * sizeof(uint16_t);
   static_assert(lds + 2 * OSDP_MAX_SHARDS * 8 <= 160 * 1024, "tile does not fit the 160 KB of LDS");
   auto kernel = [] {
     if constexpr (MB == 8 && NB == 8) return gemm_w4_kernel<kAK, kBK, kEpi, kAccIn, kCopy>;
@@ -211,6 +211,21 @@ hipError_t launch_w4(const GemmParams &p, hipStream_t stream) {
   hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
   const int tiles_m = (p.M + 32 * MB - 1) / (32 * MB), tiles_n = tile_columns_of(p, 32 * NB);
+  const int parts = p.k_parts > 1 ? p.k_parts : 1;
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), lds, stream, p, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+// The same with 128 x 128 tiles, 32 KB a slot.
+template <int kSlots, bool kAK, bool kBK, int kEpi, bool kAccIn>
+hipError_t launch_w4_128(const GemmParams &p, hipStream_t stream) {
+  constexpr size_t lds = static_cast<size_t>(kSlots) * (W4Operand<kAK, 4>::kElems + W4Operand<kBK, 4>::kElems) * sizeof(uint16_t);
+  static_assert((kSlots == 2 ? 2 : 1) * (lds + OSDP_MAX_SHARDS * 8) <= 160 * 1024, "tile does not fit the 160 KB of LDS");
+  auto kernel = gemm_w4_128_kernel<kSlots, kAK, kBK, kEpi, kAccIn>;
+  static bool configured[kMaxDevices] = {};
+  hipError_t e = allow_lds(kernel, lds, configured);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (p.M + 127) / 128, tiles_n = tile_columns_of(p, 128);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;
   hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), lds, stream, p, tiles_m, tiles_n);
   return hipGetLastError();
@@ -250,7 +265,7 @@ thread_local int64_t t_persistent_launches = 0;
 // The persistent form of the four-wave kernel: one workgroup per CU walks through the tiles.
 template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
-  constexpr size_t lds = 2 * (256 + 256) * 64 * sizeof(uint16_t);
+  constexpr size_t lds = 2 * (W4Operand<kAK, MB>::kElems + W4Operand<kBK, NB>::kElems) * sizeof(uint16_t);
   auto kernel = [] {
     if constexpr (MB == 8 && NB == 8) return gemm_w4p_kernel<kAK, kBK, kEpi, kAccIn>;
     else return gemm_w4p_small_kernel<MB, NB, kAK, kBK, kEpi, kAccIn>;
@@ -313,14 +328,11 @@ struct TileShape {
 // 1.03.  The 256x256 tile runs on the four-wave kernel (gemm_w4.h) whenever K > 128: 1.43 / 1.30 / 1.45 on the
 // same problem, which is what the penalties of the other shapes are relative to.
 // K block and LDS stages of the eight-wave kernels per layout, also measured: forward (transposing reads of B) runs
-// best with K blocks of 64 in two stages, dW and dX on the 256x256 tile and dW on the 128x128 tile with K blocks of
-// 32 in four stages.
+// best with K blocks of 64 in two stages, dW and dX on the 256x256 tile with K blocks of 32 in four stages.
 // The smaller tiles are sized for two workgroups per CU.  A launch with no more tiles than CUs has one, and is
 // then bound by the latency of its loads (1024x4096x8192 for dW on 128x128 tiles: 41 GB/s per CU with 48 KB in
-// flight); it takes the CU's whole LDS for K blocks of 64 in three or four stages, 96 KB in flight: dW 100 -> 88 us,
-// the forward launch over two 256-column slices with K = 4096 64 -> 52 us.  The lone 128x128 workgroup also runs
-// as 8 waves of 32x64 rather than 4 of 64x64, two per SIMD (another 3-10 %; without the deep pipeline it made no
-// difference).
+// flight); it takes the CU's whole LDS for K blocks of 64 in three or four stages: the forward launch over two 256-column
+// slices with K = 4096 64 -> 52 us.  The 128x128 tile runs on the four-wave kernel (gemm_w4_128_kernel).
 // The last two run on the four-wave kernel alone, in the layouts where they were measured (0: not offered).  They fill
 // rounds that whole tiles leave partly empty; the smaller the tile the more bytes from L2 each MFMA needs, which is
 // what the penalties are (7 % more for 224 x 256, 30 % more for 256 x 160).  dW of 2560 x 5120 over 16384 tokens: 200
@@ -460,9 +472,8 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         if (deep) return launch_dma<128, 256, 64, 64, 64, 3, kAK, kBK, kEpi, kAccIn>(p, stream);
         return launch_dma<128, 256, 64, 64, 32, 3, kAK, kBK, kEpi, kAccIn>(p, stream);
       case 3:
-        if (deep) return launch_dma<128, 128, 32, 64, 64, 4, kAK, kBK, kEpi, kAccIn>(p, stream);  // 8 waves of 32 x 64
-        if (kind == 1) return launch_dma<128, 128, 64, 64, 32, 4, kAK, kBK, kEpi, kAccIn>(p, stream);
-        return launch_dma<128, 128, 64, 64, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);
+        if (deep) return launch_w4_128<4, kAK, kBK, kEpi, kAccIn>(p, stream);
+        return launch_w4_128<2, kAK, kBK, kEpi, kAccIn>(p, stream);
       case 4:
         if constexpr (kind == 1) return launch_four_wave<7, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
         break;
