@@ -17,6 +17,7 @@
 // 314 -> 32 us, 4.2 TB/s; 33 tokens 8192 -> 32768 (512 MiB) 641 -> 99 us, 5.4 TB/s, where a plain copy moves 4.9 TB/s.
 #pragma once
 #include "gemm_dma.h"
+#include "gemm_w4.h"
 
 namespace osdp {
 namespace {
@@ -171,9 +172,9 @@ struct SkinnyOperand {
   }
 };
 
-template <int BM, int BN, int BK, int kStages, bool kBKc>
-__global__ __launch_bounds__(kSkinnyWaves * 64, 1)
-void gemm_skinny_kernel(SkinnyParams p) {
+// block(): which workgroup of the product this is (asked for where it is used: in front of everything else it costs 0.3 us).
+template <int BM, int BN, int BK, int kStages, bool kBKc, class Block>
+__device__ __forceinline__ void skinny_tile(const SkinnyParams &p, Block &&block) {
   constexpr int MB = BM / 16, NB = BN / 16, KS = BK / 32;
   using OpA = SkinnyOperand<true, BM, BK>;
   using OpB = SkinnyOperand<kBKc, BN, BK>;
@@ -194,7 +195,7 @@ void gemm_skinny_kernel(SkinnyParams p) {
     }
     __syncthreads();
   }
-  const int id = logical_block(), tn = __builtin_amdgcn_readfirstlane(id / p.tiles_m);
+  const int id = block(), tn = __builtin_amdgcn_readfirstlane(id / p.tiles_m);
   const int n0 = tn * BN, m0 = (id - tn * p.tiles_m) * BM;
   const int m_left = p.M - m0 < BM ? p.M - m0 : BM;
 
@@ -343,6 +344,23 @@ void gemm_skinny_kernel(SkinnyParams p) {
     }
     store_global8(p.C + static_cast<int64_t>(m0 + m) * p.ldc + n0 + n, uint2{pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])});
   }
+}
+
+template <int BM, int BN, int BK, int kStages, bool kBKc>
+__global__ __launch_bounds__(kSkinnyWaves * 64, 1)
+void gemm_skinny_kernel(SkinnyParams p) {
+  skinny_tile<BM, BN, BK, kStages, kBKc>(p, [] { return logical_block(); });
+}
+
+// The backward of few tokens as one launch: workgroups [0, n_dx) are those of dX, the others 128 x 128 tiles of dW into the
+// shards.  Neither needs the other, both are short, and a launch of its own is what the second one costs most (128 tokens
+// 256 -> 1024: dW 6.0 and dX 6.5 us, and 3 to 4 us of host time each).
+template <int BM, int BK, int kStages>
+__global__ __launch_bounds__(kSkinnyWaves * 64, 1)
+void few_token_backward_kernel(SkinnyParams dx, GemmParams dw, int n_dx, int tiles_m, int tiles_n) {
+  const int id = blockIdx.x;
+  if (id < n_dx) skinny_tile<BM, 64, BK, kStages, true>(dx, [&] { return id; });
+  else gemm_w4_tile<4, 4, 4, false, false, static_cast<int>(Epilogue::kBf16ShardMajor), false, false>(dw, tiles_m, tiles_n, id - n_dx);
 }
 
 }  // namespace

@@ -124,7 +124,7 @@ constexpr bool w4_all_placed(int MB, int NB, int L) {
 // is bound by the memory pipe the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a
 // launch of its own); it saves the launch, its gap and every cross-stream event.
 template <int MB, int NB, int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy>
-__device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, int tiles_n, int pid) {
   constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
   using OpA = W4Operand<kAK, MB>;
   using OpB = W4Operand<kBKc, NB>;
@@ -191,7 +191,6 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
   // A launch split along K: the logical ids of one part are consecutive (so an XCD's tiles still share panels),
   // each part runs its own range of k and stores its own fp32 plane.
   int tm, tn;
-  int pid = logical_block();
   int K = p.K;
   int64_t k0 = 0;    // first k of this workgroup's part
   int plane_row = 0;  // its plane starts at this row of C (the planes lie one below the other: ldc = N)
@@ -327,14 +326,14 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
 template <bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  gemm_w4_tile<8, 8, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+  gemm_w4_tile<8, 8, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n, logical_block());
 }
 
 // Tiles of fewer than 256 rows or columns: 32 * MB x 32 * NB.
 template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy = false>
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  gemm_w4_tile<MB, NB, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n);
+  gemm_w4_tile<MB, NB, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n, logical_block());
 }
 
 // Tiles of 128 x 128, two workgroups to a CU with two slots each, or one with four (launches of at most one tile per CU).
@@ -347,7 +346,7 @@ void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
 template <int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn>
 __global__ __launch_bounds__(256, kSlots == 2 ? 2 : 1)
 void gemm_w4_128_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  gemm_w4_tile<4, 4, kSlots, kAK, kBKc, kEpi, kAccIn, false>(p, tiles_m, tiles_n);
+  gemm_w4_tile<4, 4, kSlots, kAK, kBKc, kEpi, kAccIn, false>(p, tiles_m, tiles_n, logical_block());
 }
 
 }  // namespace

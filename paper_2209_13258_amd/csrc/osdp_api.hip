@@ -1205,6 +1205,15 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
   if (skinny || (in_place && (!r.any_dp || !runs.empty()))) {
     const double T = r.T, I = r.I, O = r.O;
     if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});
+    if (skinny && !r.any_dp) {
+      const GemmProblem gw = dw_gemm(r, 0, static_cast<int>(r.sub.size()), X, ldx, dY, lddy, gtab, rep);
+      if (few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
+        OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 4.0 * T * I * O, 2.0 * (T * O + I * O + T * I) + 2.0 * (T * I + T * O + I * O), sc, [&] {
+          return launch_few_token_backward(gw, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc);
+        }));
+        return OSDP_OK;
+      }
+    }
     for (const Slice &l : r.dw)
       OSDP_HIP(do_gemm(OSDP_KERNEL_GEMM_DW, dw_gemm(r, static_cast<int>(l.c0), static_cast<int>(l.c1), X, ldx, dY, lddy, gtab, rep), sc));
     if (skinny)

@@ -665,7 +665,7 @@ hipError_t check_device() {
 }
 
 namespace {
-hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) {
+GemmParams gemm_params(const GemmProblem &q) {
   GemmParams p{};
   p.M = q.M; p.N = q.N; p.K = q.K;
   p.A = static_cast<const uint16_t *>(q.A); p.lda = q.lda;
@@ -676,6 +676,11 @@ hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) 
   p.B2 = static_cast<const uint16_t *>(q.B2); p.ldb2 = q.ldb2;
   p.k_split = q.B2 ? q.k_split : 0; p.n_split = q.B2 ? q.n_split : 0;
   p.seg_k = q.b_kcontig ? 0 : q.b_shard_rows; p.seg_n = q.b_kcontig ? q.b_shard_rows : 0;
+  return p;
+}
+
+hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) {
+  GemmParams p = gemm_params(q);
   if (q.b_shard_rows && (!q.a_kcontig || q.acc_in || p.k_split || p.n_split || p.seg_k % 64)) return hipErrorInvalidValue;
   if (*carry) {
     const GatherRequest &g = *q.carry;
@@ -711,6 +716,13 @@ hipError_t dispatch_gemm(const GemmProblem &q, hipStream_t stream, bool *carry) 
 }  // namespace
 
 namespace {
+// Whether some K block lies in more than one array: whole ones lie in one shard where shards are row blocks that the blocks
+// (dX: the tiles) divide.
+template <int BN, int BK, bool kBKc>
+bool skinny_by_lane(const WeightMap &w) {
+  return w.dp_mask != 0 || w.lay.rows_per_shard == 0 || w.lay.rows_per_shard % (kBKc ? BN : BK) != 0;
+}
+
 template <int BM, int BN, int BK, int kStages, bool kBKc>
 hipError_t launch_skinny_as(SkinnyParams p, hipStream_t stream) {
   constexpr size_t lds = static_cast<size_t>(kSkinnyWaves) * kStages * (BM + BN) * BK * sizeof(uint16_t);
@@ -720,8 +732,7 @@ hipError_t launch_skinny_as(SkinnyParams p, hipStream_t stream) {
   const hipError_t e = allow_lds(kernel, lds, configured);
   if (e != hipSuccess) return e;
   p.tiles_m = (p.M + BM - 1) / BM;
-  // whole K blocks lie in one shard where shards are row blocks that the blocks (dX: the tiles) divide
-  p.by_lane = p.w.dp_mask != 0 || p.w.lay.rows_per_shard == 0 || p.w.lay.rows_per_shard % (kBKc ? BN : BK) != 0;
+  p.by_lane = skinny_by_lane<BN, BK, kBKc>(p.w);
   hipLaunchKernelGGL(kernel, dim3(p.tiles_m * ((p.N + BN - 1) / BN)), dim3(kSkinnyWaves * 64), lds, stream, p);
   return hipGetLastError();
 }
@@ -741,12 +752,12 @@ bool skinny_takes(bool dx, int64_t T, int64_t ld_act, const ShardLayout &lay, in
 // as its fullest CU: all tokens in one tile when the columns alone occupy the CUs (the weights are then read once),
 // smaller tiles, which read them again from the L2, when that leaves CUs idle (128 tokens 256 -> 1024: forward 10.0 us
 // in 16 tiles of 128 rows, 5.7 us in 128 tiles of 16; dX 15.5 against 5.0 us).
-int skinny_rows(int64_t T, int64_t N) {
+int skinny_rows(int64_t T, int64_t N, int cus = kCUs) {
   int best = 0;
   int64_t best_cost = 0;
   for (int bm : {16, 32, 48, 64, 128}) {
     const int64_t tiles = ((T + bm - 1) / bm) * ((N + 63) / 64);
-    const int64_t cost = (tiles + kCUs - 1) / kCUs * (bm + 64);
+    const int64_t cost = (tiles + cus - 1) / cus * (bm + 64);
     if (best == 0 || cost < best_cost) {
       best = bm;
       best_cost = cost;
@@ -755,9 +766,8 @@ int skinny_rows(int64_t T, int64_t N) {
   return best;
 }
 
-// As many LDS stages as fit; 128 columns to a workgroup where that still gives every CU one, else 64.
-hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
-                         hipStream_t stream) {
+namespace {
+SkinnyParams skinny_params(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out) {
   SkinnyParams p{};
   p.M = static_cast<int32_t>(T);
   p.N = static_cast<int32_t>(dx ? w.I : w.lay.O);
@@ -765,6 +775,14 @@ hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act
   p.A = static_cast<const uint16_t *>(act); p.lda = ld_act;
   p.C = static_cast<uint16_t *>(out); p.ldc = ld_out;
   p.w = w;
+  return p;
+}
+}  // namespace
+
+// As many LDS stages as fit; 128 columns to a workgroup where that still gives every CU one, else 64.
+hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
+                         hipStream_t stream) {
+  const SkinnyParams p = skinny_params(dx, w, T, act, ld_act, out, ld_out);
   const int bm = skinny_rows(T, p.N);
   if (dx) {
     if (bm == 16) return launch_skinny_as<16, 64, 64, 3, true>(p, stream);
@@ -783,6 +801,59 @@ hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act
   if (bm == 48) return launch_skinny_as<48, 64, 32, 5, false>(p, stream);
   if (bm == 64) return launch_skinny_as<64, 64, 32, 4, false>(p, stream);
   return launch_skinny_as<128, 64, 32, 3, false>(p, stream);
+}
+
+namespace {
+template <int BM, int BK, int kStages>
+hipError_t launch_backward_as(SkinnyParams dx, const GemmParams &dw, hipStream_t stream) {
+  constexpr size_t lds_dx = static_cast<size_t>(kSkinnyWaves) * kStages * (BM + 64) * BK * sizeof(uint16_t);
+  constexpr size_t lds_dw = 4 * (W4Operand<false, 4>::kElems + W4Operand<false, 4>::kElems) * sizeof(uint16_t);
+  constexpr size_t lds = lds_dx > lds_dw ? lds_dx : lds_dw;
+  static_assert(lds + 3 * OSDP_MAX_SHARDS * 8 <= 160 * 1024, "the rings do not fit the 160 KB of LDS");
+  auto kernel = few_token_backward_kernel<BM, BK, kStages>;
+  static bool configured[kMaxDevices] = {};
+  const hipError_t e = allow_lds(kernel, lds, configured);
+  if (e != hipSuccess) return e;
+  dx.tiles_m = (dx.M + BM - 1) / BM;
+  dx.by_lane = skinny_by_lane<64, BK, true>(dx.w);
+  const int n_dx = dx.tiles_m * ((dx.N + 63) / 64), tiles_m = (dw.M + 127) / 128, tiles_n = (dw.N + 127) / 128;
+  hipLaunchKernelGGL(kernel, dim3(n_dx + tiles_m * tiles_n), dim3(256), lds, stream, dx, dw, n_dx, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+}  // namespace
+
+namespace {
+// Rows of a workgroup's tile of dX beside n_dw tiles of dW: for the CUs that these leave, or the quarter of them that is
+// done with its tile of dW first.
+int beside_rows(int64_t T, int64_t N, int64_t n_dw) { return skinny_rows(T, N, static_cast<int>(std::max<int64_t>(kCUs - n_dw, kCUs / 4))); }
+}  // namespace
+
+// us, two launches / one: 128 tokens 256 -> 1024 10.7 / 5.8, 1536 -> 1536 12.3 / 8.6, 2048 -> 2048 13.9 / 12.4, 512 -> 8192
+// 24.7 / 19.5, 16 tokens 1024 -> 4096 16.5 / 11.9.  Where they make more than one round together and all tokens are in one
+// tile of dX, that tile, the longest, starts the round of the others late: 96 and 128 tokens 4096 -> 1024 13.1 / 15.7.
+bool few_token_backward_takes(const GemmProblem &dw, int64_t T) {
+  const DebugOptions &d = debug_options();
+  const GemmParams p = gemm_params(dw);
+  int axis = -1, cut = 0;
+  if (dw.epilogue != Epilogue::kBf16ShardMajor || !fast_path(p.K, 0, 0) || !fits_offsets(p) || tile_count(p.M, p.N, 128, 128) > kCUs ||
+      d.deep.load(std::memory_order_relaxed) == 0 || d.small_tile.load(std::memory_order_relaxed) == 1 ||
+      best_tile(p.M, p.N, p.K, 0, 1, nullptr) != 3)
+    return false;
+  plan_launches(p.M, p.N, p.K, 1, &axis, &cut);
+  if (axis >= 0) return false;
+  const int64_t n_dw = tile_count(p.M, p.N, 128, 128), bm = beside_rows(T, p.M, n_dw);
+  return bm <= 64 || n_dw + (T + bm - 1) / bm * ((p.M + 63) / 64) <= kCUs;
+}
+
+hipError_t launch_few_token_backward(const GemmProblem &dw, const WeightMap &w, int64_t T, const void *dY, int64_t lddy, void *dX,
+                                     int64_t lddx, hipStream_t stream) {
+  const SkinnyParams p = skinny_params(true, w, T, dY, lddy, dX, lddx);
+  const GemmParams g = gemm_params(dw);
+  const int bm = beside_rows(T, p.N, tile_count(g.M, g.N, 128, 128));
+  if (bm == 16) return launch_backward_as<16, 64, 3>(p, g, stream);
+  if (bm == 32) return launch_backward_as<32, 64, 3>(p, g, stream);
+  if (bm <= 64) return launch_backward_as<64, 64, 2>(p, g, stream);
+  return launch_backward_as<128, 32, 3>(p, g, stream);
 }
 
 hipError_t launch_gemm(const GemmProblem &q, hipStream_t stream) {

@@ -120,6 +120,12 @@ bool skinny_takes(bool dx, int64_t T, int64_t ld_act, const ShardLayout &lay, in
 hipError_t launch_skinny(bool dx, const WeightMap &w, int64_t T, const void *act, int64_t ld_act, void *out, int64_t ld_out,
                          hipStream_t stream);
 
+// dX of few tokens (skinny_takes) and dW of the whole matrix into the shards as one launch; takes: whether dW is the small
+// product that this is meant for (at most one 128 x 128 tile per CU) and the two fit beside each other.
+bool few_token_backward_takes(const GemmProblem &dw, int64_t T);
+hipError_t launch_few_token_backward(const GemmProblem &dw, const WeightMap &w, int64_t T, const void *dY, int64_t lddy, void *dX,
+                                     int64_t lddx, hipStream_t stream);
+
 // Whether a product of T tokens with the whole weight may read it from the shards (GemmProblem::b_shard_rows).
 // Up to four rows of 128-row tiles: the workgroups an XCD runs together walk the rows of a panel of weight columns
 // together (kGroupM in gemm_common.h), so that each weight still crosses from memory into one L2 once, and a staged copy

@@ -926,6 +926,37 @@ def test_few_tokens_read_the_weights_in_place(H, oracle, T, I, O, N, k):
     assert (H.to_bits(op.dW[-1])[I * O - (N - 1) * L:] == POISON).all()
 
 
+@pytest.mark.parametrize("I,O,N,one", [(64, 128, 1, True), (256, 1024, 2, True), (264, 520, 60, True),   # shards that end inside rows
+                                       (2048, 2048, 8, True),     # dW alone fills the CUs
+                                       (4096, 1024, 8, False)])   # from 65 tokens on too long beside it
+def test_few_tokens_run_the_backward_in_one_launch(H, oracle, I, O, N, one, debug):
+    """dX and dW of few tokens share a launch where both are small: the bits of the two launches (which the switch for the
+    shallow pipelines asks for), the oracle's values, nothing beside them written, for every tile of dX."""
+    import paper_2209_13258_amd as osdp
+    for T in (1, 16, 31, 64, 65, 128):
+        d = wl.small_case(77, T, I, O, N)
+        got = {}
+        for deep in (0, -1):
+            debug("deep", deep)
+            _announce("backward of few tokens", T, I, O, N, "deep", deep)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            k = 2 if O % 16 == 0 else 1
+            op.workspace(k, True)
+            torch.cuda.synchronize()
+            osdp.osdp_profile_begin(100)
+            op.bwd(k)
+            st = osdp.osdp_profile_end()
+            got[deep] = [H.to_bits(op.dX), np.concatenate([H.to_bits(s) for s in op.dW])]
+            assert st["gemm_dx"]["launches"] == 1 and (st["gemm_dw"]["launches"] == 0) == (deep == -1 and (one or T <= 64))
+        for a, b in zip(got[0], got[-1]):
+            assert np.array_equal(a, b)
+        assert (got[-1][1][I * O:] == POISON).all()
+        if I * O <= 1 << 19:
+            want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+            H.assert_close("dX", got[-1][0], want["dX"])
+            H.assert_close("dW", got[-1][1][: I * O].reshape(I, O), want["dW"])
+
+
 @pytest.mark.parametrize("I,O", [(520, 1056),      # 33 K blocks of 32: the waves' ranges depend on how they are cut
                                  (1096, 16360)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
 def test_few_tokens_sum_in_an_order_that_the_reduction_length_alone_decides(H, I, O):
