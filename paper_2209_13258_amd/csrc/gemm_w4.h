@@ -98,11 +98,12 @@ constexpr int w4_read_behind(int i, int MB, int NB) {
   return i % step == first % step && i / step < MB + NB ? i / step : -1;
 }
 
-// Load l of the L per block goes out behind MFMA (l * N) / L + 2 (+ 1 where they are as close as that) of the N in a K step;
-// l, or -1, for a given MFMA.
+// Load l of the L per block goes out behind MFMA (l * N) / L + 2 of the N in a K step (or + 1 or 0, so that the last one has a
+// place too); l, or -1, for a given MFMA.
 constexpr int w4_load_behind(int i, int N, int L) {
+  const int room = N - 1 - (L - 1) * N / L, late = room < 2 ? room : 2;
   for (int l = 0; l < L; ++l)
-    if (l * N / L + (N >= 3 * L || (L - 1) * N / L + 2 < N ? 2 : 1) == i) return l;
+    if (l * N / L + late == i) return l;
   return -1;
 }
 // Every read and every load has its place.
@@ -334,6 +335,13 @@ template <int MB, int NB, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
   gemm_w4_tile<MB, NB, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n, logical_block());
+}
+
+// Tiles of 160 columns for launches of at most one tile per CU (forward, dX), with as many slots as fit.
+template <int MB, int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn>
+__global__ __launch_bounds__(256, 1)
+void gemm_w4_160_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  gemm_w4_tile<MB, 5, kSlots, kAK, kBKc, kEpi, kAccIn, false>(p, tiles_m, tiles_n, logical_block());
 }
 
 // Tiles of 128 x 128, two workgroups to a CU with two slots each, or one with four (launches of at most one tile per CU).

@@ -231,6 +231,22 @@ hipError_t launch_w4_128(const GemmParams &p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The same with 160 columns and 128 or 64 rows.
+template <int MB, bool kAK, bool kBK, int kEpi, bool kAccIn>
+hipError_t launch_w4_160(const GemmParams &p, hipStream_t stream) {
+  constexpr size_t slot = (W4Operand<kAK, MB>::kElems + W4Operand<kBK, 5>::kElems) * sizeof(uint16_t);
+  constexpr int kSlots = 5 * slot <= 160 * 1024 ? 5 : (4 * slot <= 160 * 1024 ? 4 : 3);
+  static_assert(kSlots * slot <= 160 * 1024 && kEpi != static_cast<int>(Epilogue::kBf16ShardMajor), "tile does not fit the 160 KB of LDS");
+  auto kernel = gemm_w4_160_kernel<MB, kSlots, kAK, kBK, kEpi, kAccIn>;
+  static bool configured[kMaxDevices] = {};
+  hipError_t e = allow_lds(kernel, kSlots * slot, configured);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (p.M + 32 * MB - 1) / (32 * MB), tiles_n = tile_columns_of(p, 160);
+  const int parts = p.k_parts > 1 ? p.k_parts : 1;
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n * parts), dim3(256), kSlots * slot, stream, p, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
 // Adds up the fp32 planes of a launch that was split along K, plane 0 first, and stores the sum through the
 // launch's own epilogue.  One thread per 4 consecutive columns.
 template <int kEpi>
@@ -339,7 +355,13 @@ struct TileShape {
 // tiles of 256 rows 412 us, 240 of 224 rows 382 us.  8192 x 1280 over K = 2560: 160 tiles of 256 columns 60 us, 256
 // tiles of 160 columns 51 us (dX 48 us); where they only replace full rounds the narrow tiles lose (16384 x 2560 over
 // K = 2560 in 4 rounds 240 us, against 196 us for two rounds of large tiles and a remainder).
-constexpr int kTileShapes = 6;
+// The last two are for dX launches of at most one tile per CU: narrow slices, and few rows.  Both operands keep whole rows of
+// K blocks in LDS, so any number of rows and columns fits.  us in 128 x 128 tiles / in these: 8192 x 320 over K = 10240 71 / 64,
+// 1000 x 5120 over 2560 38 / 29, 2048 x 1280 over 4096 31 / 28, 4096 x 128 over 2048 17 / 15.  (The forward, whose weight
+// tile takes 256 columns of LDS for 160, loses: 8192 x 320 over 10240 86 / 95.)
+// 256 x 160 over K = 768 and 1024, one tile to a CU, against two tiles of 128 x 128 or fewer of 256 x 256: dX of 4096 x 2304 30 / 24,
+// 4096 x 2560 25 / 21, 8192 x 1280 31 / 25.
+constexpr int kTileShapes = 8, kPricedShapes = 6;
 // lone: K = 2560 to 10240 against 256 x 256 tiles of the same K, one to a CU.  In place of two 128 x 128 tiles a CU, one
 // of 256 x 128 took 2048 x 4096 over K = 4096 from 76 to 65 us (dX 69 to 64), 3001 x 2560 over K = 2560 from 52 to 45.
 constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}, {1.0, 1.0, 1.0}},
@@ -347,16 +369,19 @@ constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}, {1.0, 1.0
                                            {128, 256, {1.21, 1.23, 1.37}, {1.21, 1.20, 1.22}},
                                            {128, 128, {1.39, 1.20, 1.40}, {1.60, 1.55, 1.60}},
                                            {224, 256, {0.0, 1.06, 0.0}, {0.0, 1.06, 0.0}},
-                                           {256, 160, {1.30, 0.0, 1.28}, {1.30, 0.0, 1.28}}};
-constexpr int kNarrowMinK = 2048;
+                                           {256, 160, {1.30, 0.0, 1.28}, {1.30, 0.0, 1.28}},
+                                           {128, 160, {0.0, 0.0, 0.0}, {0.0, 0.0, 1.35}},
+                                           {64, 160, {0.0, 0.0, 0.0}, {0.0, 0.0, 1.70}}};
+constexpr int kNarrowMinK = 768, kNarrowPricedK = 2048;
 
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
 
 // Whether tile shape i serves a launch of the layout with K as the reduction of a workgroup: the four-wave kernel's own
 // shapes from a K loop that pays for its start-up.
-bool tile_offered(int i, int kind, int K) {
+bool tile_offered(int i, int kind, int K, int narrow_k = kNarrowMinK) {
   if (i < 4) return true;
-  return kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinK : kNarrowMinK) &&
+  if (i >= kPricedShapes) return kTiles[i].lone[kind] > 0.0 && debug_options().small_tile.load(std::memory_order_relaxed) != 0;
+  return kTiles[i].penalty[kind] > 0.0 && K >= (kind == 1 ? kW4MinK : narrow_k) &&
          debug_options().four_wave.load(std::memory_order_relaxed) != 0 &&
          debug_options().small_tile.load(std::memory_order_relaxed) != 0;
 }
@@ -364,14 +389,15 @@ bool tile_offered(int i, int kind, int K) {
 // Cheapest tile for M x N; a column split must fall on a tile boundary.
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
-int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, bool acc_in = false) {
+int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, bool acc_in = false, int shapes = kTileShapes) {
   // (a lone tile that starts from a sum in memory has only its first K blocks to cover that load with: 2048 x 4096 over K =
   // 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
   const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
   int best = -1;
   double best_cost = 0.0;
-  for (int i = 0; i < kTileShapes; ++i) {
-    if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts)) continue;
+  for (int i = 0; i < shapes; ++i) {
+    if (i >= kPricedShapes && (!lone || tile_count(M, N, kTiles[i].bm, kTiles[i].bn) * parts > kCUs)) continue;  // lone tiles only
+    if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts, shapes == kPricedShapes ? kNarrowPricedK : kNarrowMinK)) continue;
     const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0);
     if (best < 0 || c < best_cost) {
       best = i;
@@ -434,7 +460,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   constexpr int kind = layout_kind(kAK, kBK);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
   if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
-    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts, kAccIn);
+    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts, kAccIn, p.seg_n ? kPricedShapes : kTileShapes);
     const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 where it fits the segments of B
     bool force = forced >= 0 && forced <= 3;
     if (force && p.n_split % kTiles[forced].bn == 0) best = forced;
@@ -479,6 +505,12 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
         break;
       case 5:
         if constexpr (kind != 1) return launch_four_wave<8, 5, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
+        break;
+      case 6:
+        if constexpr (kind == 2 && !kAccIn) return launch_w4_160<4, kAK, kBK, kEpi, kAccIn>(p, stream);
+        break;
+      case 7:
+        if constexpr (kind == 2 && !kAccIn) return launch_w4_160<2, kAK, kBK, kEpi, kAccIn>(p, stream);
         break;
     }
   }
@@ -620,10 +652,11 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   // forward launch grouping of config 3 slightly worse)
   double cost = 0.0;
   if (M > 0 && fast_path(static_cast<int>(K), 0, 0)) {
-    best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost);
+    // (how slices are paired decides how much workspace a call asks for: it goes by the shapes that sizes were first given for)
+    best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, 1, false, kPricedShapes);
     const int parts = forward_parts ? forward_k_parts(M, K) : 1;
     if (parts > 1) {
-      best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, parts);
+      best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, parts, false, kPricedShapes);
       return cost / parts * 2.0 * static_cast<double>(K) / 5.0e6 + combine_estimate_us(M, N, parts) + 6.0;
     }
     return cost * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;

@@ -1251,6 +1251,33 @@ def test_four_wave_tiles_of_224_rows_and_of_160_columns(H, oracle, T, I, O, N, k
 
 
 # ------------------------------------------------ the persistent form of the four-wave kernel
+@pytest.mark.parametrize("T,I,O,N,k", [
+    (577, 160, 72, 1, 1),      # one tile column, K = 72: a K block and 8 left over; a row beyond nine tiles of 64
+    (640, 1288, 200, 4, 2),    # eight columns beyond the eighth tile; row slices of 644 are not multiples of 8: column slices only
+    (1100, 5120, 520, 8, 4),   # 18 x 32 tiles of 64 rows are too many: tiles of 128 rows
+    (1000, 336, 1600, 2, 3),   # row slices of 112 columns
+])
+def test_dx_tiles_of_160_columns_keep_the_bits_of_the_checked_kernel(H, oracle, T, I, O, N, k, debug):
+    """dX launches of at most one tile per CU, of 64 or 128 rows and 160 columns: for the unsplit operator and for slices of
+    either kind, the bits of the checked kernel and of 128 x 128 tiles, and the oracle's values."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(79, T, I, O, N)
+    want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"], want=("dX",))
+    cuts = [(kk, dim) for kk in (1, k) for dim in (0, 1) if (I if dim else O) % (8 * kk) == 0]
+    ref = {}
+    for switches in ({"gemm_generic": 1}, {"tile": 3}, {"split_launch": 0}, {}):
+        for name, value in {**DEBUG_DEFAULTS, **switches}.items():
+            debug(name, value)
+        for kk, dim in cuts:
+            _announce("dX in tiles of 160 columns", T, I, O, N, kk, dim, switches)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            op.bwd(kk, plan=osdp.Plan([kk], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[dim]))
+            torch.cuda.synchronize()
+            got = H.to_bits(op.dX)
+            H.assert_close("dX", got, want["dX"])
+            assert np.array_equal(got, ref.setdefault(1, got)), (switches, kk, dim)
+
+
 @pytest.mark.parametrize("dim", [0, 1])
 def test_persistent_kernel_keeps_the_bits_of_one_tile_per_workgroup(H, oracle, debug, dim):
     """A launch of more 256 x 256 tiles than CUs runs as one workgroup per CU that walks through the tiles, the loads

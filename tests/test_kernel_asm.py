@@ -118,15 +118,17 @@ def test_four_wave_kernels_of_smaller_tiles_keep_the_same_rules(gemm_asm):
             _assert_no_valu_write_in_front_of_its_mfma(name, ins, mfma)
 
 
-def test_four_wave_kernels_of_128_x_128_tiles_keep_the_same_rules(gemm_asm):
-    """One K block of 2 x 16 MFMAs and 8 fragment reads of either operand; every load of a block has its place."""
-    kernels = _kernels(gemm_asm, "gemm_w4_128_kernel")
-    assert len(kernels) >= 20, "the instantiations were not found in the assembly"
+@pytest.mark.parametrize("kernel,least", [("gemm_w4_128_kernel", 20), ("gemm_w4_160_kernel", 4)])
+def test_four_wave_kernels_of_lone_tiles_keep_the_same_rules(gemm_asm, kernel, least):
+    """32 * MB x 32 * NB tiles: one K block of 2 * MB * NB MFMAs, and every load of a block has its place."""
+    kernels = _kernels(gemm_asm, kernel)
+    assert len(kernels) >= least, "the instantiations were not found in the assembly"
     for name, ins in kernels.items():
+        mb, nb = (4, 4) if "128" in kernel else (int(re.search(kernel + r"ILi(\d+)E", name).group(1)), 5)
         mfma = [i for i, t in enumerate(ins) if t.startswith("v_mfma")]
-        assert len(mfma) == 32, f"{name}: {len(mfma)} MFMAs"
+        assert len(mfma) == 2 * mb * nb, f"{name}: {len(mfma)} MFMAs"
         loads = [t for t in ins[mfma[0]:] if t.startswith("buffer_load") and t.endswith(" lds")]
-        assert len(loads) == 8, f"{name}: {len(loads)} loads in a K block"
+        assert len(loads) == mb + nb, f"{name}: {len(loads)} loads in a K block"
         assert not [t for t in ins if t.startswith("scratch_")], f"{name}: scratch traffic"
         for i in mfma:
             assert not [t for t in ins[max(0, i - 3):i] if t.startswith(("v_accvgpr_write", "v_accvgpr_mov"))], \
