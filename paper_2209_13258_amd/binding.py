@@ -172,11 +172,7 @@ class Plan:
         mask = (ctypes.c_uint64 * n)(*self.zdp_mask) if self.zdp_mask is not None else None
         dims = (ctypes.c_uint8 * n)(*self.split_dim_per_op) if self.split_dim_per_op is not None else None
         modes = (ctypes.c_int32 * n)(*self.staging_per_op) if self.staging_per_op is not None else None
-        p = osdp_plan(n, ctypes.cast(ks, ctypes.POINTER(ctypes.c_int32)),
-                      ctypes.cast(mask, ctypes.POINTER(ctypes.c_uint64)) if mask is not None else None,
-                      self.staging,
-                      ctypes.cast(dims, ctypes.POINTER(ctypes.c_uint8)) if dims is not None else None,
-                      ctypes.cast(modes, ctypes.POINTER(ctypes.c_int32)) if modes is not None else None)
+        p = osdp_plan(n, ks, mask, self.staging, dims, modes)  # (a pointer field takes an array as it is; a cast costs 0.7 us)
         return p, (ks, mask, dims, modes)  # keep the arrays alive with the struct
 
 
