@@ -414,14 +414,15 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
  *   "gemm_generic"   0 | 1   1: every GEMM runs on the bounds-checked kernel
  *   "tile"          -1 .. 3  force tile shape 256x256, 256x128, 128x256, 128x128 (in launches over two column ranges of
  *                            the weight: where it fits them)
- *   "small_tile"    -1 .. 1  0: the four-wave kernel runs 256x256 tiles only; 1: tiles of 224x256 (dW) and 256x160
+ *   "small_tile"    -1 .. 1  0: no tiles of 224 rows or 160 columns; 1: tiles of 224x256 (dW) and 256x160
  *                            (forward, dX) wherever they serve the launch
- *   "deep"          -1 | 0   0: launches of at most one tile per CU keep the shallow LDS pipelines
+ *   "deep"          -1 | 0   0: launches of at most one tile per CU keep the shallow LDS pipelines and the tiles of
+ *                            other launches; few tokens run dX and dW as two launches
  *   "split_launch"  -1 | 0   0: no launch is cut into whole rounds of large tiles + remainder
  *   "split_k"       -1 | 0   0: forward products are never summed in parts of the reduction (this
  *                            changes the bits of the products that are otherwise summed in parts)
  *   "four_wave"     -1 .. 1  0: 256x256 tiles always run on the eight-wave kernel; 1: on the four-wave kernel
- *                            whenever it takes the launch (K > 128), also where the eight-wave one measured faster
+ *                            whenever it takes the launch (K > 128), as they do by themselves
  *   "persistent"    -1 .. 1  0: a launch of more 256x256 tiles than CUs keeps the four-wave kernel of one tile per
  *                            workgroup; otherwise one workgroup per CU walks through the tiles; 1: the walking
  *                            form also for launches of fewer tiles

@@ -1,4 +1,4 @@
-// Main GEMM kernel of libosdp: tiles stream from global memory straight into LDS
+// Eight-wave GEMM kernel of libosdp, and the operand layouts that the others share: tiles stream from global memory straight into LDS
 // (global_load_lds_dwordx4, no staging registers), a ring of LDS stages keeps one or more K
 // blocks in flight behind the MFMAs (v_mfma_f32_16x16x32_bf16), and operand fragments are
 // double-buffered in registers.

@@ -484,7 +484,7 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
     switch (best) {
       case 0:
         // (256 x 256 tiles of the eight-wave kernel are left where the four-wave kernel's loop does not fit.  dW ran on them
-        // below 8192 tokens as long as the four-wave epilogue into shards took 25 us a tile; now, eight / four waves, 8192 x
+        // below 8192 tokens as long as the four-wave epilogue into shards took 32 us a tile and not 15; now, eight / four waves, 8192 x
         // 8192 over 4096 / 1024 / 256 tokens 417 / 378, 133 / 117, 59 / 50 us; 2560 x 10240 over 3001 and 1500 160 / 130, 83 / 74)
         if (p.K / parts >= kW4MinK && fw != 0) {
           return launch_four_wave<8, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
