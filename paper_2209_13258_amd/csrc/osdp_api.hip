@@ -1207,7 +1207,11 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
     if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});
     if (skinny && !r.any_dp) {
       const GemmProblem gw = dw_gemm(r, 0, static_cast<int>(r.sub.size()), X, ldx, dY, lddy, gtab, rep);
-      if (few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
+      // (one after the other, dX may take the place of X, which dW has read by then)
+      const uintptr_t x0 = reinterpret_cast<uintptr_t>(X), x1 = x0 + 2 * static_cast<uintptr_t>((r.T - 1) * ldx + r.I);
+      const uintptr_t d0 = reinterpret_cast<uintptr_t>(dX), d1 = d0 + 2 * static_cast<uintptr_t>((r.T - 1) * lddx + r.I);
+      const bool apart = x1 <= d0 || d1 <= x0;
+      if (apart && few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
         OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 4.0 * T * I * O, 2.0 * (T * O + I * O + T * I) + 2.0 * (T * I + T * O + I * O), sc, [&] {
           return launch_few_token_backward(gw, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc);
         }));

@@ -950,6 +950,10 @@ def test_few_tokens_run_the_backward_in_one_launch(H, oracle, I, O, N, one, debu
             assert st["gemm_dx"]["launches"] == 1 and (st["gemm_dw"]["launches"] == 0) == (deep == -1 and (one or T <= 64))
         for a, b in zip(got[0], got[-1]):
             assert np.array_equal(a, b)
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)   # dX over X
+        op.dX = op.X
+        op.bwd(k)
+        assert np.array_equal(H.to_bits(op.X), got[0][0]) and np.array_equal(np.concatenate([H.to_bits(s) for s in op.dW]), got[0][1])
         assert (got[-1][1][I * O:] == POISON).all()
         if I * O <= 1 << 19:
             want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
