@@ -245,6 +245,9 @@ OSDP_API osdp_status osdp_split_linear_fwd_noalloc(const osdp_shape *shape, cons
  * between passes.
  *   dY : device [T x O], lddy >= O       dX : device [T x I], lddx >= I
  *   dw_shards : host array of N device pointers, each L elements
+ * dX may take the place of X (the same pointer and leading dimension), for any T; for T <= 128, I <= min(O, 64) and
+ * lddy < 2^22 that of dY instead, whose first I columns it then overwrites.  No other output may overlap an input,
+ * another output or the workspace.
  * With row slices: dW[r0_j:r1_j, :] = X[:, r0_j:r1_j]^T . dY and dX[:, r0_j:r1_j] = dY . Wr_j^T, no sum.
  * dW is bit-identical for every k and split dimension; dX is too when every slice width is a
  * multiple of 16 (row slices: always; with T <= 4096 and O >= 16384 their dX is summed in parts of 8192 output

@@ -1207,11 +1207,14 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
     if (!r.any_dp) r.dw.assign(1, Slice{0, static_cast<int64_t>(r.sub.size())});
     if (skinny && !r.any_dp) {
       const GemmProblem gw = dw_gemm(r, 0, static_cast<int>(r.sub.size()), X, ldx, dY, lddy, gtab, rep);
-      // (one after the other, dX may take the place of X, which dW has read by then)
-      const uintptr_t x0 = reinterpret_cast<uintptr_t>(X), x1 = x0 + 2 * static_cast<uintptr_t>((r.T - 1) * ldx + r.I);
-      const uintptr_t d0 = reinterpret_cast<uintptr_t>(dX), d1 = d0 + 2 * static_cast<uintptr_t>((r.T - 1) * lddx + r.I);
-      const bool apart = x1 <= d0 || d1 <= x0;
-      if (apart && few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
+      // (one after the other, dX may take the place of X, or of dY where one tile holds its columns: dW has read both by
+      // then; in one launch nothing orders dX's stores behind dW's loads)
+      auto clear_of_dx = [&](const void *p, int64_t ld, int64_t cols) {
+        const uintptr_t p0 = reinterpret_cast<uintptr_t>(p), p1 = p0 + 2 * static_cast<uintptr_t>((r.T - 1) * ld + cols);
+        const uintptr_t d0 = reinterpret_cast<uintptr_t>(dX), d1 = d0 + 2 * static_cast<uintptr_t>((r.T - 1) * lddx + r.I);
+        return p1 <= d0 || d1 <= p0;
+      };
+      if (clear_of_dx(X, ldx, r.I) && clear_of_dx(dY, lddy, r.O) && few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
         OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 4.0 * T * I * O, 2.0 * (T * O + I * O + T * I) + 2.0 * (T * I + T * O + I * O), sc, [&] {
           return launch_few_token_backward(gw, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc);
         }));

@@ -961,6 +961,56 @@ def test_few_tokens_run_the_backward_in_one_launch(H, oracle, I, O, N, one, debu
             H.assert_close("dW", got[-1][1][: I * O].reshape(I, O), want["dW"])
 
 
+@pytest.mark.parametrize("I,O,N", [(64, 128, 1), (64, 2048, 8), (40, 264, 33), (8, 64, 2)])
+def test_few_tokens_store_dx_in_the_place_of_dy(H, oracle, I, O, N):
+    """With at most 64 in-features a tile of dX reads all of its rows of dY before it stores them, and dW has read dY by then
+    where it is a launch of its own: dX may take dY's place, and may not share a launch with dW there."""
+    import paper_2209_13258_amd as osdp
+    for T in (1, 33, 128):
+        _announce("dX in the place of dY", T, I, O, N)
+        d = wl.small_case(81, T, I, O, N)
+        want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        op.bwd(1)
+        torch.cuda.synchronize()
+        ref = [H.to_bits(op.dX)] + [H.to_bits(s) for s in op.dW]
+        over = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        over.dX = over.dY[:, :I]
+        over.workspace(1, True)
+        osdp.osdp_profile_begin(100)
+        over.bwd(1)
+        st = osdp.osdp_profile_end()
+        assert (st["gemm_dw"]["launches"], st["gemm_dx"]["launches"]) == (1, 1)
+        for a, b in zip([H.to_bits(over.dX)] + [H.to_bits(s) for s in over.dW], ref):
+            assert np.array_equal(a, b)
+        assert np.array_equal(H.to_bits(over.dY)[:, I:], d["dY"][:, I:])   # the other columns stay
+        H.assert_close("dX", ref[0], want["dX"])
+        H.assert_close("dW", np.concatenate(ref[1:])[: I * O].reshape(I, O), want["dW"])
+
+
+@pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("T,I,O,N,k", [(96, 256, 512, 4, 2), (300, 256, 512, 4, 2),   # few tokens; shards in place
+                                       (300, 520, 264, 8, 1), (700, 384, 640, 8, 4),  # staged
+                                       (640, 512, 16384, 8, 4)])                      # row slices: dX in parts, added up behind dW
+def test_dx_in_the_place_of_x(H, T, I, O, N, k, rows):
+    """Every product that reads X runs before the one that stores its columns of dX: the same bits with dX over X."""
+    import paper_2209_13258_amd as osdp
+    d = wl.small_case(83, T, I, O, N)
+    for staging in ("SINGLE", "DOUBLE"):
+        plan = osdp.Plan([k], staging=getattr(osdp, f"OSDP_STAGING_{staging}"), split_dim_per_op=[int(rows)])
+        got = []
+        for over in (False, True):
+            _announce("dX over X", T, I, O, N, k, rows, staging, over)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            if over:
+                op.dX = op.X
+            op.bwd(k, plan=plan)
+            torch.cuda.synchronize()
+            got.append([H.to_bits(op.dX)] + [H.to_bits(s) for s in op.dW])
+        for a, b in zip(*got):
+            assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("I,O", [(520, 1056),      # 33 K blocks of 32: the waves' ranges depend on how they are cut
                                  (1096, 16360)])   # 128-row tiles, K blocks of 32: the same for their ranges of 35 K blocks
 def test_few_tokens_sum_in_an_order_that_the_reduction_length_alone_decides(H, I, O):
