@@ -119,11 +119,12 @@ constexpr bool w4_all_placed(int MB, int NB, int L) {
 // kCopy: the launch also carries p.job, the gather of a slice that a later launch will read (the forward GEMM of
 // slice j gathers slice j+1 into the other staging slot; a dW launch, which needs no weights, gathers the slices of
 // the dX pass that follows it).  Every workgroup copies total_vecs / gridDim.x vectors, 256 per K block: one 16-byte
-// load and one 16-byte store per lane and block, against that block's 16 KB of operand loads per wave.  A gather
-// kernel of its own cannot run beside this kernel, whose four waves hold every register of their SIMDs: on a second
-// stream it only takes turns with the tiles, and both get slower.  The carried copy is not free either (the kernel
-// is bound by the memory pipe the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a
-// launch of its own); it saves the launch, its gap and every cross-stream event.
+// load and one 16-byte store per lane and block, against that block's 16 KB of operand loads per wave.  The host sends
+// only copies that the K blocks hold (carry_fits): the kernel has no other place for them.  A gather kernel of its own
+// cannot run beside this kernel, whose four waves hold every register of their SIMDs: on a second stream it only takes
+// turns with the tiles, and both get slower.  The carried copy is not free either (the kernel is bound by the memory pipe
+// the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a launch of its own); it saves the
+// launch, its gap and every cross-stream event.
 template <int MB, int NB, int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn, bool kCopy>
 __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, int tiles_n, int pid) {
   constexpr int WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN;
@@ -308,15 +309,6 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
     fill = after(fill);
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
-  if constexpr (kCopy) {
-    // the piece still in registers, and whatever the K loop was too short for
-    if (copy_i < copy_pieces) store_global16(p.job.dst + copy_v, copy_data);
-    for (uint32_t i = copy_i + 1; i < copy_pieces; ++i) {
-      uint32_t v;
-      const uint4 *src = copy_src(i, &v);
-      store_global16(p.job.dst + v, load_global16(src));
-    }
-  }
 
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");

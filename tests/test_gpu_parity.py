@@ -1792,6 +1792,38 @@ def test_gathers_carried_by_gemm_launches_match_the_gather_kernel(H, oracle, T, 
                         assert np.array_equal(got[name], base[name]), f"{name} differs from the unsplit result"
 
 
+@pytest.mark.parametrize("fwd,T,I,O,N,carried", [
+    (False, 640, 4096, 4096, 8, 0),      # dW: 10 K blocks for 32 pieces
+    (False, 2048, 4096, 4096, 8, 1),     # 32 for 32
+    (False, 2056, 4080, 4096, 16, 1),    # 33; the last piece of the last workgroup ends early
+    (False, 2056, 4080, 4096, 64, 1),    # shards that end inside rows
+    (True, 1536, 512, 16384, 8, 0),      # forward: 8 blocks for 11
+    (True, 2048, 512, 16384, 8, 1),      # 8 for 8
+])
+def test_gemm_launches_take_along_the_gathers_that_their_k_blocks_hold(H, fwd, T, I, O, N, carried, debug):
+    """The bits of gathers as launches of their own; a copy that the K blocks of the launch cannot hold is one."""
+    import paper_2209_13258_amd as osdp
+    debug("fwd_pair", 0)
+    d = wl.small_case(143, T, I, O, N)
+    plan = osdp.Plan([2], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[0 if fwd else 1])
+    got = {}
+    for fused in (0, -1):
+        debug("fused_gather", fused)
+        _announce("gather along", fwd, T, I, O, N, "fused", fused)
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        run = op.fwd if fwd else op.bwd
+        op.workspace(2, not fwd, plan)
+        torch.cuda.synchronize()
+        osdp.osdp_profile_begin(100)
+        run(2, plan=plan)
+        st = osdp.osdp_profile_end()
+        assert st["gather_carried"]["launches"] == (carried if fused else 0)
+        assert st["gather"]["launches"] >= (1 if fwd else 1 - carried)
+        got[fused] = [H.to_bits(op.Y)] if fwd else [H.to_bits(op.dX)] + [H.to_bits(s) for s in op.dW]
+    for a, b in zip(got[0], got[-1]):
+        assert np.array_equal(a, b)
+
+
 # ------------------------------------------------ forward products that run as parts of the reduction
 @pytest.mark.parametrize("T,I,O,N", [(512, 32768, 1024, 8),    # four parts of 8192
                                      (300, 49152, 520, 4)])    # six parts; ragged T and slices: the checked kernel
