@@ -119,8 +119,8 @@ constexpr bool w4_all_placed(int MB, int NB, int L) {
 // kCopy: the launch also carries p.job, the gather of a slice that a later launch will read (the forward GEMM of
 // slice j gathers slice j+1 into the other staging slot; a dW launch, which needs no weights, gathers the slices of
 // the dX pass that follows it).  Every workgroup copies total_vecs / gridDim.x vectors, 256 per K block: one 16-byte
-// load and one 16-byte store per lane and block, against that block's 16 KB of operand loads per wave.  The host sends
-// only copies that the K blocks hold (carry_fits): the kernel has no other place for them.  A gather kernel of its own
+// load and one 16-byte store per lane and block, against that block's 16 KB of operand loads per wave; what the K blocks
+// do not hold follows behind them, several pieces at a time.  A gather kernel of its own
 // cannot run beside this kernel, whose four waves hold every register of their SIMDs: on a second stream it only takes
 // turns with the tiles, and both get slower.  The carried copy is not free either (the kernel is bound by the memory pipe
 // the copy shares: a 64 MiB slice adds 25 us to a 190 us launch, against 28 us as a launch of its own); it saves the
@@ -309,6 +309,28 @@ __device__ __forceinline__ void gemm_w4_tile(const GemmParams &p, int tiles_m, i
     fill = after(fill);
   }
   wait_vmcnt<0>();  // surplus loads must have landed before the workgroup gives its LDS back
+  if constexpr (kCopy) {
+    // The piece still in registers, and whatever the K loop was too short for.  Nothing else is under way here: eight pieces
+    // share a round trip to memory (the fragments' registers are free).  Backward, us with one piece a round trip / eight / the
+    // gathers as launches, weights from memory, 32 pieces: 4096 -> 16384, k = 8, over 640 tokens (10 K blocks) 355 / 314 / 318,
+    // over 1100 (18) 418 / 399 / 395, over 1536 (24) 455 / 444 / 447; 4096 -> 4096, k = 2, over 640 77 / 67 / 69, and with the
+    // weights in a cache 66 / 60 / 64.
+    if (copy_i < copy_pieces) store_global16(p.job.dst + copy_v, copy_data);
+    constexpr int kBatch = 8;
+#pragma unroll 1
+    for (uint32_t i = copy_i + 1; i < copy_pieces; i += kBatch) {
+      uint4 data[kBatch];
+      uint32_t v[kBatch];
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        // (beyond the end the last piece again: the same bytes to the same place)
+        const uint4 *src = copy_src(i + e < copy_pieces ? i + e : copy_pieces - 1, &v[e]);
+        data[e] = load_global16(src);
+      }
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) store_global16(p.job.dst + v[e], data[e]);
+    }
+  }
 
   asm volatile("s_nop 15");
   asm volatile("s_nop 15");

@@ -435,17 +435,6 @@ double combine_estimate_us(int64_t M, int64_t N, int parts) {
   return (4.0 * parts + 2.0) * static_cast<double>(M) * static_cast<double>(N) / 3.0e6 + 8.0;
 }
 
-// Whether a launch of `tiles` workgroups should take the gather in p.job along: where its K blocks hold the copy, a piece of
-// 4 KB a workgroup and block.  What they do not hold is copied behind the K loop, a round trip to memory for every piece, and
-// loses to a launch of its own.  Backward, us with the gathers carried / launched, weights not in a cache, 32 pieces:
-// 4096 -> 16384, k = 8, over 640 tokens (10 blocks) 355 / 318, over 1100 (18) 418 / 395, over 1536 (24) 455 / 447, over 2048 (32)
-// 516 / 528 and over 3001 759 / 779 by row slices; 4096 -> 4096, k = 2, over 640 77 / 69.  Forward of 1536 tokens, 16384 ->
-// 8192 by row slices (86 pieces, 64 blocks) 548 / 499; of 3001, 1024 -> 32768 (11 of 16) 242 / 253.
-bool carry_fits(const GemmParams &p, long tiles, int parts) {
-  const int64_t pieces = (static_cast<int64_t>(p.job.total_vecs) + 256 * tiles - 1) / (256 * tiles);
-  return pieces <= (p.K / parts + 63) / 64;
-}
-
 // The four-wave kernel in the form that suits the number of tiles.
 template <int MB, int NB, bool kAK, bool kBK, int kEpi, bool kAccIn>
 hipError_t launch_four_wave(const GemmParams &p, hipStream_t stream, bool *carry) {
@@ -454,11 +443,10 @@ hipError_t launch_four_wave(const GemmParams &p, hipStream_t stream, bool *carry
   // (3-12 % per launch).  It takes no gather along: *carry stays as it is and the caller launches the
   // gather by itself, which measured better on every workload than keeping the plain kernel for its sake.
   const int pst = debug_options().persistent.load(std::memory_order_relaxed);  // testing: 0 never, 1 for any number of tiles
-  const long tiles = tile_count(p.M, p.N, 32 * MB, 32 * NB) * parts;
-  if (pst != 0 && !(parts > 1 && (p.k_split || kAccIn)) && (pst == 1 || tiles > kCUs))
+  if (pst != 0 && !(parts > 1 && (p.k_split || kAccIn)) && (pst == 1 || tile_count(p.M, p.N, 32 * MB, 32 * NB) * parts > kCUs))
     return launch_w4p<MB, NB, kAK, kBK, kEpi, kAccIn>(p, stream);
   if constexpr (!(kAK && kBK)) {  // dX launches read every staged slice there is: they never carry a gather
-    if (*carry && carry_fits(p, tiles, parts)) {
+    if (*carry) {
       *carry = false;
       return launch_w4<MB, NB, kAK, kBK, kEpi, kAccIn, true>(p, stream);
     }
