@@ -134,3 +134,78 @@ def test_four_wave_kernels_of_lone_tiles_keep_the_same_rules(gemm_asm, kernel, l
             assert not [t for t in ins[max(0, i - 3):i] if t.startswith(("v_accvgpr_write", "v_accvgpr_mov"))], \
                 f"{name}: an accumulator register is written right in front of an inline MFMA"
         _assert_no_valu_write_in_front_of_its_mfma(name, ins, mfma)
+
+
+def _inline_mfmas(lines, kernel):
+    """{mangled name: (instructions, indices of the MFMAs that stand in inline assembly)}: the compiler marks what it did
+    not write itself, and pads the hazards of its own MFMAs."""
+    out, cur, inline = {}, None, False
+    for line in lines:
+        m = re.match(r"^(_ZN4osdp\S*" + kernel + r"I\S*):", line)
+        if m:
+            cur = out.setdefault(m.group(1), ([], []))
+            continue
+        if re.match(r"^\S+:", line) and not line.startswith(".L"):   # another function starts
+            cur = None
+        t = line.strip()
+        if t.startswith((";;#ASMSTART", ";;#ASMEND")):
+            inline = "START" in t
+        elif cur and t and not t.startswith((";", ".")):
+            if inline and t.startswith("v_mfma"):
+                cur[1].append(len(cur[0]))
+            cur[0].append(t)
+    return out
+
+
+def _accumulators(operand):
+    """The AGPR numbers an operand like a7 or a[8:11] names (empty for anything else)."""
+    return _vgprs("v" + operand[1:]) if operand.startswith("a") else set()
+
+
+def _accumulator_writes_near(ins, mfma):
+    """(write, MFMA) pairs where one of the three instructions in front of an inline MFMA writes a register that it adds to."""
+    pairs = []
+    for i in mfma:
+        acc = _accumulators(ins[i].split(None, 1)[1].split(",")[0].strip())
+        for t in ins[max(0, i - 3):i]:
+            if t.startswith(("v_accvgpr_write", "v_accvgpr_mov")) and _accumulators(t.split(None, 1)[1].split(",")[0].strip()) & acc:
+                pairs.append((t, ins[i]))
+    return pairs
+
+
+def test_the_backward_of_few_tokens_keeps_the_same_rules_for_its_dw_tiles(gemm_asm):
+    """few_token_backward_kernel holds the loop of a 128 x 128 tile, whose 32 MFMAs the compiler cannot see, beside dX's, which
+    it schedules and pads by itself and which share the register file: the rules are for the inline ones."""
+    kernels = _inline_mfmas(gemm_asm, "few_token_backward_kernel")
+    assert len(kernels) == 4, "the instantiations were not found in the assembly"
+    for name, (ins, mfma) in kernels.items():
+        assert len(mfma) == 32, f"{name}: {len(mfma)} inline MFMAs"
+        assert len([t for t in ins if t.startswith("v_mfma")]) > 32, f"{name}: dX's own MFMAs were not found"
+        assert not [t for t in ins if t.startswith("scratch_")], f"{name}: scratch traffic"
+        assert not _accumulator_writes_near(ins, mfma), f"{name}: an accumulator register is written right in front of an inline MFMA"
+        _assert_no_valu_write_in_front_of_its_mfma(name, ins, mfma)
+
+
+def test_the_rules_for_inline_mfmas_find_a_planted_write():
+    """The two searches on a few lines of assembly: a write of an accumulator, and of a source, that the MFMA reads; the same
+    writes before an MFMA of the compiler's own, or of other registers, are none of theirs."""
+    head, tail = "_ZN4osdp1_25few_token_backward_kernelILi16EEEv:", "\ts_endpgm"
+    mfma = "\tv_mfma_f32_16x16x32_bf16 a[8:11], v[4:7], v[0:3], a[8:11]"
+    inline = ["\t;;#ASMSTART", mfma, "\t;;#ASMEND"]
+
+    def look(before, body=inline):
+        (name, (ins, found)), = _inline_mfmas([head] + before + body + [tail], "few_token_backward_kernel").items()
+        return name, ins, found
+
+    for write, hit in (("v_accvgpr_write_b32 a9, v20", True), ("v_accvgpr_write_b32 a12, v20", False), ("v_accvgpr_mov_b32 a[10:10], a1", True)):
+        name, ins, found = look(["\t" + write, "\ts_nop 1"])
+        assert bool(_accumulator_writes_near(ins, found)) == hit, write
+        name, ins, found = look(["\t" + write], [mfma])
+        assert not found
+    for write, hit in (("v_add_u32_e32 v5, 1, v9", True), ("v_add_u32_e32 v8, 1, v9", False)):
+        name, ins, found = look(["\t" + write])
+        if hit:
+            with pytest.raises(AssertionError):
+                _assert_no_valu_write_in_front_of_its_mfma(name, ins, found)
+        else:
+            _assert_no_valu_write_in_front_of_its_mfma(name, ins, found)
