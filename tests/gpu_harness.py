@@ -1,6 +1,8 @@
 """Test-side glue: moves seeded bf16 bit patterns to the GPU, calls libosdp, brings results back."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -65,6 +67,38 @@ class Operator:
 def streams():
     """(compute, copy) torch streams at the default priority; the compute stream is made current by the caller."""
     return torch.cuda.Stream(), torch.cuda.Stream()
+
+
+class _KernelNode(ctypes.Structure):   # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def kernels(call):
+    """(name, workgroups) of every kernel that call(stream) launches, in order, without running any: it is captured into a
+    graph, whose nodes are read.  The kernels' attributes have to be set, i.e. the call has run once."""
+    hip, stream = osdp.lib, torch.cuda.Stream()     # (libosdp brings the runtime along)
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    handle = ctypes.c_void_p(stream.cuda_stream)
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(handle, 2) == 0    # hipStreamCaptureModeRelaxed
+    try:
+        call(stream)
+    finally:
+        ended = hip.hipStreamEndCapture(handle, ctypes.byref(graph))
+    assert ended == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), handle)
+        out.append((name.decode(), p.grid[0]))
+    assert hip.hipGraphDestroy(graph) == 0
+    return out
 
 
 REL_TOL = 2e-2  # max relative error against the fp64 oracle (bf16 inputs, fp32 accumulation)

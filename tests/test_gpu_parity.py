@@ -1305,31 +1305,43 @@ def test_four_wave_tiles_of_224_rows_and_of_160_columns(H, oracle, T, I, O, N, k
 
 
 # ------------------------------------------------ the persistent form of the four-wave kernel
-@pytest.mark.parametrize("T,I,O,N,k", [
-    (577, 160, 72, 1, 1),      # one tile column, K = 72: a K block and 8 left over; a row beyond nine tiles of 64
-    (640, 1288, 200, 4, 2),    # eight columns beyond the eighth tile; row slices of 644 are not multiples of 8: column slices only
-    (1100, 5120, 520, 8, 4),   # 18 x 32 tiles of 64 rows are too many: tiles of 128 rows
-    (1000, 336, 1600, 2, 3),   # row slices of 112 columns
+@pytest.mark.parametrize("T,I,O,N,k,rows", [
+    (577, 160, 96, 1, 2, 64),      # one tile column; K = 96 is a K block and a half, in column slices 48; a row beyond nine tiles of 64
+    (640, 1288, 224, 4, 2, 64),    # eight columns beyond the eighth tile; row slices of 644 would not be whole vectors
+    (1000, 5120, 544, 8, 2, 128),  # 16 x 32 tiles of 64 rows are too many: tiles of 128 rows; of the row slices 64 again
+    (1000, 336, 1632, 2, 3, 64),   # row slices of 112 columns: less than a tile
 ])
-def test_dx_tiles_of_160_columns_keep_the_bits_of_the_checked_kernel(H, oracle, T, I, O, N, k, debug):
-    """dX launches of at most one tile per CU, of 64 or 128 rows and 160 columns: for the unsplit operator and for slices of
-    either kind, the bits of the checked kernel and of 128 x 128 tiles, and the oracle's values."""
+def test_dx_tiles_of_160_columns_keep_the_bits_of_the_checked_kernel(H, oracle, T, I, O, N, k, rows, debug):
+    """dX launches of at most one tile per CU, of 64 or 128 rows and 160 columns, with results in bf16 (the unsplit operator, row
+    slices) and in fp32 (the first of the column slices, which the others add to): the bits of the checked kernel and of 128 x
+    128 tiles, and the oracle's values.  The kernels that ran are read from a capture of the call."""
     import paper_2209_13258_amd as osdp
     d = wl.small_case(79, T, I, O, N)
     want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"], want=("dX",))
-    cuts = [(kk, dim) for kk in (1, k) for dim in (0, 1) if (I if dim else O) % (8 * kk) == 0]
+    cuts = [(1, 0)] + [(k, dim) for dim in (0, 1) if (I if dim else O) % (8 * k) == 0]
+    assert (k, 0) in cuts
     ref = {}
     for switches in ({"gemm_generic": 1}, {"tile": 3}, {"split_launch": 0}, {}):
-        for name, value in {**DEBUG_DEFAULTS, **switches}.items():
+        for name, value in {**DEBUG_DEFAULTS, "recut": 0, **switches}.items():
             debug(name, value)
         for kk, dim in cuts:
             _announce("dX in tiles of 160 columns", T, I, O, N, kk, dim, switches)
             op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
-            op.bwd(kk, plan=osdp.Plan([kk], staging=osdp.OSDP_STAGING_DOUBLE, split_dim_per_op=[dim]))
+            plan = osdp.Plan([kk], staging=osdp.OSDP_STAGING_SINGLE, split_dim_per_op=[dim])
+            op.bwd(kk, plan=plan)
             torch.cuda.synchronize()
             got = H.to_bits(op.dX)
             H.assert_close("dX", got, want["dX"])
             assert np.array_equal(got, ref.setdefault(1, got)), (switches, kk, dim)
+            tiles = [name for name, _ in H.kernels(lambda s: op.bwd(kk, plan=plan, streams=(s, None))) if "gemm_w4_160_kernel" in name]
+            if not switches:
+                # <rows / 32, slots, both operands K-contiguous, epilogue, no sum to start from>: one launch, or one per row slice
+                r = 64 if dim else rows
+                assert len(tiles) == (k if dim else 1)
+                for name in tiles:
+                    assert f"ILi{r // 32}E" in name and f"ELb1ELb1ELi{2 if (kk, dim) == (k, 0) else 0}ELb0E" in name, (kk, dim, name)
+            elif "split_launch" not in switches:
+                assert not tiles
 
 
 @pytest.mark.parametrize("dim", [0, 1])
