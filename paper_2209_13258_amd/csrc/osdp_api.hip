@@ -426,9 +426,11 @@ bool recut(const osdp_shape *shape, const Resolved &r, bool is_fwd, Resolved *ou
   if (forced == 1) return true;
   auto us = [&](const Resolved &q, bool adds) {
     double t = 0.0;
+    bool first = true;  // (the first launch of a pass that adds up starts from zero)
     for (const Slice &l : is_fwd ? q.fwd : q.pass) {
       const int64_t span = q.sub[l.c1 - 1].c1 - q.sub[l.c0].c0;
-      t += adds ? gemm_planned_us(q.T, q.D, span, !is_fwd) : gemm_planned_us(q.T, span, q.D, !is_fwd);
+      t += adds ? gemm_planned_us(q.T, q.D, span, !is_fwd, !first) : gemm_planned_us(q.T, span, q.D, !is_fwd, false);
+      first = false;
     }
     if (adds) t += static_cast<double>(sum.size() - 1) * 8.0 * static_cast<double>(q.T) * static_cast<double>(q.D) / 4.5e6;
     if (!is_fwd)

@@ -386,18 +386,26 @@ bool tile_offered(int i, int kind, int K, int narrow_k = kNarrowMinK) {
          debug_options().small_tile.load(std::memory_order_relaxed) != 0;
 }
 
+// What a tile is chosen for, which decides the shapes and prices that count.
+enum class TileUse {
+  kLaunch,       // a launch, or a plan of launches, that starts from zero: all shapes
+  kSumLaunch,    // a launch that starts from a sum in memory: no prices of lone tiles, whose first K blocks alone would have to
+                 // cover that load (2048 x 4096 over K = 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
+  kSumPlan,      // a plan of such launches: see plan_launches
+  kFirstShapes,  // the shapes that workspace sizes were first given for
+};
+
 // Cheapest tile for M x N; a column split must fall on a tile boundary.
 // parts > 1: the launch has that many workgroups per tile (parts of the reduction); the cost is in tile passes over
 // the whole reduction all the same, so the caller divides it by parts.
-int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, bool acc_in = false, int shapes = kTileShapes) {
-  // (a lone tile that starts from a sum in memory has only its first K blocks to cover that load with: 2048 x 4096 over K =
-  // 4096 and 8192 1 to 3 us slower than in pairs of 128 x 128)
-  const bool lone = !acc_in && debug_options().deep.load(std::memory_order_relaxed) != 0;
+int best_tile(int M, int N, int K, int n_split, int kind, double *cost, int parts = 1, TileUse use = TileUse::kLaunch) {
+  const bool lone = use != TileUse::kSumLaunch && debug_options().deep.load(std::memory_order_relaxed) != 0;
+  const int shapes = lone && use == TileUse::kLaunch ? kTileShapes : kPricedShapes;
   int best = -1;
   double best_cost = 0.0;
   for (int i = 0; i < shapes; ++i) {
-    if (i >= kPricedShapes && (!lone || tile_count(M, N, kTiles[i].bm, kTiles[i].bn) * parts > kCUs)) continue;  // lone tiles only
-    if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts, shapes == kPricedShapes ? kNarrowPricedK : kNarrowMinK)) continue;
+    if (i >= kPricedShapes && tile_count(M, N, kTiles[i].bm, kTiles[i].bn) * parts > kCUs) continue;  // lone tiles only
+    if (n_split % kTiles[i].bn || !tile_offered(i, kind, K / parts, use == TileUse::kFirstShapes ? kNarrowPricedK : kNarrowMinK)) continue;
     const double c = tile_cost(M, N, kTiles[i].bm, kTiles[i].bn, kTiles[i].penalty[kind], parts, lone ? kTiles[i].lone[kind] : 0.0);
     if (best < 0 || c < best_cost) {
       best = i;
@@ -460,7 +468,8 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
   constexpr int kind = layout_kind(kAK, kBK);
   const int parts = p.k_parts > 1 ? p.k_parts : 1;  // parts of the reduction run as further tiles of the same launch
   if (fast_path(p.K, p.k_split, p.n_split) && fits_offsets(p)) {
-    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts, kAccIn, p.seg_n ? kPricedShapes : kTileShapes);
+    int best = best_tile(p.M, p.N, p.K, p.n_split, kind, nullptr, parts,
+                         kAccIn ? TileUse::kSumLaunch : p.seg_n ? TileUse::kFirstShapes : TileUse::kLaunch);
     const int forced = debug_options().tile.load(std::memory_order_relaxed);  // testing: tile 0..3 where it fits the segments of B
     bool force = forced >= 0 && forced <= 3;
     if (force && p.n_split % kTiles[forced].bn == 0) best = forced;
@@ -549,11 +558,17 @@ GemmParams row_range(const GemmParams &p, int m0, int m1) {
 // (usually a small one that spreads it over all CUs).  Tile shape never changes a result bit, so neither does this.
 // Returns the modelled cost (tile-area units) of the best plan for a one-segment M x N x K problem of the given
 // layout; axis = 1: columns [0, cut) and [cut, N) are launched separately; axis = 0: rows; axis = -1: one launch.
-double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
+// acc_in: launches that start from a sum in memory.  They run no tile that is for lone launches only, and none is priced here: a
+// remainder that looked as cheap as in 64 x 160 tiles ran in 128 x 128 (a dX pass of three slices, us priced so / priced as
+// here: 10241 x 3136 over K = 512 224 / 199, 6131 x 3008 over 3264 385 / 363, 5652 x 2944 over 1024 184 / 170).  The shapes that both
+// kinds of launches run keep their prices as lone tiles, although best_tile picks those launches without: with both alike 60
+// dX passes are as fast within 0.4 %, and 39 forward passes 3 % slower, some by 15.
+double plan_launches(int M, int N, int K, int kind, bool acc_in, int *axis, int *cut) {
+  const TileUse use = acc_in ? TileUse::kSumPlan : TileUse::kLaunch;
   double whole = 0.0;
   *axis = -1;
   *cut = 0;
-  best_tile(M, N, K, 0, kind, &whole);
+  best_tile(M, N, K, 0, kind, &whole, 1, use);
   // testing: split_launch = 0 keeps every problem in one launch, as does a forced tile shape
   if (debug_options().split_launch.load(std::memory_order_relaxed) == 0 ||
       debug_options().tile.load(std::memory_order_relaxed) >= 0)
@@ -567,7 +582,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cn = static_cast<int>(static_cast<long>(kCUs) * r / tm);
     if (cn <= 0) continue;
     if (cn >= tn) break;
-    best_tile(M, N - cn * 256, K, 0, kind, &rest);
+    best_tile(M, N - cn * 256, K, 0, kind, &rest, 1, use);
     const double c = tile_cost(M, cn * 256, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 1; *cut = cn * 256; }
   }
@@ -575,7 +590,7 @@ double plan_launches(int M, int N, int K, int kind, int *axis, int *cut) {
     const int cm = static_cast<int>(static_cast<long>(kCUs) * r / tn);
     if (cm <= 0) continue;
     if (cm >= tm) break;
-    best_tile(M - cm * 256, N, K, 0, kind, &rest);
+    best_tile(M - cm * 256, N, K, 0, kind, &rest, 1, use);
     const double c = tile_cost(cm * 256, N, 256, 256, 1.0) + rest + between;
     if (c < best) { best = c; *axis = 0; *cut = cm * 256; }
   }
@@ -607,7 +622,7 @@ hipError_t launch_planned(const GemmParams &p, hipStream_t stream, bool *carry, 
   }
   if (!p.k_split && !p.n_split && !p.seg_k && !p.seg_n && fast_path(p.K, 0, 0) && fits_offsets(p)) {
     int axis, cut;
-    plan_launches(p.M, p.N, p.K, layout_kind(kAK, kBK), &axis, &cut);
+    plan_launches(p.M, p.N, p.K, layout_kind(kAK, kBK), kAccIn, &axis, &cut);
     if (axis == 1) {
       hipError_t e = launch_best<kAK, kBK, kEpi, kAccIn>(column_range<kBK, kEpi>(p, 0, cut), stream, carry);
       if (e != hipSuccess) return e;
@@ -653,10 +668,10 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   double cost = 0.0;
   if (M > 0 && fast_path(static_cast<int>(K), 0, 0)) {
     // (how slices are paired decides how much workspace a call asks for: it goes by the shapes that sizes were first given for)
-    best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, 1, false, kPricedShapes);
+    best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, 1, TileUse::kFirstShapes);
     const int parts = forward_parts ? forward_k_parts(M, K) : 1;
     if (parts > 1) {
-      best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, parts, false, kPricedShapes);
+      best_tile(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), 0, 0, &cost, parts, TileUse::kFirstShapes);
       return cost / parts * 2.0 * static_cast<double>(K) / 5.0e6 + combine_estimate_us(M, N, parts) + 6.0;
     }
     return cost * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;
@@ -666,10 +681,10 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts) {
   return rounds * GBM * GBN * 5.0 * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;  // the checked kernel is about 5x slower per tile
 }
 
-double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx) {
+double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx, bool acc_in) {
   if (M <= 0 || !fast_path(static_cast<int>(K), 0, 0)) return gemm_estimate_us(M, N, K);
   int axis, cut;
-  const double cost = plan_launches(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), dx ? 2 : 0, &axis, &cut);
+  const double cost = plan_launches(static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), dx ? 2 : 0, acc_in, &axis, &cut);
   return cost * 2.0 * static_cast<double>(K) / 5.0e6 + 6.0;
 }
 
@@ -872,7 +887,7 @@ bool few_token_backward_takes(const GemmProblem &dw, int64_t T) {
       d.deep.load(std::memory_order_relaxed) == 0 || d.small_tile.load(std::memory_order_relaxed) == 1 ||
       best_tile(p.M, p.N, p.K, 0, 1, nullptr) != 3)
     return false;
-  plan_launches(p.M, p.N, p.K, 1, &axis, &cut);
+  plan_launches(p.M, p.N, p.K, 1, false, &axis, &cut);
   if (axis >= 0) return false;
   const int64_t n_dw = tile_count(p.M, p.N, 128, 128), bm = beside_rows(T, p.M, n_dw);
   return bm <= 64 || n_dw + (T + bm - 1) / bm * ((p.M + 63) / 64) <= kCUs;

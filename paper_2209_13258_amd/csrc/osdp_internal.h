@@ -155,7 +155,7 @@ double gemm_estimate_us(int64_t M, int64_t N, int64_t K, bool forward_parts = fa
 
 // The same for a forward or (dx) dX product of one segment as launch_gemm runs it, whole rounds and a remainder as two
 // launches where that is faster.
-double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx);
+double gemm_planned_us(int64_t M, int64_t N, int64_t K, bool dx, bool acc_in);
 
 // Launches of the calling thread that ran as the persistent four-wave kernel so far (for the profile).
 int64_t gemm_persistent_launches();

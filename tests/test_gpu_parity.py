@@ -1,4 +1,6 @@
 """GPU parity: libosdp (HIP, through the C ABI) against the CPU oracle, element by element."""
+import re
+
 import numpy as np
 import pytest
 
@@ -1342,6 +1344,20 @@ def test_dx_tiles_of_160_columns_keep_the_bits_of_the_checked_kernel(H, oracle, 
                     assert f"ILi{r // 32}E" in name and f"ELb1ELb1ELi{2 if (kk, dim) == (k, 0) else 0}ELb0E" in name, (kk, dim, name)
             elif "split_launch" not in switches:
                 assert not tiles
+
+
+def test_a_launch_onto_a_sum_is_planned_by_the_tiles_that_it_runs(H, debug):
+    """dX of column slices: from the second on the launches start from the sum in the workspace and take no tile that is for
+    lone launches only.  Priced as in 64 x 160 tiles, 128 columns of 7296 looked cheap enough for a launch of their own."""
+    import paper_2209_13258_amd as osdp
+    debug("recut", 0)
+    T, I, O, k = 2200, 7296, 960, 3
+    op = H.Operator(np.zeros((T, I), np.uint16), np.zeros((T, O), np.uint16), [np.zeros(I * O // 8, np.uint16)] * 8, O)
+    plan = osdp.Plan([k], staging=osdp.OSDP_STAGING_SINGLE)
+    op.bwd(k, plan=plan)
+    names = [name for name, _ in H.kernels(lambda s: op.bwd(k, plan=plan, streams=(s, None)))]
+    onto_sum = [n for n in names if re.search(r"ELb1ELb1ELi[02]ELb1E", n)]   # both operands K-contiguous, starts from a sum
+    assert len(onto_sum) == k - 1, names
 
 
 @pytest.mark.parametrize("dim", [0, 1])
