@@ -452,7 +452,8 @@ typedef enum {
   OSDP_KERNEL_GATHER = 0,
   OSDP_KERNEL_GEMM_FWD = 1,
   OSDP_KERNEL_GEMM_DW = 2,
-  OSDP_KERNEL_GEMM_DX = 3,
+  OSDP_KERNEL_GEMM_DX = 3,        /* and, with the work of both, the one launch that computes dX and dW of a small operator for
+                                     few tokens: kind 2 then counts none */
   OSDP_KERNEL_GATHER_CARRIED = 4, /* gathers that ran inside a GEMM launch: launches and bytes only, their time is
                                      part of the GEMM launches that carried them */
   OSDP_KERNEL_GEMM_PERSISTENT = 5, /* the GEMM launches among kinds 1-3 that ran as the persistent kernel (one workgroup

@@ -1216,8 +1216,9 @@ static osdp_status backward(const osdp_shape *shape, const osdp_plan *plan, int3
         const uintptr_t d0 = reinterpret_cast<uintptr_t>(dX), d1 = d0 + 2 * static_cast<uintptr_t>((r.T - 1) * lddx + r.I);
         return p1 <= d0 || d1 <= p0;
       };
-      if (clear_of_dx(X, ldx, r.I) && clear_of_dx(dY, lddy, r.O) && few_token_backward_takes(gw, r.T)) {  // (the profile counts it as the dX launch, with the work of both)
-        OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 4.0 * T * I * O, 2.0 * (T * O + I * O + T * I) + 2.0 * (T * I + T * O + I * O), sc, [&] {
+      if (clear_of_dx(X, ldx, r.I) && clear_of_dx(dY, lddy, r.O) && few_token_backward_takes(gw, r.T)) {
+        // (the profile counts it as the dX launch, with the work of both: dY, which both read, once)
+        OSDP_HIP(timed(OSDP_KERNEL_GEMM_DX, 4.0 * T * I * O, 2.0 * (T * O + 2.0 * T * I + 2.0 * I * O), sc, [&] {
           return launch_few_token_backward(gw, weight_map(r, tab, rep), r.T, dY, lddy, dX, lddx, sc);
         }));
         return OSDP_OK;

@@ -963,6 +963,21 @@ def test_few_tokens_run_the_backward_in_one_launch(H, oracle, I, O, N, one, debu
             H.assert_close("dW", got[-1][1][: I * O].reshape(I, O), want["dW"])
 
 
+def test_the_profile_counts_the_operands_of_a_shared_launch_once(H):
+    """dX and dW of few tokens in one launch: under dX, the flops of both, every operand (dY too, which both read) once."""
+    import paper_2209_13258_amd as osdp
+    T, I, O = 33, 256, 512
+    d = wl.small_case(85, T, I, O, 4)
+    op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+    op.workspace(1, True)
+    osdp.osdp_profile_begin(10)
+    op.bwd(1)
+    st = osdp.osdp_profile_end()
+    assert (st["gemm_dw"]["launches"], st["gemm_dx"]["launches"]) == (0, 1)
+    assert st["gemm_dx"]["flops"] == 2 * 2 * T * I * O
+    assert st["gemm_dx"]["bytes"] == 2 * ((T * I + T * O + I * O) + (T * I + I * O))
+
+
 @pytest.mark.parametrize("I,O,N", [(64, 128, 1), (64, 2048, 8), (40, 264, 33), (8, 64, 2)])
 def test_few_tokens_store_dx_in_the_place_of_dy(H, oracle, I, O, N):
     """With at most 64 in-features a tile of dX reads all of its rows of dY before it stores them, and dW has read dY by then
