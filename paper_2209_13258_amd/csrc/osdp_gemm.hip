@@ -871,14 +871,17 @@ hipError_t launch_backward_as(SkinnyParams dx, const GemmParams &dw, hipStream_t
 }  // namespace
 
 namespace {
-// Rows of a workgroup's tile of dX beside n_dw tiles of dW: for the CUs that these leave, or the quarter of them that is
-// done with its tile of dW first.
+// Rows of a workgroup's tile of dX beside n_dw tiles of dW: for the CUs that these leave, or a quarter of all where they leave
+// fewer.  us for tiles chosen for a quarter / a half / all of the CUs: 128 tokens 1024 -> 3072 12.2 / 13.5 / 13.5, 1024 -> 4096 14.2 /
+// 15.2 / 15.2; 64 tokens 3072 -> 768 7.2 / 7.4 / 9.9; 128 tokens 2048 -> 2048 12.8 / 11.3 / 18.4; over 90 calls of 16 to 128 tokens
+// (two launches: 1) 0.72 / 0.70 / 0.74.
 int beside_rows(int64_t T, int64_t N, int64_t n_dw) { return skinny_rows(T, N, static_cast<int>(std::max<int64_t>(kCUs - n_dw, kCUs / 4))); }
 }  // namespace
 
 // us, two launches / one: 128 tokens 256 -> 1024 10.7 / 5.8, 1536 -> 1536 12.3 / 8.6, 2048 -> 2048 13.9 / 12.4, 512 -> 8192
-// 24.7 / 19.5, 16 tokens 1024 -> 4096 16.5 / 11.9.  Where they make more than one round together and all tokens are in one
-// tile of dX, that tile, the longest, starts the round of the others late: 96 and 128 tokens 4096 -> 1024 13.1 / 15.7.
+// 24.7 / 19.5, 16 tokens 1024 -> 4096 16.5 / 11.9.  Two launches are kept for more than 64 tokens and so many in-features that tiles of dX
+// with all rows make more than one round with those of dW: 128 tokens 4096 -> 1024 13.7 against 15.7 for one launch with such tiles (of 64
+// rows, as one launch has now, 10.4; 8192 -> 512 13.5 and 12.5: the line could move).
 bool few_token_backward_takes(const GemmProblem &dw, int64_t T) {
   const DebugOptions &d = debug_options();
   const GemmParams p = gemm_params(dw);
@@ -900,8 +903,9 @@ hipError_t launch_few_token_backward(const GemmProblem &dw, const WeightMap &w, 
   const int bm = beside_rows(T, p.N, tile_count(g.M, g.N, 128, 128));
   if (bm == 16) return launch_backward_as<16, 64, 3>(p, g, stream);
   if (bm == 32) return launch_backward_as<32, 64, 3>(p, g, stream);
-  if (bm <= 64) return launch_backward_as<64, 64, 2>(p, g, stream);
-  return launch_backward_as<128, 32, 3>(p, g, stream);
+  // (never 128 rows: their tile is the longest of the launch by far.  us as two launches / one with 128 rows / one with 64, 128
+  // tokens: 3072 -> 1024 13.4 / 16.3 / 10.0, 2560 -> 1280 14.0 / 18.3 / 10.5)
+  return launch_backward_as<64, 64, 2>(p, g, stream);
 }
 
 hipError_t launch_gemm(const GemmProblem &q, hipStream_t stream) {

@@ -963,6 +963,28 @@ def test_few_tokens_run_the_backward_in_one_launch(H, oracle, I, O, N, one, debu
             H.assert_close("dW", got[-1][1][: I * O].reshape(I, O), want["dW"])
 
 
+@pytest.mark.parametrize("T,I,O", [(96, 3072, 1024), (128, 3072, 1024), (128, 2560, 1280)])
+def test_tiles_of_dx_beside_those_of_dw_have_at_most_64_rows(H, T, I, O, debug):
+    """So many tiles of dW that few CUs are left: a tile of dX with 96 or 128 rows lasted longer than two launches.  The bits of
+    the two."""
+    d = wl.small_case(87, T, I, O, 8)
+    got = []
+    for deep in (-1, 0):
+        debug("deep", deep)
+        _announce("64 rows of dX beside dW", T, I, O, "deep", deep)
+        op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+        op.bwd(1)
+        torch.cuda.synchronize()
+        got.append([H.to_bits(op.dX)] + [H.to_bits(s) for s in op.dW])
+        names = [name for name, _ in H.kernels(lambda s: op.bwd(1, streams=(s, None)))]
+        if deep:
+            assert len(names) == 1 and "few_token_backward_kernelILi64E" in names[0], names
+        else:
+            assert len(names) == 2, names
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_the_profile_counts_the_operands_of_a_shared_launch_once(H):
     """dX and dW of few tokens in one launch: under dX, the flops of both, every operand (dY too, which both read) once."""
     import paper_2209_13258_amd as osdp
