@@ -424,8 +424,8 @@ OSDP_API osdp_status osdp_plan_search(const osdp_operator_cost *ops, int32_t n, 
  *   "split_launch"  -1 | 0   0: no launch is cut into whole rounds of large tiles + remainder
  *   "split_k"       -1 | 0   0: forward products are never summed in parts of the reduction (this
  *                            changes the bits of the products that are otherwise summed in parts)
- *   "four_wave"     -1 .. 1  0: 256x256 tiles always run on the eight-wave kernel; 1: on the four-wave kernel
- *                            whenever it takes the launch (K > 128), as they do by themselves
+ *   "four_wave"     -1 .. 1  0: 256x256 tiles always run on the eight-wave kernel; 1: on the four-wave kernel,
+ *                            also for K <= 128
  *   "persistent"    -1 .. 1  0: a launch of more 256x256 tiles than CUs keeps the four-wave kernel of one tile per
  *                            workgroup; otherwise one workgroup per CU walks through the tiles; 1: the walking
  *                            form also for launches of fewer tiles

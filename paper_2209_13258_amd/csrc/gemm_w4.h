@@ -16,8 +16,9 @@
 // Same MFMA sequence per output element as every other GEMM kernel of the library (K ascending in steps of 32,
 // v_mfma_f32_16x16x32_bf16, the same lane -> k map), so the result bits are the same.
 //
-// Tiles of 32 * MB x 32 * NB, the large one (8 x 8) wherever its rounds are full.  Any M and N, K > 128 (k_split % 64 == 0, n_split % 256 == 0): edges are handled by the range check of the operand
-// loads and guarded stores (OperandSource in gemm_dma.h).
+// Tiles of 32 * MB x 32 * NB, the large one (8 x 8) wherever its rounds are full.  Any M, N and K
+// (k_split % 64 == 0, n_split a multiple of the tile's columns): edges are handled by the range check of the operand
+// loads, which also lets blocks beyond the last one deliver nothing, and guarded stores (OperandSource in gemm_dma.h).
 #pragma once
 #include "gemm_common.h"
 #include "gemm_dma.h"
@@ -351,7 +352,7 @@ void gemm_w4_small_kernel(GemmParams p, int tiles_m, int tiles_n) {
   gemm_w4_tile<MB, NB, 2, kAK, kBKc, kEpi, kAccIn, kCopy>(p, tiles_m, tiles_n, logical_block());
 }
 
-// Tiles of 160 columns for launches of at most one tile per CU (forward, dX), with as many slots as fit.
+// Tiles of 160 columns for launches of at most one tile per CU (dX), with as many slots as fit.
 template <int MB, int kSlots, bool kAK, bool kBKc, int kEpi, bool kAccIn>
 __global__ __launch_bounds__(256, 1)
 void gemm_w4_160_kernel(GemmParams p, int tiles_m, int tiles_n) {

@@ -11,8 +11,8 @@
 // acknowledgement.)
 //
 // Same tiles in the same order per XCD, same MFMA sequence per output element as every other GEMM kernel of the
-// library: same bits.  Takes what the plain kernel takes except a carried gather: any M and N (n_split % 256 == 0),
-// K > 128 (k_split % 64 == 0; per part, when the launch runs parts of the reduction).
+// library: same bits.  Takes what the plain kernel takes except a carried gather: any M, N and K (n_split a multiple of the
+// tile's columns, k_split % 64 == 0; per part, when the launch runs parts of the reduction).
 #pragma once
 #include "gemm_w4.h"
 

@@ -297,7 +297,7 @@ hipError_t launch_w4p(const GemmParams &p, hipStream_t stream) {
 }
 
 constexpr int kShortK = 1024;
-constexpr int kW4MinK = 129;  // the four-wave kernel's K loop assumes at least three K blocks of 64
+constexpr int kW4MinK = 129;  // 256 x 256 tiles: from three K blocks of 64 on the four-wave kernel (both sides at case 0 of launch_best)
 
 // Estimated cost of covering M x N with BM x BN tiles on 256 CUs: tiles per CU times the tile's area, with a
 // penalty for the lower MFMA efficiency of smaller tiles.  Tiles that run two to a CU were measured in pairs; a
@@ -489,13 +489,16 @@ hipError_t launch_best(const GemmParams &p, hipStream_t stream, bool *carry) {
     // the whole LDS for a deeper pipeline instead (twice the bytes in flight).
     const bool deep = best > 0 && best < 4 && tile_count(p.M, p.N, kTiles[best].bm, kTiles[best].bn) * parts <= kCUs &&
                       debug_options().deep.load(std::memory_order_relaxed) != 0;  // testing: 0 keeps the shallow pipelines
-    const int fw = debug_options().four_wave.load(std::memory_order_relaxed);  // testing: 0 never, 1 whenever it can
+    const int fw = debug_options().four_wave.load(std::memory_order_relaxed);  // testing: 0 never, 1 for any K
     switch (best) {
       case 0:
-        // (256 x 256 tiles of the eight-wave kernel are left where the four-wave kernel's loop does not fit.  dW ran on them
+        // (The four-wave kernel takes any K; 256 x 256 tiles of the eight-wave kernel are left for at most two K blocks of 64, where
+        // start-up is all there is and neither is ahead everywhere: us, eight / four waves, forward of 4096 x 4096 over K = 64 and 128
+        // 13.2 / 13.8, 14.9 / 15.6, of 8192 x 16384 over 64 64 / 69, but 8192 x 8192 over 128 46 / 37; dX of those 13.1 / 13.5, 15.1 / 15.0,
+        // 45 / 37; dW of 8192 x 16384 over 96 79 / 75.  dW ran on them
         // below 8192 tokens as long as the four-wave epilogue into shards took 32 us a tile and not 15; now, eight / four waves, 8192 x
         // 8192 over 4096 / 1024 / 256 tokens 417 / 378, 133 / 117, 59 / 50 us; 2560 x 10240 over 3001 and 1500 160 / 130, 83 / 74)
-        if (p.K / parts >= kW4MinK && fw != 0) {
+        if (fw != 0 && (fw == 1 || p.K / parts >= kW4MinK)) {
           return launch_four_wave<8, 8, kAK, kBK, kEpi, kAccIn>(p, stream, carry);
         }
         if (kind == 0) return launch_dma<256, 256, 64, 128, 64, 2, kAK, kBK, kEpi, kAccIn>(p, stream);

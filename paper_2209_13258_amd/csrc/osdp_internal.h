@@ -184,7 +184,7 @@ struct DebugOptions {
   std::atomic<int32_t> small_tile{-1};     // 0: no four-wave tiles below 256 x 256; 1: those wherever they serve the layout
   std::atomic<int32_t> recut{-1};          // 0: a pass that adds slices up keeps the plan's cut; 1: it is cut the other way wherever the slices allow
   std::atomic<int32_t> fused_gather{-1};   // 0: gathers always run as launches of their own (second stream where given)
-  std::atomic<int32_t> four_wave{-1};      // 0: 256 x 256 tiles run on the eight-wave kernel
+  std::atomic<int32_t> four_wave{-1};      // 0: 256 x 256 tiles run on the eight-wave kernel; 1: on the four-wave kernel for any K
   std::atomic<int32_t> persistent{-1};     // 0: launches of more 256 x 256 tiles than CUs keep the plain four-wave kernel instead of its persistent form; 1: the persistent form for any number of tiles
   std::atomic<int32_t> split_k{-1};        // 0: forward products are never split along K (changes the bits of those that are)
   std::atomic<int32_t> poison_staging{0};  // 1: staging slots hold NaN patterns whenever no gathered slice is live in them

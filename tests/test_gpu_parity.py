@@ -1475,6 +1475,29 @@ def test_persistent_kernel_with_tiles_of_three_to_five_k_blocks(H, oracle, debug
     assert np.array_equal(got[0], got[-1])
 
 
+@pytest.mark.parametrize("n", [8, 64, 72, 128])
+def test_four_wave_tiles_of_one_and_two_k_blocks(H, oracle, debug, n):
+    """256 x 256 tiles over at most 128 k, which the switch sends to the four-wave kernel too, one tile per workgroup and
+    walking through several: forward, dX and dW each with the short dimension as the reduction; the checked kernel's bits."""
+    for T, I, O in ((768, n, 4624), (768, 4624, n), (n, 520, 4624)):   # 3 x 19 tiles, or dW's 3 x 19
+        d = wl.small_case(97, T, I, O, 4)
+        want = oracle.linear(d["X"], d["W_shards"], O, dY=d["dY"])
+        ref = None
+        for switches in ({"gemm_generic": 1}, {"tile": 0, "four_wave": 1, "persistent": 0}, {"tile": 0, "four_wave": 1, "persistent": 1}):
+            for name, value in {**DEBUG_DEFAULTS, **switches}.items():
+                debug(name, value)
+            _announce("one or two K blocks", T, I, O, switches)
+            op = H.Operator(d["X"], d["dY"], d["W_shards"], O)
+            op.fwd(1)
+            op.bwd(1)
+            got = op.results()
+            ref = ref or got
+            for name in ("Y", "dX", "dW"):
+                H.assert_close(name, got[name], want[name])
+                if T > 128 or name == "dW":   # (forward and dX of few tokens run on a kernel of their own)
+                    assert np.array_equal(got[name], ref[name]), (T, I, O, name, switches)
+
+
 @pytest.mark.parametrize("rows", [False, True])
 def test_persistent_kernel_reads_a_dp_and_a_gathered_slice_in_one_launch(H, oracle, debug, rows):
     """Launches over a DP slice (read in its replica, row length of the whole weight) and a gathered neighbour (in a
