@@ -339,28 +339,32 @@ struct TileShape {
   double penalty[3];
   double lone[3];  // the same for a launch of at most one tile per CU
 };
-// 8192^3 on MI355X, forward / dW / dX in PFLOP/s, eight-wave kernels: 256x256 1.22 / 1.23 / 1.26; 256x128 (two
-// workgroups per CU) 1.04 / 0.90 / 1.09; 128x256 (two per CU) 1.19 / 1.02 / 1.06; 128x128 (two per CU) 1.03 / 1.05 /
-// 1.03.  The 256x256 tile runs on the four-wave kernel (gemm_w4.h) whenever K > 128: 1.43 / 1.30 / 1.45 on the
-// same problem, which is what the penalties of the other shapes are relative to.
+// 8192^3 on MI355X, forward / dW / dX in PFLOP/s: 256x256 on the four-wave kernel 1.47 / 1.45 / 1.48, on the eight-wave one 1.27 / 1.37 /
+// 1.37; 256x128 (two workgroups per CU) 1.19 / 1.28 / 1.10; 128x256 (two per CU) 1.28 / 1.27 / 1.06; 128x128 (two per CU) 1.20 / 1.12 /
+// 1.20.  The penalties are older than these kernels' short epilogues and than the four-wave kernel's 128x128 tiles: they were taken
+// from 1.43 / 1.30 / 1.45 for 256x256 against 1.04 / 0.90 / 1.09, 1.19 / 1.02 / 1.06 and 1.03 / 1.05 / 1.03 (128x128 in eight waves), and
+// fitted to launches of one and two tiles a CU.  From the rates above they would be 1.23 / 1.13 / 1.34, 1.15 / 1.14 / 1.39 and 1.23 / 1.30 / 1.23;
+// with those below the choice was still within 6 % of the best tile in 183 of 192 launches (4096 rows, 512 to 12288 columns, K from
+// 1024 to 10240).
 // K block and LDS stages of the eight-wave kernels per layout, also measured: forward (transposing reads of B) runs
 // best with K blocks of 64 in two stages, dW and dX on the 256x256 tile with K blocks of 32 in four stages.
 // The smaller tiles are sized for two workgroups per CU.  A launch with no more tiles than CUs has one, and is
 // then bound by the latency of its loads (1024x4096x8192 for dW on 128x128 tiles: 41 GB/s per CU with 48 KB in
 // flight); it takes the CU's whole LDS for K blocks of 64 in three or four stages: the forward launch over two 256-column
 // slices with K = 4096 64 -> 52 us.  The 128x128 tile runs on the four-wave kernel (gemm_w4_128_kernel).
-// The last two run on the four-wave kernel alone, in the layouts where they were measured (0: not offered).  They fill
+// 224 x 256 and 256 x 160 run on the four-wave kernel alone, in the layouts where they were measured (0: not offered).  They fill
 // rounds that whole tiles leave partly empty; the smaller the tile the more bytes from L2 each MFMA needs, which is
 // what the penalties are (7 % more for 224 x 256, 30 % more for 256 x 160).  dW of 2560 x 5120 over 16384 tokens: 200
 // tiles of 256 rows 412 us, 240 of 224 rows 382 us.  8192 x 1280 over K = 2560: 160 tiles of 256 columns 60 us, 256
 // tiles of 160 columns 51 us (dX 48 us); where they only replace full rounds the narrow tiles lose (16384 x 2560 over
 // K = 2560 in 4 rounds 240 us, against 196 us for two rounds of large tiles and a remainder).
-// The last two are for dX launches of at most one tile per CU: narrow slices, and few rows.  Both operands keep whole rows of
+// 128 x 160 and 64 x 160 are for dX launches of at most one tile per CU: narrow slices, and few rows.  Both operands keep whole rows of
 // K blocks in LDS, so any number of rows and columns fits.  us in 128 x 128 tiles / in these: 8192 x 320 over K = 10240 71 / 64,
 // 1000 x 5120 over 2560 38 / 29, 2048 x 1280 over 4096 31 / 28, 4096 x 128 over 2048 17 / 15.  (The forward, whose weight
 // tile takes 256 columns of LDS for 160, loses: 8192 x 320 over 10240 86 / 95.)
-// 256 x 160 over K = 768 and 1024, one tile to a CU, against two tiles of 128 x 128 or fewer of 256 x 256: dX of 4096 x 2304 30 / 24,
-// 4096 x 2560 25 / 21, 8192 x 1280 31 / 25.
+// 256 x 160 from K = 768 on, one tile to a CU, against two tiles of 128 x 128 or fewer of 256 x 256, us: dX of 4096 x 2304 over 768 24.5 /
+// 21.5, 4096 x 2560 over 768 25.0 / 21.1 and over 1024 29.5 / 24.5, 8192 x 1280 over 1024 29.5 / 24.5; forward of 4096 x 2304 over 768 26.6 /
+// 23.4, 4096 x 2560 over 768 25.6 / 22.7, over 1024 30.2 / 25.8 and over 1536 39.0 / 33.9, 3001 x 3200 over 1024 29.6 / 25.2.
 constexpr int kTileShapes = 8, kPricedShapes = 6;
 // lone: K = 2560 to 10240 against 256 x 256 tiles of the same K, one to a CU.  In place of two 128 x 128 tiles a CU, one
 // of 256 x 128 took 2048 x 4096 over K = 4096 from 76 to 65 us (dX 69 to 64), 3001 x 2560 over K = 2560 from 52 to 45.
@@ -372,6 +376,8 @@ constexpr TileShape kTiles[kTileShapes] = {{256, 256, {1.0, 1.0, 1.0}, {1.0, 1.0
                                            {256, 160, {1.30, 0.0, 1.28}, {1.30, 0.0, 1.28}},
                                            {128, 160, {0.0, 0.0, 0.0}, {0.0, 0.0, 1.35}},
                                            {64, 160, {0.0, 0.0, 0.0}, {0.0, 0.0, 1.70}}};
+// From which K 256 x 160 is launched, and from which it counts where slices are paired: how much workspace a call asks for hangs on
+// that, and must not change with the kernels.
 constexpr int kNarrowMinK = 768, kNarrowPricedK = 2048;
 
 constexpr int layout_kind(bool a_kcontig, bool b_kcontig) { return (a_kcontig && !b_kcontig) ? 0 : (!a_kcontig ? 1 : 2); }
