@@ -849,6 +849,38 @@ def test_every_tile_shape_at_ragged_sizes_gives_the_bits_of_the_checked_kernel(H
                 assert np.array_equal(got[name], want_bits[name]), f"{name} differs (tile {tile}, k {kk}, dim {dim})"
 
 
+@pytest.mark.parametrize("T,switches", [(64, {}), (768, {}), (768, {"tile": 0, "four_wave": 0}), (768, {"tile": 1}), (768, {"tile": 3})])
+def test_results_are_rounded_to_the_nearest_bf16_ties_to_even(H, T, switches, debug):
+    """Sums of two bf16 numbers that fp32 holds exactly: halfway between two results, next to halfway, of either sign and parity,
+    at powers of two, and beyond the largest bf16.  Whatever instruction rounds them, the bits are those of integer arithmetic."""
+    for name, value in switches.items():
+        debug(name, value)
+    rng = np.random.default_rng(99)
+    R, O = 32, 2048
+    a = rng.integers(0, 1 << 16, (R, O)).astype(np.uint32)
+    e = rng.integers(20, 255, (R, O)).astype(np.uint32)              # (sums and halves stay normal)
+    mant = np.where(rng.random((R, O)) < 0.2, rng.choice([0, 1, 126, 127], (R, O)), a & 0x7f).astype(np.uint32)
+    a = (a & 0x8000) | (e << 7) | mant
+    # half a unit in the last place of a, that times 1 + 2^-7 and 1 - 2^-8, a quarter, of either sign
+    b = np.where(rng.random((R, O)) < 0.5, 0x8000, 0).astype(np.uint32) | np.choose(
+        rng.integers(0, 4, (R, O)), [(e - 8) << 7, ((e - 8) << 7) + 1, ((e - 8) << 7) - 1, (e - 9) << 7]).astype(np.uint32)
+    exact = (a << 16).view(np.float32) + (b << 16).view(np.float32)
+    assert np.array_equal(exact.astype(np.float64), (a << 16).view(np.float32).astype(np.float64) + (b << 16).view(np.float32).astype(np.float64))
+    u = exact.view(np.uint32)
+    want = ((u + 0x7fff + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+    assert ((want & 0x7fff) == 0x7f80).any() and (u & 0xffff == 0x8000).mean() > 0.1
+    W = np.empty((2 * R, O), np.uint16)
+    W[0::2], W[1::2] = a, b
+    X = np.zeros((T, 2 * R), np.uint16)
+    rows = np.arange(T) % R
+    X[np.arange(T), 2 * rows] = X[np.arange(T), 2 * rows + 1] = 0x3f80   # 1.0
+    op = H.Operator(X, None, [W.reshape(-1)], O)
+    _announce("rounding", T, switches)
+    op.fwd(1)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_bits(op.Y), want[rows])
+
+
 @pytest.mark.parametrize("I,O,N", [
     (40, 264, 33),    # shards of 320: every row reaches over an end, at a column that changes with the row
     (264, 520, 60),   # 2288, 4.4 rows
